@@ -330,7 +330,7 @@ int mhd_last_dt(mhd_ctx* ctx, double* dt);
 /* Tile shape of the stage kernels: columns per workgroup, 0: 64x4,
  * 1: 32x8, 2: 16x16, 3: 16x8 (256 threads), 4: 64x8, 5: 32x16 (512
  * threads).  Any shape gives the same results (bit for bit); the default is
- * 32x8 (float32) or 16x8 (float64).  Other values: MHD_EINVAL.  Also sets
+ * chosen by mhd_init from the boxes.  Other values: MHD_EINVAL.  Also sets
  * pass F to this shape (mhd_set_final_tile).                               */
 int mhd_set_tile(mhd_ctx* ctx, int32_t tile);
 

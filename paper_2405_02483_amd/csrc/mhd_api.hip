@@ -40,7 +40,7 @@ struct mhd_ctx {
   std::vector<BoxDev> h_boxes;
   // workspace
   void* work = nullptr;            // work_arrays(p) * nelem elements
-  RedItem* d_red = nullptr;        // per-item partials of mhd_reductions (nitems)
+  RedItem* d_red = nullptr;        // per-item partials of mhd_reductions (nitems[ZC_A])
   RedTotal* d_tot = nullptr;       // their fold
   void* adj = nullptr;             // adjoint workspace (allocated on first use)
   size_t adj_bytes = 0;
@@ -50,10 +50,8 @@ struct mhd_ctx {
   VFused* d_fused = nullptr;       // prog->fused in device memory
   VStep* d_bsteps = nullptr;       // prog->bsteps in device memory
   // z-march stage kernels: work items, tile shape, Courant partials, dt
-  ZItem* d_items = nullptr;
-  int nitems = 0;
-  ZItem* d_fitems = nullptr;       // pass F's own work items (tile ftile)
-  int nfitems = 0;
+  ZItem* d_items[ZC_COUNT] = {};   // one table per class of passes
+  int nitems[ZC_COUNT] = {};
   int ftile = ZTILE_32x8;
   int tile = ZTILE_32x8;
   CPart* d_cpart = nullptr;
@@ -303,11 +301,11 @@ template <class T> static ZWork<T> make_zwork(const mhd_ctx* c) { return make_zw
 static ZLaunch make_zlaunch(const mhd_ctx* c, const Scratch& s) {
   ZLaunch L;
   L.boxes = c->d_boxes;
-  L.items = c->d_items;
-  L.nitems = c->nitems;
+  for (int q = 0; q < ZC_COUNT; ++q) {
+    L.items[q] = c->d_items[q];
+    L.nitems[q] = c->nitems[q];
+  }
   L.tile = c->tile;
-  L.fitems = c->d_fitems;
-  L.nfitems = c->nfitems;
   L.ftile = c->ftile;
   L.queue = s.queue;
   L.persistent = c->persistent;
@@ -323,32 +321,63 @@ static ZLaunch make_zlaunch(const mhd_ctx* c, const Scratch& s) {
 static ZLaunch make_zlaunch(const mhd_ctx* c) { return make_zlaunch(c, own_scratch(c)); }
 
 // Work items of the z-march kernels: tiles of TX x TY columns, z split into
-// chunks of about kZChunk planes (each chunk recomputes a few planes of
-// lead-in).
-#ifndef MHD_ZCHUNK
-#define MHD_ZCHUNK 128
-#endif
-static constexpr int kZChunk = MHD_ZCHUNK;
-// The z-range of an item: kZChunk planes, halved (down to kZChunkMin) while
-// the items would number fewer than kItemsPerCU per compute unit, so that
-// small boxes still fill the device.  The chunking changes no result: every
-// output plane sums its z contributions in the same order.
-static constexpr int kZChunkMin = 16, kItemsPerCU = 4;
-static void build_items(const mhd_ctx* c, int tile, std::vector<ZItem>& items) {
+// chunks (each chunk recomputes a few planes of lead-in, kZLead).  The
+// chunking changes no result: every output plane sums its z contributions in
+// the same order.
+static int zchunks(int nzt, int chunk) { return std::max(1, (nzt + chunk / 2) / chunk); }
+static long long ztiles(const BoxDev& d, int tile) {
   const int TX = ztile_x(tile), TY = ztile_y(tile);
-  auto nchunks = [](int nzt, int chunk) { return std::max(1, (nzt + chunk / 2) / chunk); };
-  int chunk = kZChunk;
-  for (;;) {
-    long long n = 0;
-    for (const BoxDev& d : c->h_boxes)
-      n += (long long)nchunks(d.nzt, chunk) * ((d.ny + TY - 1) / TY) * ((d.nx + TX - 1) / TX);
-    if (n >= (long long)kItemsPerCU * c->ncu || chunk / 2 < kZChunkMin) break;
-    chunk /= 2;
+  return (long long)((d.ny + TY - 1) / TY) * ((d.nx + TX - 1) / TX);
+}
+
+// The z-range of a class's chunks: every length from 1 to kZChunkMax planes
+// is priced as rounds of workgroups (the device holds `groups` of the
+// class's kernel at once) times the planes an item marches, lead-in
+// included, and the cheapest is taken.  Short marches win while the device
+// is not full, whole rounds after that.  With many rounds workgroups start
+// as others end and a partial last one costs its share only.  Measured per
+// RK stage against one length for all passes (halved from 128 to 16 planes
+// until there were 4 items a compute unit): 20x22x24 float64 339 -> 107 us,
+// 32^3 float64 402 -> 107, 64^3 float32 with walls 379 -> 168, 128^3
+// float32 502 -> 392 (with the 64x8 tile), 200x180x225 float64 3029 ->
+// 2670, 96 boxes of 48^3..96^3 float32 7159 -> 6512.  Beyond kZChunkMax
+// planes the tiles of a plane drift apart and their halos miss in L2 (512^3
+// float32, ms per step: 128 planes 57.4, 192 56.4, 256 59.7).
+static constexpr int kZChunkMax = 192;
+static int plan_chunk(const mhd_ctx* c, int tile, int cls) {
+  const double groups =
+      c->esize == 4 ? zclass_groups<float>(cls, tile, c->ncu) : zclass_groups<double>(cls, tile, c->ncu);
+  int best = 1, nzmax = 1;
+  for (const BoxDev& d : c->h_boxes) nzmax = std::max(nzmax, d.nzt);
+  double cost = 0.0;
+  for (int chunk = 1; chunk <= std::min(nzmax, kZChunkMax); ++chunk) {
+    double n = 0.0, planes = 0.0;
+    int longest = 0;
+    for (const BoxDev& d : c->h_boxes) {
+      const int nch = zchunks(d.nzt, chunk);
+      const double t = (double)ztiles(d, tile);
+      n += t * nch;
+      planes += t * (d.nzt + (double)nch * kZLead[cls]);
+      longest = std::max(longest, (d.nzt + nch - 1) / nch + kZLead[cls]);
+    }
+    const double x = n / groups, up = std::ceil(x);
+    const double rounds = x + (up - x) * std::min(1.0, 4.0 / up);
+    const double v = x <= 1.0 ? (double)longest : rounds * planes / n;
+    if (cost == 0.0 || v < cost) {
+      cost = v;
+      best = chunk;
+    }
   }
+  return best;
+}
+
+static void build_items(const mhd_ctx* c, int tile, int cls, std::vector<ZItem>& items) {
+  const int TX = ztile_x(tile), TY = ztile_y(tile);
+  const int chunk = plan_chunk(c, tile, cls);
   items.clear();
   for (int b = 0; b < (int)c->h_boxes.size(); ++b) {
     const BoxDev& d = c->h_boxes[b];
-    const int nch = nchunks(d.nzt, chunk);
+    const int nch = zchunks(d.nzt, chunk);
     for (int ch = 0; ch < nch; ++ch) {
       const int z0 = (int)((long long)d.nzt * ch / nch), z1 = (int)((long long)d.nzt * (ch + 1) / nch);
       for (int ty = 0; ty < d.ny; ty += TY)
@@ -366,37 +395,42 @@ static void build_items(const mhd_ctx* c, int tile, std::vector<ZItem>& items) {
   }
 }
 
-// Uploads the work items of a tile shape; *d and *n are replaced.  With
-// cpart (the items of every pass but F), also the per-item Courant and
-// reduction partials.
-static int upload_items(mhd_ctx* c, int tile, ZItem** d, int* n, CPart** cpart) {
-  std::vector<ZItem> items;
-  build_items(c, tile, items);
-  ZItem* di = nullptr;
+// Uploads the work items of classes c0..c1-1 in a tile shape, with the
+// per-item Courant and reduction partials of ZC_A; the context changes only
+// when everything has succeeded.
+static int upload_items(mhd_ctx* c, int tile, int c0, int c1) {
+  ZItem* di[ZC_COUNT] = {};
+  int n[ZC_COUNT] = {};
   CPart* dp = nullptr;
   RedItem* dr = nullptr;
-  hipError_t e;
-  if ((e = hipMalloc(&di, sizeof(ZItem) * items.size())) != hipSuccess ||
-      (cpart && (e = hipMalloc(&dp, sizeof(CPart) * items.size())) != hipSuccess) ||
-      (cpart && (e = hipMalloc(&dr, sizeof(RedItem) * items.size())) != hipSuccess)) {
-    (void)hipFree(di);
-    (void)hipFree(dp);
-    return fail(c, MHD_ENOMEM, std::string("work item tables: ") + hipGetErrorString(e));
+  hipError_t e = hipSuccess;
+  for (int q = c0; q < c1 && e == hipSuccess; ++q) {
+    std::vector<ZItem> items;
+    build_items(c, tile, q, items);
+    n[q] = (int)items.size();
+    e = hipMalloc(&di[q], sizeof(ZItem) * items.size());
+    if (e == hipSuccess && q == ZC_A) e = hipMalloc(&dp, sizeof(CPart) * items.size());
+    if (e == hipSuccess && q == ZC_A) e = hipMalloc(&dr, sizeof(RedItem) * items.size());
+    if (e == hipSuccess)
+      e = hipMemcpy(di[q], items.data(), sizeof(ZItem) * items.size(), hipMemcpyHostToDevice);
   }
-  if ((e = hipMemcpy(di, items.data(), sizeof(ZItem) * items.size(), hipMemcpyHostToDevice)) != hipSuccess) {
-    (void)hipFree(di);
+  if (e != hipSuccess) {
+    for (ZItem* d : di) (void)hipFree(d);
     (void)hipFree(dp);
     (void)hipFree(dr);
-    return hipfail(c, e, "work item upload");
+    return fail(c, e == hipErrorOutOfMemory ? MHD_ENOMEM : MHD_EHIP,
+                std::string("work item tables: ") + hipGetErrorString(e));
   }
   if (c->stream) (void)hipStreamSynchronize(c->stream);
-  (void)hipFree(*d);
-  *d = di;
-  *n = (int)items.size();
-  if (cpart) {
-    (void)hipFree(*cpart);
-    *cpart = dp;
+  for (int q = c0; q < c1; ++q) {
+    (void)hipFree(c->d_items[q]);
+    c->d_items[q] = di[q];
+    c->nitems[q] = n[q];
+  }
+  if (c0 == ZC_A) {
+    (void)hipFree(c->d_cpart);
     (void)hipFree(c->d_red);
+    c->d_cpart = dp;
     c->d_red = dr;
   }
   return MHD_OK;
@@ -404,17 +438,41 @@ static int upload_items(mhd_ctx* c, int tile, ZItem** d, int* n, CPart** cpart) 
 
 // Pass F alone (its kernels read no per-item partials).
 static int set_ftile(mhd_ctx* c, int tile) {
-  const int rc = upload_items(c, tile, &c->d_fitems, &c->nfitems, nullptr);
+  const int rc = upload_items(c, tile, ZC_F, ZC_F + 1);
   if (rc == MHD_OK) c->ftile = tile;
   return rc;
 }
 
 // Every pass.
 static int set_tile(mhd_ctx* c, int tile) {
-  int rc = upload_items(c, tile, &c->d_items, &c->nitems, &c->d_cpart);
-  if (rc != MHD_OK) return rc;
-  c->tile = tile;
-  return set_ftile(c, tile);
+  const int rc = upload_items(c, tile, 0, ZC_COUNT);
+  if (rc == MHD_OK) c->tile = c->ftile = tile;
+  return rc;
+}
+
+// The tiles a context starts with, from the columns they pad and the size.
+// Wide tiles read fewer halo columns per cell, narrow ones fill the device
+// on small boxes.  Measured per RK stage: float32 64x8 against 32x8, 128^3
+// 392 against 418 us, 256^3 2430 against 2662, but 96^3 (a third of the
+// wide tile's columns idle) 268 against 238.  float64 16x16 against 16x8:
+// 128^3 709 against 771 us (pass P 121 against 192), 200x180x225 2763
+// against 2867, 48^3 a few us behind; pass F in 32x8 there: 128^3 254
+// against 283 us, 200x180x225 1034 against 1095.
+static void start_tiles(const mhd_ctx* c, int& tile, int& ftile) {
+  const bool big = c->nelem >= 400000;
+  auto columns = [&](int t) {
+    double a = 0.0;
+    for (const BoxDev& d : c->h_boxes) a += (double)ztiles(d, t) * ztile_x(t) * ztile_y(t) * d.nzt;
+    return a;
+  };
+  if (c->esize == 8) {
+    tile = big && columns(ZTILE_16x16) <= 1.1 * columns(ZTILE_16x8) ? ZTILE_16x16 : ZTILE_16x8;
+    ftile = big && columns(ZTILE_32x8) <= 1.1 * columns(tile) ? ZTILE_32x8 : tile;
+  } else {
+    tile = columns(ZTILE_32x8) <= 1.1 * columns(ZTILE_16x8) ? ZTILE_32x8 : ZTILE_16x8;
+    if (big && columns(ZTILE_64x8) <= 1.1 * columns(tile)) tile = ZTILE_64x8;
+    ftile = tile;
+  }
 }
 
 template <class T> static P8<T> p8(void* const f[8]) {
@@ -505,8 +563,7 @@ void mhd_destroy(mhd_ctx* c) {
   (void)hipFree(c->d_pm);
   (void)hipFree(c->d_fused);
   (void)hipFree(c->d_bsteps);
-  (void)hipFree(c->d_items);
-  (void)hipFree(c->d_fitems);
+  for (ZItem* d : c->d_items) (void)hipFree(d);
   (void)hipFree(c->d_cpart);
   (void)hipFree(c->d_dt);
   (void)hipFree(c->d_queue);
@@ -739,9 +796,9 @@ int mhd_init(const mhd_params* p, void* hip_stream, mhd_ctx** out) {
     mhd_destroy(c);
     return MHD_ENOMEM;
   }
-  // float64 kernels hold twice the data per column: smaller default tile
-  const int tile = p->dtype == MHD_F64 ? ZTILE_16x8 : ZTILE_32x8;
-  if (set_tile(c, tile) != MHD_OK) {
+  int tile, ftile;
+  start_tiles(c, tile, ftile);
+  if (set_tile(c, tile) != MHD_OK || (ftile != tile && set_ftile(c, ftile) != MHD_OK)) {
     g_init_err = c->err;
     mhd_destroy(c);
     return MHD_ENOMEM;

@@ -356,7 +356,7 @@ int zresident_groups(const void* kern, int block, int ncu) { return resident_gro
 template <class T, int TX, int TY, bool PERS, unsigned FM, class G>
 static void zF_one(const G& grid, dim3 block, const ZLaunch& L, const ZStageArgs<T>& a, int* q) {
   hipLaunchKernelGGL((zF<T, TX, TY, PERS, FM>), grid((const void*)zF<T, TX, TY, PERS, FM>), block, 0,
-                     L.stream, L.boxes, L.fitems, L.nfitems, a.ztab, q, a.f, a.w, a.ph, a.du, a.du_mode, a.f_out,
+                     L.stream, L.boxes, L.items[ZC_F], L.nitems[ZC_F], a.ztab, q, a.f, a.w, a.ph, a.du, a.du_mode, a.f_out,
                      a.alpha, a.beta, a.dt_dev, a.dt_host);
 }
 // The momentum launch's mask with the Coriolis bit (8) set; others unchanged.
@@ -384,7 +384,7 @@ static void zF_launch(const G& grid, dim3 block, const ZLaunch& L, const ZStageA
 // Pass F, in its own tile shape (L.ftile) over its own work items.
 template <class T, int TX, int TY, bool PERS>
 static void launch_final_t(const ZLaunch& L, const ZStageArgs<T>& a, int* q) {
-  const int n = L.nfitems;
+  const int n = L.nitems[ZC_F];
   auto grid = [&](const void* kern) {
     if (!q) return dim3(8 * ((n + 7) / 8));
     const int r = std::min(n, resident_groups(kern, TX * TY, L.ncu));
@@ -410,6 +410,22 @@ void launch_final(const ZLaunch& L, const ZStageArgs<T>& a, int* q) {
     default: launch_final_t<T, 64, 4, PERS>(L, a, q); break;
   }
 }
+
+template <class T, int TX, int TY> static int final_groups_t(int ncu) {
+  return resident_groups((const void*)zF<T, TX, TY, false, kFMasks[0]>, TX * TY, ncu);
+}
+template <class T> int zfinal_groups(int tile, int ncu) {
+  switch (tile) {
+    case ZTILE_32x8: return final_groups_t<T, 32, 8>(ncu);
+    case ZTILE_16x16: return final_groups_t<T, 16, 16>(ncu);
+    case ZTILE_16x8: return final_groups_t<T, 16, 8>(ncu);
+    case ZTILE_64x8: return final_groups_t<T, 64, 8>(ncu);
+    case ZTILE_32x16: return final_groups_t<T, 32, 16>(ncu);
+    default: return final_groups_t<T, 64, 4>(ncu);
+  }
+}
+template int zfinal_groups<float>(int, int);
+template int zfinal_groups<double>(int, int);
 
 template void launch_final<float, false>(const ZLaunch&, const ZStageArgs<float>&, int*);
 template void launch_final<float, true>(const ZLaunch&, const ZStageArgs<float>&, int*);

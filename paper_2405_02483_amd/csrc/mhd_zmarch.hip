@@ -1382,22 +1382,22 @@ __global__ __launch_bounds__(kRedThreads) void k_red_final(const BoxDev* __restr
 template <class T, int TX, int TY>
 static void launch_zreduce_t(const ZLaunch& L, CP8<T> f, CP8<T> dfdt, const ZWork<T>& w, const Phys<T>& ph,
                              const T* ztab, RedItem* red, double nuB, double eta_const) {
-  const int n = L.nitems;
+  const int n = L.nitems[ZC_A];
   const dim3 grid(8 * ((n + 7) / 8)), block(TX * TY);
   if (smag_on(ph)) {
-    hipLaunchKernelGGL((zA1<T, TX, TY, false, true, true>), grid, block, 0, L.stream, L.boxes, L.items, n, ztab,
+    hipLaunchKernelGGL((zA1<T, TX, TY, false, true, true>), grid, block, 0, L.stream, L.boxes, L.items[ZC_A], n, ztab,
                        (int*)nullptr, f, ph, w, (CPart*)nullptr, dfdt, red);
-    hipLaunchKernelGGL((zS<T, TX, TY, false>), grid, block, 0, L.stream, L.boxes, L.items, n, ztab,
+    hipLaunchKernelGGL((zS<T, TX, TY, false>), grid, block, 0, L.stream, L.boxes, L.items[ZC_A], n, ztab,
                        (int*)nullptr, ph, w);
   } else {
-    hipLaunchKernelGGL((zA1<T, TX, TY, false, true>), grid, block, 0, L.stream, L.boxes, L.items, n, ztab,
+    hipLaunchKernelGGL((zA1<T, TX, TY, false, true>), grid, block, 0, L.stream, L.boxes, L.items[ZC_A], n, ztab,
                        (int*)nullptr, f, ph, w, (CPart*)nullptr, dfdt, red);
   }
   if (ph.terms & T_MAX5)
-    hipLaunchKernelGGL((zA2<T, TX, TY, false, true, 5>), grid, block, 0, L.stream, L.boxes, L.items, n, ztab,
+    hipLaunchKernelGGL((zA2<T, TX, TY, false, true, 5>), grid, block, 0, L.stream, L.boxes, L.items[ZC_A], n, ztab,
                        (int*)nullptr, w, (CPart*)nullptr, nuB, eta_const, red);
   else
-    hipLaunchKernelGGL((zA2<T, TX, TY, false, true>), grid, block, 0, L.stream, L.boxes, L.items, n, ztab,
+    hipLaunchKernelGGL((zA2<T, TX, TY, false, true>), grid, block, 0, L.stream, L.boxes, L.items[ZC_A], n, ztab,
                        (int*)nullptr, w, (CPart*)nullptr, nuB, eta_const, red);
 }
 
@@ -1413,7 +1413,7 @@ void launch_zreduce(const ZLaunch& L, CP8<T> f, CP8<T> dfdt, const ZWork<T>& w, 
     case ZTILE_32x16: launch_zreduce_t<T, 32, 16>(L, f, dfdt, w, ph, ztab, red, nuB, eta_const); break;
     default: launch_zreduce_t<T, 64, 4>(L, f, dfdt, w, ph, ztab, red, nuB, eta_const); break;
   }
-  hipLaunchKernelGGL(k_red_final, dim3(1), dim3(kRedThreads), 0, L.stream, L.boxes, L.items, L.nitems, red, Cdt, Cdtd,
+  hipLaunchKernelGGL(k_red_final, dim3(1), dim3(kRedThreads), 0, L.stream, L.boxes, L.items[ZC_A], L.nitems[ZC_A], red, Cdt, Cdtd,
                      Cdtr, tot);
 }
 
@@ -1430,10 +1430,11 @@ __global__ __launch_bounds__(128) void k_qreset(int* q) {
 
 template <class T, int TX, int TY, bool PERS>
 static void launch_zstage_m(const ZLaunch& L, const ZStageArgs<T>& a) {
-  const int n = L.nitems;
+  const int na = L.nitems[ZC_A], nq = L.nitems[ZC_Q], np = L.nitems[ZC_P];
+  const ZItem *ia = L.items[ZC_A], *iq = L.items[ZC_Q], *ip = L.items[ZC_P];
   const dim3 block(TX * TY);
   int* q = PERS ? L.queue : nullptr;
-  auto grid = [&](const void* kern) {
+  auto grid = [&](int n, const void* kern) {
     if (!q) return dim3(8 * ((n + 7) / 8));
     const int r = std::min(n, zresident_groups(kern, TX * TY, L.ncu));
     return dim3(std::max(8, r - r % 8));
@@ -1441,24 +1442,24 @@ static void launch_zstage_m(const ZLaunch& L, const ZStageArgs<T>& a) {
   if (q) hipLaunchKernelGGL(k_qreset, dim3(1), dim3(128), 0, L.stream, q);
   L.at(PASS_PRIM);
   if (smag_on(a.ph)) {
-    hipLaunchKernelGGL((zA1<T, TX, TY, PERS, false, true>), grid((const void*)zA1<T, TX, TY, PERS, false, true>),
-                       block, 0, L.stream, L.boxes, L.items, n, a.ztab, q, a.f, a.ph, a.w, a.cpart);
-    hipLaunchKernelGGL((zS<T, TX, TY, PERS>), grid((const void*)zS<T, TX, TY, PERS>), block, 0, L.stream,
-                       L.boxes, L.items, n, a.ztab, q ? q + 64 : q, a.ph, a.w);
+    hipLaunchKernelGGL((zA1<T, TX, TY, PERS, false, true>), grid(na, (const void*)zA1<T, TX, TY, PERS, false, true>),
+                       block, 0, L.stream, L.boxes, ia, na, a.ztab, q, a.f, a.ph, a.w, a.cpart);
+    hipLaunchKernelGGL((zS<T, TX, TY, PERS>), grid(na, (const void*)zS<T, TX, TY, PERS>), block, 0, L.stream,
+                       L.boxes, ia, na, a.ztab, q ? q + 64 : q, a.ph, a.w);
   } else {
-    hipLaunchKernelGGL((zA1<T, TX, TY, PERS>), grid((const void*)zA1<T, TX, TY, PERS>), block, 0, L.stream,
-                       L.boxes, L.items, n, a.ztab, q, a.f, a.ph, a.w, a.cpart);
+    hipLaunchKernelGGL((zA1<T, TX, TY, PERS>), grid(na, (const void*)zA1<T, TX, TY, PERS>), block, 0, L.stream,
+                       L.boxes, ia, na, a.ztab, q, a.f, a.ph, a.w, a.cpart);
   }
   L.at(PASS_MEAN3);
   if (a.ph.terms & T_MAX5)
-    hipLaunchKernelGGL((zA2<T, TX, TY, PERS, false, 5>), grid((const void*)zA2<T, TX, TY, PERS, false, 5>), block,
-                       0, L.stream, L.boxes, L.items, n, a.ztab, q ? q + 8 : q, a.w, a.cpart);
+    hipLaunchKernelGGL((zA2<T, TX, TY, PERS, false, 5>), grid(na, (const void*)zA2<T, TX, TY, PERS, false, 5>), block,
+                       0, L.stream, L.boxes, ia, na, a.ztab, q ? q + 8 : q, a.w, a.cpart);
   else
-    hipLaunchKernelGGL((zA2<T, TX, TY, PERS>), grid((const void*)zA2<T, TX, TY, PERS>), block, 0, L.stream,
-                       L.boxes, L.items, n, a.ztab, q ? q + 8 : q, a.w, a.cpart);
+    hipLaunchKernelGGL((zA2<T, TX, TY, PERS>), grid(na, (const void*)zA2<T, TX, TY, PERS>), block, 0, L.stream,
+                       L.boxes, ia, na, a.ztab, q ? q + 8 : q, a.w, a.cpart);
   if (a.cpart) {
     L.at(PASS_REDUCE);
-    hipLaunchKernelGGL(k_dt, dim3(1), dim3(256), 0, L.stream, L.boxes, L.items, n, a.cpart, a.Cdt,
+    hipLaunchKernelGGL(k_dt, dim3(1), dim3(256), 0, L.stream, L.boxes, ia, na, a.cpart, a.Cdt,
                        a.Cdtd, a.nuB, a.eta_const, a.dt_dev);
     L.at(PASS_MEAN3);   // the plane means below are booked with A2 in every stage
   }
@@ -1477,48 +1478,48 @@ static void launch_zstage_m(const ZLaunch& L, const ZStageArgs<T>& a) {
   }
   L.at(PASS_EDGES);
   // the optional passes run in grid mode (their own launches, no queue)
-  const dim3 gq(8 * ((n + 7) / 8));
+  const dim3 gq(8 * ((nq + 7) / 8)), gp(8 * ((np + 7) / 8));
   // second-order switch: the flags of every cell; pass P then writes the
   // second-order div u that pass Q's tau_zz takes, so P goes first
   ZWork<T> wq = a.w;
   const bool o2 = (a.ph.terms & T_ORDER2) && (a.ph.terms & T_VISC);
   if (o2) {
-    hipLaunchKernelGGL((zRough<T, TX, TY, false>), gq, block, 0, L.stream, L.boxes, L.items, n, a.ztab,
+    hipLaunchKernelGGL((zRough<T, TX, TY, false>), gq, block, 0, L.stream, L.boxes, iq, nq, a.ztab,
                        (int*)nullptr, a.f, a.ph, a.w);
     wq.rgh = a.w.arr(WS_RGH);
   }
   // quenching: the raw stress (stress-only launches of P and Q), then its
   // quenched version, which P and Q below take in place of their own
   if ((a.ph.terms & T_QUENCH) && (a.ph.terms & T_VISC)) {
-    hipLaunchKernelGGL((zP<T, TX, TY, false, true>), gq, block, 0, L.stream, L.boxes, L.items, n, a.ztab,
+    hipLaunchKernelGGL((zP<T, TX, TY, false, true>), gp, block, 0, L.stream, L.boxes, ip, np, a.ztab,
                        (int*)nullptr, a.f, a.ph, wq);
-    hipLaunchKernelGGL((zQ<T, TX, TY, false, QM_EDGES | QM_TAU>), gq, block, 0, L.stream, L.boxes, L.items, n,
+    hipLaunchKernelGGL((zQ<T, TX, TY, false, QM_EDGES | QM_TAU>), gq, block, 0, L.stream, L.boxes, iq, nq,
                        a.ztab, (int*)nullptr, a.f, a.ph, wq, a.lnavg, a.w.lnpav);
-    hipLaunchKernelGGL((zQ<T, TX, TY, false, QM_ZC | QM_TAU>), gq, block, 0, L.stream, L.boxes, L.items, n,
+    hipLaunchKernelGGL((zQ<T, TX, TY, false, QM_ZC | QM_TAU>), gq, block, 0, L.stream, L.boxes, iq, nq,
                        a.ztab, (int*)nullptr, a.f, a.ph, wq, a.lnavg, a.w.lnpav);
-    hipLaunchKernelGGL((zQn<T, TX, TY>), dim3(gq.x, TAU_COUNT), block, 0, L.stream, L.boxes, L.items, n, a.ztab,
+    hipLaunchKernelGGL((zQn<T, TX, TY>), dim3(gq.x, TAU_COUNT), block, 0, L.stream, L.boxes, iq, nq, a.ztab,
                        a.ph, a.w);
     wq.tq = a.w.arr(WS_TQ0);
   }
   auto launch_p = [&]() {
     L.at(PASS_CF);
-    hipLaunchKernelGGL((zP<T, TX, TY, PERS>), grid((const void*)zP<T, TX, TY, PERS>), block, 0, L.stream,
-                       L.boxes, L.items, n, a.ztab, q ? q + 24 : q, a.f, a.ph, wq);
+    hipLaunchKernelGGL((zP<T, TX, TY, PERS>), grid(np, (const void*)zP<T, TX, TY, PERS>), block, 0, L.stream,
+                       L.boxes, ip, np, a.ztab, q ? q + 24 : q, a.f, a.ph, wq);
   };
   if (o2) {
     launch_p();
     L.at(PASS_EDGES);
   }
-  hipLaunchKernelGGL((zQ<T, TX, TY, PERS, QM_EDGES>), grid((const void*)zQ<T, TX, TY, PERS, QM_EDGES>), block, 0,
-                     L.stream, L.boxes, L.items, n, a.ztab, q ? q + 16 : q, a.f, a.ph, wq, a.lnavg,
+  hipLaunchKernelGGL((zQ<T, TX, TY, PERS, QM_EDGES>), grid(nq, (const void*)zQ<T, TX, TY, PERS, QM_EDGES>), block, 0,
+                     L.stream, L.boxes, iq, nq, a.ztab, q ? q + 16 : q, a.f, a.ph, wq, a.lnavg,
                      a.w.lnpav);
   if (lnp)
-    hipLaunchKernelGGL((zQ<T, TX, TY, PERS, QM_ZC | QM_LNP>), grid((const void*)zQ<T, TX, TY, PERS, QM_ZC | QM_LNP>),
-                       block, 0, L.stream, L.boxes, L.items, n, a.ztab, q ? q + 32 + 8 * kNFMasks : q, a.f, a.ph,
+    hipLaunchKernelGGL((zQ<T, TX, TY, PERS, QM_ZC | QM_LNP>), grid(nq, (const void*)zQ<T, TX, TY, PERS, QM_ZC | QM_LNP>),
+                       block, 0, L.stream, L.boxes, iq, nq, a.ztab, q ? q + 32 + 8 * kNFMasks : q, a.f, a.ph,
                        wq, a.lnavg, a.w.lnpav);
   else
-    hipLaunchKernelGGL((zQ<T, TX, TY, PERS, QM_ZC>), grid((const void*)zQ<T, TX, TY, PERS, QM_ZC>), block, 0,
-                       L.stream, L.boxes, L.items, n, a.ztab, q ? q + 32 + 8 * kNFMasks : q, a.f, a.ph, wq,
+    hipLaunchKernelGGL((zQ<T, TX, TY, PERS, QM_ZC>), grid(nq, (const void*)zQ<T, TX, TY, PERS, QM_ZC>), block, 0,
+                       L.stream, L.boxes, iq, nq, a.ztab, q ? q + 32 + 8 * kNFMasks : q, a.f, a.ph, wq,
                        a.lnavg, a.w.lnpav);
   if (!o2) launch_p();
   L.at(PASS_FINAL);
@@ -1545,6 +1546,26 @@ void launch_zstage(const ZLaunch& L, const ZStageArgs<T>& a) {
       break;
   }
 }
+
+template <class T, int TX, int TY> static int class_groups_t(int cls, int ncu) {
+  const void* k = cls == ZC_A ? (const void*)zA1<T, TX, TY, false>
+                              : (cls == ZC_Q ? (const void*)zQ<T, TX, TY, false, QM_EDGES>
+                                             : (const void*)zP<T, TX, TY, false>);
+  return zresident_groups(k, TX * TY, ncu);
+}
+template <class T> int zclass_groups(int cls, int tile, int ncu) {
+  if (cls == ZC_F) return zfinal_groups<T>(tile, ncu);
+  switch (tile) {
+    case ZTILE_32x8: return class_groups_t<T, 32, 8>(cls, ncu);
+    case ZTILE_16x16: return class_groups_t<T, 16, 16>(cls, ncu);
+    case ZTILE_16x8: return class_groups_t<T, 16, 8>(cls, ncu);
+    case ZTILE_64x8: return class_groups_t<T, 64, 8>(cls, ncu);
+    case ZTILE_32x16: return class_groups_t<T, 32, 16>(cls, ncu);
+    default: return class_groups_t<T, 64, 4>(cls, ncu);
+  }
+}
+template int zclass_groups<float>(int, int, int);
+template int zclass_groups<double>(int, int, int);
 
 template void launch_zstage<float>(const ZLaunch&, const ZStageArgs<float>&);
 template void launch_zstage<double>(const ZLaunch&, const ZStageArgs<double>&);

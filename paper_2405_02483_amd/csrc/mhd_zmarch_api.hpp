@@ -75,14 +75,26 @@ constexpr int kPlaneSlices = 8;
 // Item queues of the persistent mode: 8 counters per launch, at most 9 launches.
 constexpr int kQueueInts = 72;
 
+// Work-item tables of a stage, one per class of passes: the classes differ
+// in the planes a chunk recomputes before its first output and in how many
+// workgroups fit on a compute unit, so each has its own z-chunks (plan_chunk).
+enum ZClass : int {
+  ZC_A = 0,   // A1, S, A2 and the reductions (they share the per-item partials)
+  ZC_Q,       // Q, the roughness and quench passes
+  ZC_P,       // P
+  ZC_F,       // F, in its own tile shape
+  ZC_COUNT
+};
+// planes a chunk's march takes besides its own (P marches only its own: one
+// plane's worth of set-up)
+constexpr int kZLead[ZC_COUNT] = {9, 5, 1, 5};
+
 struct ZLaunch {
   const BoxDev* boxes;
-  const ZItem* items;     // device
-  int nitems;
-  int tile;               // ZTile of these items
-  const ZItem* fitems;    // device: the work items of pass F, of tile ftile
-  int nfitems;
-  int ftile;
+  const ZItem* items[ZC_COUNT];   // device
+  int nitems[ZC_COUNT];
+  int tile;               // ZTile of every class but ZC_F
+  int ftile;              // ZTile of ZC_F
   int* queue;             // device, kQueueInts counters (persistent mode)
   int persistent;         // 0: one workgroup per item; 1: item queues
   int ncu;                // compute units of the device
@@ -120,6 +132,9 @@ template <class T> void launch_zstage(const ZLaunch& L, const ZStageArgs<T>& a);
 template <class T, bool PERS> void launch_final(const ZLaunch& L, const ZStageArgs<T>& a, int* q);
 // Workgroups of a kernel that fit on the device at once (cached per kernel).
 int zresident_groups(const void* kern, int block, int ncu);
+// The same for the heaviest kernel of a class of passes in a tile shape.
+template <class T> int zclass_groups(int cls, int tile, int ncu);
+template <class T> int zfinal_groups(int tile, int ncu);   // ZC_F
 
 // mhd_reductions: passes A1 and A2 in their reduction instantiations over
 // the work items of L (grid mode), then the fold of the per-item partials
