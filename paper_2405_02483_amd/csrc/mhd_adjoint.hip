@@ -1,620 +1,101 @@
-// Discrete adjoint of the right-hand side (see mhd_adjoint.hpp): the program
-// builder (host) and the forward / transposed whole-box kernels.
+// (dF/df)^T w of the right-hand side F (eqs. mass, mom, ien, indu with
+// itv, ohm, vdiss, RMnu, nuij, ediffuse and the optional terms), in
+// hand-fused passes over the cells of all boxes.
+//
+// The passes follow the right-hand side backwards.  Every flux, edge
+// quantity and heating term of F is differenced or interpolated once more
+// before it reaches an output, so its cotangent at its own position is a
+// stencil of w and is formed there, in registers.  What is stored are the
+// cotangents of the interpolated and differenced inputs at each position
+// (10 per cell edge, 6 per face, 4 per axis at the centre); the next pass
+// gathers their transposed stencils into velocities, momenta, B, energy and
+// density.  On a periodic axis the transpose of an interpolation is the
+// interpolation of the opposite stagger, that of a derivative minus the
+// derivative of the opposite stagger; near the ends of a wall-bounded z
+// axis the gather runs over the columns of the box's coefficient table.
+//
+// One thread per cell; a workgroup takes 256 consecutive cells, and
+// consecutive workgroups of an XCD take consecutive cells, so that the
+// stencils' repeated reads hit in L1 (x, y) and in that XCD's L2 (z).
+//
+// The passes are bound by the arrays they stream: about 95 with the core
+// terms, some 190 reads and writes per cell and stage, against 1700 of an
+// operation-by-operation program, which this replaced (each operation a
+// pass over 2 to 5 arrays, 160 launches a stage).  One step's adjoint:
+// 128^3 float32 23.06 -> 3.33 ms, 64^3 float32 with walls and every
+// optional term 14.37 -> 2.35 ms; a 6-step float64 rollout of 48^3 with its
+// gradient 63.2 -> 9.54 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cmath>
 
 #include "mhd_adjoint.hpp"
 
 namespace smhd {
-
-// ---------------------------------------------------------------------------
-// Program builder.  Follows the right-hand side of eqs. mass, mom, ien, indu,
-// ohm, itv, vdiss, RMnu, nuij and ediffuse term by term, with the readings
-// of the float64 reference (dissipative viscous sign, eta a magnetic
-// diffusivity, shock viscosity nu2 h max(0, -div u), edge viscosities by
-// averaging ln nu, the energy-diffusion flux without the extra grid step).
 namespace {
 
-constexpr int ZERO = -1;   // the zero field: never stored, folded away
+// Workspace arrays.  Vectors take three (x, y, z); edge quantities 10 per
+// edge direction (EdgeQ), edge c running along axis c between the axes
+// a = c + 1 and b = c + 2 (cyclic).
+enum VArr : int {
+  VA_U = 0,                 // face velocities
+  VA_R = VA_U + 3,          // face densities dn_a(rho)
+  VA_EM = VA_R + 3, VA_LEM, // e / rho and its log
+  VA_XWE, VA_YWE,           // x and y transposes of w_e's centre interpolation
+  VA_NT, VA_LNT,            // <nu> (floored) and its log
+  VA_XL, VA_YL,             // dn_x, dn_y of ln <nu>
+  VA_EDGE,                  // 30
+  VA_XE = VA_EDGE + 30,     // cotangents of dn_a(e), dn_a(nu), dn_a(e_m), ddn_a(ln e_m)
+  VA_XNT = VA_XE + 3, VA_XEM = VA_XNT + 3, VA_DLEM = VA_XEM + 3,
+  VA_RF = VA_DLEM + 3,      // of the face densities, from the energy diffusion
+  VA_UF = VA_RF + 3,        // of the face velocities, from the energy flux
+  VA_XLB = VA_UF + 3, VA_YLB,   // of dn_x, dn_y of ln <nu>
+  VA_NTB,                   // of <nu>
+  VA_MB0, VA_MB1,           // of the maxima, in turn
+  VA_CP, VA_CU = VA_CP + 3, VA_SD = VA_CU + 3, VA_CB = VA_SD + 3,   // of up_a(p_a, u_a), dup_a(u_a), up_a(B_a)
+  VA_RHOB = VA_CB + 3, VA_EB,   // pointwise parts of rho and e
+  VA_RB,                    // of the face densities
+  VA_MX = VA_RB + 3,        // speed-like viscosity and its maxima so far
+  VA_CORE = VA_MX + 4,
+  VA_MX5 = VA_CORE,         // three more with T_MAX5
+  VA_LNP = VA_MX5 + 3,      // T_LNP: ln P, cotangents of dn_a, ddn_a of it
+  VA_QI = VA_LNP + 1, VA_QD = VA_QI + 3,
+  VA_DVB = VA_QD + 3,       // T_DIVB: of div B
+  VA_EDX,                   // T_EDIFFAV: of the plane mean's log, cell by cell
+  VA_SE,                    // T_SMAG: shear on the edges, then its centre value and cotangent
+  VA_SC = VA_SE + 3,
+  VA_TAU = VA_SC + 3,       // T_QUENCH: raw stress, q, its maxima, cotangents (6 each)
+  VA_QQ = VA_TAU + 6, VA_Q1 = VA_QQ + 6, VA_Q2 = VA_Q1 + 6, VA_Q3 = VA_Q2 + 6, VA_TB = VA_Q3 + 6,
+  VA_QB0 = VA_TB + 6, VA_QB1 = VA_QB0 + 6,
+  VA_RGH = VA_QB1 + 6,      // T_ORDER2: rough cells, flags, second-order parts of the strain's cotangents
+  VA_RGF, VA_HS2, VA_SD2 = VA_HS2 + 3,
+  VA_COUNT = VA_SD2 + 3
+};
+enum EdgeQ : int { EQ_UAB = 0, EQ_UBA, EQ_HS, EQ_PAB, EQ_PBA, EQ_BAB, EQ_BBA, EQ_J, EQ_RHO, EQ_LNU, EQ_COUNT };
 
-struct Builder {
-  VProgram P;
+constexpr int X = 0, Y = 1, Z = 2;
 
-  int emit(int op, int a, int b, int c, double k, int geo, int ax, int fam, int form) {
-    VInstr I{};
-    I.op = op;
-    I.out = P.nslots++;
-    I.a = a;
-    I.b = b;
-    I.c = c;
-    I.k = k;
-    I.geo = geo;
-    I.ax = ax;
-    I.fam = fam;
-    I.form = form;
-    P.code.push_back(I);
-    return I.out;
-  }
-  int un(int op, int a, double k = 0.0, int geo = G_ONE) {
-    return emit(op, a, ZERO, ZERO, k, geo, 0, 0, 0);
-  }
-  int st(int a, int ax, int fam, int form) {
-    return a == ZERO ? ZERO : emit(V_STEN, a, ZERO, ZERO, 0.0, G_ONE, ax, fam, form);
-  }
-  // staggered operators (eqs. deriv, interp): fam 0 interpolation, 1 derivative
-  int xdn(int a) { return st(a, VX, 0, 0); }
-  int xup(int a) { return st(a, VX, 0, 1); }
-  int ydn(int a) { return st(a, VY, 0, 0); }
-  int yup(int a) { return st(a, VY, 0, 1); }
-  int zdn(int a) { return st(a, VZ, 0, 0); }
-  int zup(int a) { return st(a, VZ, 0, 1); }
-  int ddxdn(int a) { return st(a, VX, 1, 0); }
-  int ddxup(int a) { return st(a, VX, 1, 1); }
-  int ddydn(int a) { return st(a, VY, 1, 0); }
-  int ddyup(int a) { return st(a, VY, 1, 1); }
-  int ddzdn(int a) { return st(a, VZ, 1, 0); }
-  int ddzup(int a) { return st(a, VZ, 1, 1); }
-
-  int neg(int a) { return a == ZERO ? ZERO : un(V_SCALE, a, -1.0); }
-  int add(int a, int b) {
-    if (a == ZERO) return b;
-    if (b == ZERO) return a;
-    return emit(V_ADD, a, b, ZERO, 0.0, G_ONE, 0, 0, 0);
-  }
-  int sub(int a, int b) {
-    if (b == ZERO) return a;
-    if (a == ZERO) return neg(b);
-    return emit(V_SUB, a, b, ZERO, 0.0, G_ONE, 0, 0, 0);
-  }
-  int mul(int a, int b) {
-    if (a == ZERO || b == ZERO) return ZERO;
-    return emit(V_MUL, a, b, ZERO, 0.0, G_ONE, 0, 0, 0);
-  }
-  int div(int a, int b) {   // b is never the zero field
-    if (a == ZERO) return ZERO;
-    return emit(V_DIV, a, b, ZERO, 0.0, G_ONE, 0, 0, 0);
-  }
-  int scale(int a, double k, int geo = G_ONE) { return a == ZERO ? ZERO : un(V_SCALE, a, k, geo); }
-  int divc(int a, double k) { return a == ZERO ? ZERO : un(V_DIVC, a, k); }
-  int fsqrt(int a) { return un(V_SQRT, a); }
-  int flog(int a) { return un(V_LOG, a); }
-  int fexp(int a) { return un(V_EXP, a); }
-  int relu(int a) { return a == ZERO ? ZERO : un(V_RELU, a); }
-  int floor_at(int a, double k) { return un(V_FLOOR, a, k); }
-  int norm3(int a, int b, int c) { return emit(V_NORM3, a, b, c, 0.0, G_ONE, 0, 0, 0); }
-  int max3(int a, int ax) { return emit(V_MAX3, a, ZERO, ZERO, 0.0, G_ONE, ax, 0, 0); }
-  int mean3(int a, int ax) { return emit(V_MEAN3, a, ZERO, ZERO, 0.0, G_ONE, ax, 0, 0); }
-  int fill(double k, int geo = G_ONE) { return emit(V_FILL, ZERO, ZERO, ZERO, k, geo, 0, 0, 0); }
-  int fabs_(int a) { return un(V_ABS, a); }
-  int d2(int a, int ax) { return emit(V_D2, a, ZERO, ZERO, 0.0, G_ONE, ax, 0, 0); }
-  int sdiv(int a, int b) { return emit(V_SDIV, a, b, ZERO, 0.0, G_ONE, 0, 0, 0); }
-  int cap(int a, double k) { return un(V_CAP, a, k); }
-  // second-order staggered derivative (form 0 dn, 1 up)
-  int dd2(int a, int ax, int form) { return emit(V_STEN, a, ZERO, ZERO, 0.0, G_ONE, ax, 2, form); }
-  // 1 where a cell touching position `kind` is rough, else 0 (no derivative)
-  int rough(int lnr, int lne, double lim, int kind) {
-    return emit(V_ROUGH, lnr, lne, ZERO, lim, G_ONE, kind, 0, 0);
-  }
-  int sel(int a, int b, int m) { return emit(V_SEL, a, b, m, 0.0, G_ONE, 0, 0, 0); }
-  int pmean(int a) { return emit(V_PMEAN, a, ZERO, ZERO, 0.0, G_ONE, 0, 0, 0); }
+template <class T> struct VK {
+  const BoxDev* boxes;
+  const Blk* tab;
+  int nblk;
+  CP8<T> s, w;
+  P8<T> g;
+  T* base;
+  long long stride;
+  const T* zt;
+  const double* pm;
+  int nplanes;
+  Phys<T> ph;
+  double nu2, c_smag, dt;
+  double c_divb;
+  int acc;
+  int nmax;                 // maxima in the chain (3, or 6 with T_MAX5)
 };
 
-// Drops instructions whose results never reach an output, renumbers slots
-// densely (0..7 stay the state) and makes every output a slot of its own
-// that no instruction reads.
-VProgram finish(Builder& B, int out[8]) {
-  for (int v = 0; v < 8; ++v) {
-    if (out[v] == ZERO) out[v] = B.fill(0.0);
-    bool shared = out[v] < 8;
-    for (int w = 0; w < v; ++w) shared |= out[w] == out[v];
-    for (const auto& I : B.P.code) shared |= I.a == out[v] || I.b == out[v] || I.c == out[v];
-    if (shared) out[v] = B.un(V_SCALE, out[v], 1.0);
-  }
-  VProgram& P = B.P;
-  std::vector<char> live(P.nslots, 0);
-  for (int v = 0; v < 8; ++v) live[out[v]] = 1;
-  std::vector<char> keep(P.code.size(), 0);
-  for (int n = (int)P.code.size() - 1; n >= 0; --n) {
-    const VInstr& I = P.code[n];
-    if (!live[I.out]) continue;
-    keep[n] = 1;
-    for (int s : {I.a, I.b, I.c})
-      if (s >= 0) live[s] = 1;
-  }
-  std::vector<int> remap(P.nslots, -1);
-  for (int s = 0; s < 8; ++s) remap[s] = s;
-  VProgram R;
-  R.nslots = 8;
-  for (size_t n = 0; n < P.code.size(); ++n) {
-    if (!keep[n]) continue;
-    VInstr I = P.code[n];
-    remap[I.out] = R.nslots++;
-    I.out = remap[I.out];
-    I.a = I.a >= 0 ? remap[I.a] : ZERO;
-    I.b = I.b >= 0 ? remap[I.b] : ZERO;
-    I.c = I.c >= 0 ? remap[I.c] : ZERO;
-    R.code.push_back(I);
-  }
-  for (int v = 0; v < 8; ++v) R.out[v] = remap[out[v]];
-  return R;
-}
-
-}  // namespace
-
-VProgram build_rhs_program(const mhd_params& p, double dt) {
-  Builder B;
-  const unsigned T = p.terms;
-  const int rho = 0, px = 1, py = 2, pz = 3, e = 4, bx = 5, by = 6, bz = 7;
-  const int Z = ZERO;
-
-  // primitives and the smoothed viscosity (Section 6.1.1, eq. RMnu)
-  const int P = B.scale(e, p.gamma - 1.0);
-  const int ux = B.div(px, B.xdn(rho)), uy = B.div(py, B.ydn(rho)), uz = B.div(pz, B.zdn(rho));
-  const int sxx = B.ddxup(ux), syy = B.ddyup(uy), szz = B.ddzup(uz);
-  const int D = B.add(B.add(sxx, syy), szz);
-  int nus;
-  if (p.nu_const > 0) {
-    nus = B.fill(p.nu_const, G_HINV);
-  } else {
-    const int ub = B.norm3(B.xup(ux), B.yup(uy), B.zup(uz));
-    const int bb = B.norm3(B.xup(bx), B.yup(by), B.zup(bz));
-    const int cs = B.fsqrt(B.div(B.scale(P, p.gamma), rho));
-    const int ca = B.div(bb, B.fsqrt(B.scale(rho, p.mu)));
-    nus = B.add(B.add(B.scale(ub, p.nu1), B.scale(B.add(cs, ca), p.nu3)),
-                B.scale(B.relu(B.neg(D)), p.nu2, G_H));
-    // Smagorinsky viscosity (eq. nusmag): the strain of eq. itv, its edge
-    // components interpolated to the centre
-    if (T & MHD_T_SMAG) {
-      const int cxy = B.yup(B.xup(B.scale(B.add(B.ddydn(ux), B.ddxdn(uy)), 0.5)));
-      const int cxz = B.zup(B.xup(B.scale(B.add(B.ddzdn(ux), B.ddxdn(uz)), 0.5)));
-      const int cyz = B.zup(B.yup(B.scale(B.add(B.ddzdn(uy), B.ddydn(uz)), 0.5)));
-      const int dia = B.add(B.add(B.mul(sxx, sxx), B.mul(syy, syy)), B.mul(szz, szz));
-      const int off = B.add(B.add(B.mul(cxy, cxy), B.mul(cxz, cxz)), B.mul(cyz, cyz));
-      const int s2 = B.scale(B.add(B.sub(dia, B.scale(B.mul(D, D), 1.0 / 3.0)), B.scale(off, 2.0)), 2.0);
-      nus = B.add(nus, B.scale(B.fsqrt(B.relu(s2)), p.c_smag, G_H));
-    }
-  }
-  // maximum over three (or, with MHD_T_MAX5, five) cells along each axis
-  auto mx = [&](int a, int ax) { return T & MHD_T_MAX5 ? B.max3(B.max3(a, ax), ax) : B.max3(a, ax); };
-  int m = mx(mx(mx(nus, VX), VY), VZ);
-  int nt = B.mean3(B.mean3(B.mean3(m, VX), VY), VZ);
-  nt = B.floor_at(nt, 1e-30);
-  const int em = B.div(e, rho);
-  const int lnt = B.flog(nt);
-
-  // edge viscosities and densities (eq. nuij)
-  const int nxy = B.scale(B.fexp(B.ydn(B.xdn(lnt))), 1.0, G_LXY);
-  const int nxz = B.scale(B.fexp(B.zdn(B.xdn(lnt))), 1.0, G_LXZ);
-  const int nyz = B.scale(B.fexp(B.zdn(B.ydn(lnt))), 1.0, G_LYZ);
-  const int rxy = B.ydn(B.xdn(rho)), rxz = B.zdn(B.xdn(rho)), ryz = B.zdn(B.ydn(rho));
-
-  // strain and stress (eq. itv)
-  int vxx = sxx, vyy = syy, vzz = szz, Dt = D;
-  int vxy = B.scale(B.add(B.ddydn(ux), B.ddxdn(uy)), 0.5);
-  int vxz = B.scale(B.add(B.ddzdn(ux), B.ddxdn(uz)), 0.5);
-  int vyz = B.scale(B.add(B.ddzdn(uy), B.ddydn(uz)), 0.5);
-  // second-order switch (Section 3 after eq. itv): where a touching cell is
-  // rough, the stress's strain and div u from second-order derivatives
-  if ((T & MHD_T_ORDER2) && (T & MHD_T_VISC)) {
-    const int lnr = B.flog(rho), lne = B.flog(em);
-    const int mc = B.rough(lnr, lne, p.d2_lim, 0), mxe = B.rough(lnr, lne, p.d2_lim, 1);
-    const int mye = B.rough(lnr, lne, p.d2_lim, 2), mze = B.rough(lnr, lne, p.d2_lim, 3);
-    const int s2xx = B.dd2(ux, VX, 1), s2yy = B.dd2(uy, VY, 1), s2zz = B.dd2(uz, VZ, 1);
-    Dt = B.sel(D, B.add(B.add(s2xx, s2yy), s2zz), mc);
-    vxx = B.sel(vxx, s2xx, mc);
-    vyy = B.sel(vyy, s2yy, mc);
-    vzz = B.sel(vzz, s2zz, mc);
-    vxy = B.sel(vxy, B.scale(B.add(B.dd2(ux, VY, 0), B.dd2(uy, VX, 0)), 0.5), mze);
-    vxz = B.sel(vxz, B.scale(B.add(B.dd2(ux, VZ, 0), B.dd2(uz, VX, 0)), 0.5), mye);
-    vyz = B.sel(vyz, B.scale(B.add(B.dd2(uy, VZ, 0), B.dd2(uz, VY, 0)), 0.5), mxe);
-  }
-  int txx = B.mul(B.mul(rho, B.scale(nt, 1.0, G_LX)), B.add(vxx, B.scale(Dt, p.c1)));
-  int tyy = B.mul(B.mul(rho, B.scale(nt, 1.0, G_LY)), B.add(vyy, B.scale(Dt, p.c1)));
-  int tzz = B.mul(B.mul(rho, B.scale(nt, 1.0, G_LZ)), B.add(vzz, B.scale(Dt, p.c1)));
-  int txy = B.mul(B.mul(rxy, nxy), vxy);
-  int txz = B.mul(B.mul(rxz, nxz), vxz);
-  int tyz = B.mul(B.mul(ryz, nyz), vyz);
-  // quenching (Section 6.2, eq. quench): each component times
-  // min(max over 3x3x3 of D2 / (|tau| + D2 / q_max), q_lim)
-  if ((T & MHD_T_QUENCH) && (T & MHD_T_VISC)) {
-    auto quench = [&](int t) {
-      const int s = B.add(B.add(B.fabs_(B.d2(t, VX)), B.fabs_(B.d2(t, VY))), B.fabs_(B.d2(t, VZ)));
-      const int q = B.sdiv(s, B.add(B.fabs_(t), B.divc(s, p.q_max)));
-      return B.mul(t, B.cap(B.max3(B.max3(B.max3(q, VX), VY), VZ), p.q_lim));
-    };
-    txx = quench(txx);
-    tyy = quench(tyy);
-    tzz = quench(tzz);
-    txy = quench(txy);
-    txz = quench(txz);
-    tyz = quench(tyz);
-  }
-
-  // current and electric field (eq. ohm)
-  const int jx = B.sub(B.ddydn(bz), B.ddzdn(by));
-  const int jy = B.sub(B.ddzdn(bx), B.ddxdn(bz));
-  const int jz = B.sub(B.ddxdn(by), B.ddydn(bx));
-  int etx, ety, etz;
-  if (p.eta_const > 0) {
-    etx = ety = etz = B.fill(p.eta_const);
-  } else {
-    etx = B.scale(nyz, p.nuB);
-    ety = B.scale(nxz, p.nuB);
-    etz = B.scale(nxy, p.nuB);
-  }
-  int ex = Z, ey = Z, ez = Z;
-  if (T & MHD_T_INDUCT) {
-    ex = B.sub(ex, B.sub(B.mul(B.zdn(uy), B.ydn(bz)), B.mul(B.ydn(uz), B.zdn(by))));
-    ey = B.sub(ey, B.sub(B.mul(B.xdn(uz), B.zdn(bx)), B.mul(B.zdn(ux), B.xdn(bz))));
-    ez = B.sub(ez, B.sub(B.mul(B.ydn(ux), B.xdn(by)), B.mul(B.xdn(uy), B.ydn(bx))));
-  }
-  if (T & MHD_T_RESIST) {
-    ex = B.add(ex, B.mul(etx, jx));
-    ey = B.add(ey, B.mul(ety, jy));
-    ez = B.add(ez, B.mul(etz, jz));
-  }
-
-  // mass (eq. mass)
-  int drho = Z;
-  if (T & MHD_T_CONT) drho = B.neg(B.add(B.add(B.ddxup(px), B.ddyup(py)), B.ddzup(pz)));
-
-  // momentum (eq. mom)
-  int dpx = Z, dpy = Z, dpz = Z;
-  if (T & MHD_T_ADV) {
-    dpx = B.sub(dpx, B.add(B.add(B.ddxdn(B.mul(B.xup(px), B.xup(ux))),
-                                 B.ddyup(B.mul(B.ydn(px), B.xdn(uy)))),
-                           B.ddzup(B.mul(B.zdn(px), B.xdn(uz)))));
-    dpy = B.sub(dpy, B.add(B.add(B.ddydn(B.mul(B.yup(py), B.yup(uy))),
-                                 B.ddzup(B.mul(B.zdn(py), B.ydn(uz)))),
-                           B.ddxup(B.mul(B.xdn(py), B.ydn(ux)))));
-    dpz = B.sub(dpz, B.add(B.add(B.ddzdn(B.mul(B.zup(pz), B.zup(uz))),
-                                 B.ddxup(B.mul(B.xdn(pz), B.zdn(ux)))),
-                           B.ddyup(B.mul(B.ydn(pz), B.zdn(uy)))));
-  }
-  if (T & MHD_T_PRES) {
-    if (T & MHD_T_LNP) {
-      // eq. pressure: exp(adn ln P_aver) exp(adn q) (ddadn q + ddadn ln P_aver),
-      // q = ln(P / P_aver), P_aver the mean of P over each z plane
-      const int lpa = B.flog(B.pmean(P));
-      const int q = B.sub(B.flog(P), lpa);
-      auto g = [&](int ax) {
-        return B.mul(B.mul(B.fexp(B.st(lpa, ax, 0, 0)), B.fexp(B.st(q, ax, 0, 0))),
-                     B.add(B.st(q, ax, 1, 0), B.st(lpa, ax, 1, 0)));
-      };
-      dpx = B.sub(dpx, g(VX));
-      dpy = B.sub(dpy, g(VY));
-      dpz = B.sub(dpz, g(VZ));
-    } else {
-      dpx = B.sub(dpx, B.ddxdn(P));
-      dpy = B.sub(dpy, B.ddydn(P));
-      dpz = B.sub(dpz, B.ddzdn(P));
-    }
-  }
-  if (T & MHD_T_LORENTZ) {
-    dpx = B.add(dpx, B.divc(B.sub(B.zup(B.mul(jy, B.xdn(bz))), B.yup(B.mul(jz, B.xdn(by)))), p.mu));
-    dpy = B.add(dpy, B.divc(B.sub(B.xup(B.mul(jz, B.ydn(bx))), B.zup(B.mul(jx, B.ydn(bz)))), p.mu));
-    dpz = B.add(dpz, B.divc(B.sub(B.yup(B.mul(jx, B.zdn(by))), B.xup(B.mul(jy, B.zdn(bx)))), p.mu));
-  }
-  if (T & MHD_T_VISC) {
-    dpx = B.add(B.add(B.add(dpx, B.ddxdn(txx)), B.ddyup(txy)), B.ddzup(txz));
-    dpy = B.add(B.add(B.add(dpy, B.ddydn(tyy)), B.ddzup(tyz)), B.ddxup(txy));
-    dpz = B.add(B.add(B.add(dpz, B.ddzdn(tzz)), B.ddxup(txz)), B.ddyup(tyz));
-  }
-  if (T & MHD_T_GRAV) dpz = B.sub(dpz, B.scale(B.zdn(rho), p.gz));
-  // Coriolis force (eq. mom): -2 Omega x p, each component on its own face
-  if (T & MHD_T_CORI) {
-    const double wx = 2.0 * p.omega[0], wy = 2.0 * p.omega[1], wz = 2.0 * p.omega[2];
-    auto term = [&](int acc, int v, double w) { return w == 0.0 ? acc : B.add(acc, B.scale(v, w)); };
-    dpx = term(term(dpx, B.xdn(B.zup(pz)), -wy), B.xdn(B.yup(py)), wz);
-    dpy = term(term(dpy, B.ydn(B.xup(px)), -wz), B.ydn(B.zup(pz)), wx);
-    dpz = term(term(dpz, B.zdn(B.yup(py)), -wx), B.zdn(B.xup(px)), wy);
-  }
-
-  // internal energy (eqs. ien, vdiss, ediffuse)
-  int de = Z;
-  if (T & MHD_T_ADV)
-    de = B.sub(de, B.add(B.add(B.ddxup(B.mul(B.xdn(e), ux)), B.ddyup(B.mul(B.ydn(e), uy))),
-                         B.ddzup(B.mul(B.zdn(e), uz))));
-  if (T & MHD_T_PRES) de = B.sub(de, B.mul(P, D));
-  if (T & MHD_T_VISC) {
-    int qv = B.add(B.add(B.mul(txx, vxx), B.mul(tyy, vyy)), B.mul(tzz, vzz));
-    qv = B.add(qv, B.scale(B.add(B.add(B.yup(B.xup(B.mul(txy, vxy))), B.zup(B.xup(B.mul(txz, vxz)))),
-                                 B.zup(B.yup(B.mul(tyz, vyz)))),
-                           2.0));
-    de = B.add(de, qv);
-  }
-  if (T & MHD_T_RESIST) {
-    const int qj = B.divc(B.add(B.add(B.zup(B.yup(B.mul(B.mul(etx, jx), jx))),
-                                      B.zup(B.xup(B.mul(B.mul(ety, jy), jy)))),
-                                B.yup(B.xup(B.mul(B.mul(etz, jz), jz)))),
-                          p.mu);
-    de = B.add(de, qj);
-  }
-  if (T & MHD_T_EDIFF) {
-    const int lne = B.flog(em);
-    const int fx = B.mul(B.mul(B.mul(B.scale(B.xdn(rho), p.nuE), B.scale(B.xdn(nt), 1.0, G_LX)), B.xdn(em)),
-                         B.ddxdn(lne));
-    const int fy = B.mul(B.mul(B.mul(B.scale(B.ydn(rho), p.nuE), B.scale(B.ydn(nt), 1.0, G_LY)), B.ydn(em)),
-                         B.ddydn(lne));
-    // eq. ediffav: the z flux differentiates ln e_m - ln <e_m>_horiz
-    const int lnez = (T & MHD_T_EDIFFAV) ? B.sub(lne, B.flog(B.pmean(em))) : lne;
-    const int fz = B.mul(B.mul(B.mul(B.scale(B.zdn(rho), p.nuE), B.scale(B.zdn(nt), 1.0, G_LZF)), B.zdn(em)),
-                         B.ddzdn(lnez));
-    de = B.add(B.add(B.add(de, B.ddxup(fx)), B.ddyup(fy)), B.ddzup(fz));
-  }
-  // Newtonian cooling (eq. NewtonCool, eq. rhocool)
-  if (T & MHD_T_COOL) {
-    int q = B.scale(B.mul(rho, B.sub(em, B.fill(p.e_cool))), -1.0 / p.t_cool);
-    if (p.cool_cut == 1 || p.cool_cut == 2) {
-      const int r = B.scale(rho, 1.0 / p.rho_cool);
-      const int r2 = B.mul(r, r);
-      const int den = B.add(B.fill(1.0), r2);
-      q = B.mul(q, B.div(p.cool_cut == 1 ? r2 : B.fill(1.0), den));
-    }
-    de = B.add(de, q);
-  }
-
-  // induction (eq. indu)
-  int dbx = B.neg(B.sub(B.ddyup(ez), B.ddzup(ey)));
-  int dby = B.neg(B.sub(B.ddzup(ex), B.ddxup(ez)));
-  int dbz = B.neg(B.sub(B.ddxup(ey), B.ddyup(ex)));
-  // div B diffusion c_divb h_min^2 / dt grad(div B), with the step's dt
-  if ((T & MHD_T_DIVB) && dt > 0.0) {
-    const int divb = B.add(B.add(B.ddxup(bx), B.ddyup(by)), B.ddzup(bz));
-    auto kd = [&](int a) { return B.scale(B.scale(a, p.c_divb / dt, G_HMIN), 1.0, G_HMIN); };
-    dbx = B.add(dbx, kd(B.ddxdn(divb)));
-    dby = B.add(dby, kd(B.ddydn(divb)));
-    dbz = B.add(dbz, kd(B.ddzdn(divb)));
-  }
-
-  int out[8] = {drho, dpx, dpy, dpz, de, dbx, dby, dbz};
-  return finish(B, out);
-}
-
-// ---------------------------------------------------------------------------
-// Storage plan.
-VPlan plan_program(const VProgram& P) {
-  const int n = (int)P.code.size(), S = P.nslots;
-  // values some transpose reads: stored, never recycled
-  std::vector<char> keep(S, 0);
-  for (int s = 0; s < 8; ++s) keep[s] = 1;
-  for (const VInstr& I : P.code) {
-    switch (I.op) {
-      case V_MUL: keep[I.a] = keep[I.b] = 1; break;
-      case V_DIV: keep[I.b] = keep[I.out] = 1; break;
-      case V_SQRT: case V_EXP: keep[I.out] = 1; break;
-      case V_LOG: case V_RELU: case V_FLOOR: case V_MAX3: case V_ABS: case V_CAP: keep[I.a] = 1; break;
-      case V_SDIV: keep[I.b] = keep[I.out] = 1; break;
-      case V_SEL: keep[I.c] = 1; break;
-      case V_NORM3: keep[I.a] = keep[I.b] = keep[I.c] = keep[I.out] = 1; break;
-      default: break;
-    }
-  }
-  std::vector<int> last(S, -1), prod(S, -1);
-  for (int q = 0; q < n; ++q) {
-    prod[P.code[q].out] = q;
-    for (int x : {P.code[q].a, P.code[q].b, P.code[q].c})
-      if (x >= 0) last[x] = q;
-  }
-  // groups of up to kGroupMax operations; a neighbour operation reads its
-  // operand at neighbouring cells from memory, so it opens a new group only
-  // when that operand is made in the current one
-  VPlan R;
-  std::vector<int> gid(n), gend;
-  for (int q = 0; q < n; ++q) {
-    const VInstr& I = P.code[q];
-    const bool nb = I.op == V_STEN || I.op == V_MAX3 || I.op == V_MEAN3 || I.op == V_D2 || I.op == V_ROUGH ||
-                    I.op == V_PMEAN;
-    const bool dep = nb && !R.groups.empty() &&
-                     (prod[I.a] >= R.groups.back().first ||
-                      (I.op == V_ROUGH && prod[I.b] >= R.groups.back().first));
-    // the mask runs in a launch of its own (k_vm_rough): its eight-cell
-    // gathers would size the registers of every group's launch
-    const bool alone = I.op == V_ROUGH || I.op == V_PMEAN ||
-                       (q > 0 && (P.code[q - 1].op == V_ROUGH || P.code[q - 1].op == V_PMEAN));
-    if (q == 0 || dep || alone || q - R.groups.back().first == kGroupMax) {
-      if (!R.groups.empty()) gend.push_back(q);
-      R.groups.push_back({q, 0});
-    }
-    R.groups.back().count++;
-    gid[q] = (int)R.groups.size() - 1;
-  }
-  gend.push_back(n);
-  // a result is stored if a transpose or a later group reads it
-  std::vector<char> store(S, 0);
-  for (int s = 0; s < 8; ++s) store[s] = 1;
-  for (int q = 0; q < n; ++q) {
-    const int o = P.code[q].out;
-    store[o] = keep[o] || (last[o] >= gend[gid[q]]);
-  }
-  // value slots for the stored results; a slot is free again at the end of
-  // the group of its last reader (a group's first operation may read it at
-  // neighbouring cells while other cells of the group already write)
-  std::vector<int> vphys(S, -1), freev;
-  std::vector<std::vector<int>> release(R.groups.size());
-  for (int x = 0; x < 8; ++x) vphys[x] = x;
-  R.nval = 8;
-  R.steps.resize(n);
-  R.fused.resize(n);
-  for (int q = 0; q < n; ++q) {
-    const VInstr& I = P.code[q];
-    if (q == R.groups[gid[q]].first && gid[q] > 0) {
-      for (int ph : release[gid[q] - 1]) freev.push_back(ph);
-    }
-    int ph = -1;
-    if (store[I.out]) {
-      if (!freev.empty()) {
-        ph = freev.back();
-        freev.pop_back();
-      } else {
-        ph = R.nval++;
-      }
-    }
-    vphys[I.out] = ph;
-    VInstr F = I;
-    F.out = ph;
-    F.a = I.a >= 0 ? vphys[I.a] : -1;
-    F.b = I.b >= 0 ? vphys[I.b] : -1;
-    F.c = I.c >= 0 ? vphys[I.c] : -1;
-    R.steps[q].f = F;
-    VFused& G = R.fused[q];
-    G.f = F;
-    const int g0 = R.groups[gid[q]].first;
-    auto local = [&](int x) { return (x >= 0 && prod[x] >= g0 && prod[x] < q) ? prod[x] - g0 : -1; };
-    G.la = local(I.a);
-    G.lb = local(I.b);
-    G.lc = local(I.c);
-    G.pad = 0;
-    int done[3] = {-1, -1, -1}, nd = 0;
-    for (int x : {I.a, I.b, I.c}) {
-      if (x < 8 || keep[x] || last[x] != q || vphys[x] < 0) continue;
-      bool dup = false;
-      for (int m = 0; m < nd; ++m) dup |= done[m] == x;
-      if (dup) continue;
-      done[nd++] = x;
-      release[gid[q]].push_back(vphys[x]);
-    }
-  }
-  // the reverse sweep in groups (fills carry no transpose and are skipped);
-  // a neighbour transpose reads its output's cotangent at neighbouring cells,
-  // so it opens a new group only when a transpose of the current group has
-  // added to that cotangent (contrib: position of the last contribution)
-  std::vector<int> border, contrib(S, -1);
-  for (int q = n - 1; q >= 0; --q) {
-    const VInstr& I = P.code[q];
-    if (I.op == V_FILL) continue;
-    const bool nb = I.op == V_STEN || I.op == V_MAX3 || I.op == V_MEAN3 || I.op == V_D2;
-    const bool dep = nb && !R.bgroups.empty() && contrib[I.out] >= R.bgroups.back().first;
-    // a plane mean's transpose runs in launches of its own (a plane sum of
-    // the cotangent, then its broadcast)
-    const bool alone = I.op == V_PMEAN || (!border.empty() && P.code[border.back()].op == V_PMEAN);
-    if (R.bgroups.empty() || dep || alone || (int)border.size() - R.bgroups.back().first == kBGroupMax)
-      R.bgroups.push_back({(int)border.size(), 0});
-    R.bgroups.back().count++;
-    for (int x : {I.a, I.b, I.c})
-      if (x >= 0) contrib[x] = (int)border.size();
-    border.push_back(q);
-  }
-  // cotangents, allocated in the reverse sweep; a slot is free again at the
-  // end of the group of its last use (a group's first transpose may read it
-  // at neighbouring cells while other cells of the group already write)
-  std::vector<int> cphys(S, -1), freec, pend;
-  auto alloc = [&]() {
-    if (!freec.empty()) {
-      const int c = freec.back();
-      freec.pop_back();
-      return c;
-    }
-    return R.ncot++;
-  };
-  for (int v = 0; v < 8; ++v) R.cout[v] = cphys[P.out[v]] = alloc();
-  size_t bg = 0;
-  for (size_t u = 0; u < border.size(); ++u) {
-    if (bg < R.bgroups.size() && (int)u == R.bgroups[bg].first) {
-      for (int c : pend) freec.push_back(c);
-      pend.clear();
-      ++bg;
-    }
-    const int q = border[u];
-    const VInstr& I = P.code[q];
-    VStep& st = R.steps[q];
-    st.cout = cphys[I.out];
-    st.over = 0;
-    int* dst[3] = {&st.ca, &st.cb, &st.cc};
-    const int src[3] = {I.a, I.b, I.c};
-    for (int m = 0; m < 3; ++m) {
-      *dst[m] = -1;
-      if (src[m] < 0) continue;
-      if (cphys[src[m]] < 0) {
-        cphys[src[m]] = alloc();
-        st.over |= 1 << m;
-      }
-      *dst[m] = cphys[src[m]];
-    }
-    pend.push_back(st.cout);
-  }
-  for (int v = 0; v < 8; ++v) R.cin[v] = cphys[v];
-  for (int q : border) R.bsteps.push_back(R.steps[q]);
-  return R;
-}
-
-// ---------------------------------------------------------------------------
-// Kernels: one thread per cell of the packed boxes (block table as for the
-// other whole-box passes).
-
-// Pointwise operations need only the element index o; the neighbour
-// operations (stencils, max and mean over three cells) also the cell's
-// coordinates, found with 32-bit arithmetic (boxes hold < 2^31 cells).
-#define VM_PROLOGUE                                                  \
-  const Blk tb_ = tab[blockIdx.x];                                   \
-  if ((int)threadIdx.x >= tb_.n) return;                             \
-  const BoxDev& bx_ = boxes[tb_.box];                                \
-  const unsigned q_ = (unsigned)tb_.start + threadIdx.x;             \
-  const long long o = bx_.off + q_;                                  \
-  auto coords = [&](int& i, int& j, int& k) {                        \
-    const unsigned nx_ = (unsigned)bx_.nx, ny_ = (unsigned)bx_.ny;   \
-    const unsigned qx_ = q_ / nx_, qy_ = qx_ / ny_;                   \
-    i = (int)(q_ - qx_ * nx_);                                       \
-    j = (int)(qx_ - qy_ * ny_);                                      \
-    k = (int)qy_;                                                    \
-  };
-
-namespace {
-
-// (selects, not a switch: a switch over runtime values becomes a lookup
-// table in scratch memory)
-__device__ __forceinline__ double geo_of(const BoxDev& b, int geo) {
-  double r = 1.0;
-  r = geo == G_LX ? b.lv[0] : r;
-  r = geo == G_LY ? b.lv[1] : r;
-  r = geo == G_LZ ? b.lv[2] : r;
-  r = geo == G_H ? b.hmin : r;
-  r = geo == G_LXY ? b.le[0] : r;
-  r = geo == G_LXZ ? b.le[1] : r;
-  r = geo == G_LYZ ? b.le[2] : r;
-  r = geo == G_LZF ? b.lv[2] : r;
-  r = geo == G_HMIN ? b.hmin : r;
-  return r;
-}
-
-// The same at plane k: on a stretched z axis the z-dependent factors come
-// from the plane's entries of the per-plane table.
-template <class T>
-__device__ __forceinline__ double geo_at(const BoxDev& b, int geo, const T* zt, int k) {
-  if (!b.stretched) return geo_of(b, geo);
-  const T* e = zt + b.joff + (long long)k * ZJ_COUNT;
-  double r = geo_of(b, geo);
-  r = geo == G_LZ ? double(e[ZJ_LZZ]) : r;
-  r = geo == G_LXZ ? double(e[ZJ_LXZ]) : r;
-  r = geo == G_LYZ ? double(e[ZJ_LYZ]) : r;
-  r = geo == G_LZF ? double(e[ZJ_LZF]) : r;
-  r = geo == G_H ? double(e[ZJ_H]) : r;
-  return r;
-}
-
-// Value of a at offset m along axis ax from (i, j, k).
-template <class T>
-__device__ __forceinline__ T along(const T* a, const Geo<T>& g, int ax, int i, int j, int k, int m) {
-  return ax == VX ? a[g.at(i + m, j, k)] : (ax == VY ? a[g.at(i, j + m, k)] : a[g.at(i, j, k + m)]);
-}
-
-// Planes of a wall-bounded z axis within this distance of an end take the
-// wall forms of the z operators (the tables); the others (and their
-// transposes) the periodic pair forms, whose samples then all lie inside.
-constexpr int kWallReach = 6;
-
-__device__ __forceinline__ bool wall_z(const BoxDev& b, int ax) { return ax == VZ && b.wall; }
-// (on a stretched axis every plane takes the table forms: the Jacobian
-// varies from output to output, so the pair forms' transposes do not hold)
-__device__ __forceinline__ bool near_end(const BoxDev& b, int k) {
-  return b.stretched || k < kWallReach || k >= b.nzt - kWallReach;
-}
-
-// The factor of a z derivative at output plane k of a wall-bounded axis:
-// the Jacobian of an up (centre) or down (face) output from the per-plane
-// table, with the end copy built in (1/dz on a uniform axis).
+// The factor of a z derivative at output plane k of a wall-bounded axis: the
+// Jacobian of an up (centre) or down (face) output, end copy built in (1/dz
+// on a uniform axis).
 template <class T>
 __device__ __forceinline__ T zjac(const T* zt, const BoxDev& b, int form, int k) {
   return zt[b.joff + (long long)k * ZJ_COUNT + (form ? ZJ_C : ZJ_F)];
@@ -632,92 +113,8 @@ __device__ __forceinline__ T zw_coef(const T* zt, const BoxDev& b, int fam, int 
     const int c = form ? (k + 1 < N ? k + 1 : N - 1) : (k > 0 ? k : 1);
     return p == c ? T(1) : (p == c - 1 ? T(-1) : T(0));
   }
-  const int d = p - k;
-  if (d < -3 || d > 3) return T(0);
   const int type = fam == 0 ? (form ? ZT_IUP : ZT_IDN) : (form ? ZT_DUP : ZT_DDN);
-  return zt[b.zoff + ((long long)type * N + k) * 7 + d + 3];
-}
-
-// The step's reciprocal comes from the box record in global memory: picking
-// one of a local Geo's fields by a runtime axis would put Geo in scratch.
-template <class T>
-__device__ __forceinline__ T sten(const T* a, const Geo<T>& g, const BoxDev& bx, const T* zt, int ax,
-                                  int fam, int form, int i, int j, int k) {
-  auto at = [&](int m) { return along(a, g, ax, i, j, k, m); };
-  const T hinv = T(1.0 / (ax == VX ? bx.dx : (ax == VY ? bx.dy : bx.dz)));
-  if (wall_z(bx, ax) && near_end(bx, k)) {
-    T acc = T(0);
-    const int p0 = k - 3 > 0 ? k - 3 : 0, p1 = k + 3 < bx.nzt - 1 ? k + 3 : bx.nzt - 1;
-    for (int p = p0; p <= p1; ++p) acc += zw_coef(zt, bx, fam, form, k, p) * a[g.at(i, j, p)];
-    return fam ? acc * (bx.stretched ? zjac(zt, bx, form, k) : hinv) : acc;
-  }
-  if (fam == 2) return form ? (at(1) - at(0)) * hinv : (at(0) - at(-1)) * hinv;
-  if (fam == 0) return form ? op6<0, 1, T>(at, hinv) : op6<0, 0, T>(at, hinv);
-  return form ? op6<1, 1, T>(at, hinv) : op6<1, 0, T>(at, hinv);
-}
-
-// Transpose of sten at input cell (i, j, k), applied to the cotangent yb of
-// its outputs: the opposite stagger (minus it for a derivative), or near
-// the ends of a wall axis the gather over the table's columns.
-template <class T>
-__device__ __forceinline__ T sten_t(const T* yb, const Geo<T>& g, const BoxDev& bx, const T* zt, int ax,
-                                    int fam, int form, int i, int j, int k) {
-  if (wall_z(bx, ax) && near_end(bx, k)) {
-    const T hinv = T(1.0 / bx.dz);
-    T acc = T(0);
-    const int k0 = k - 3 > 0 ? k - 3 : 0, k1 = k + 3 < bx.nzt - 1 ? k + 3 : bx.nzt - 1;
-    if (bx.stretched && fam) {
-      for (int q = k0; q <= k1; ++q)
-        acc += zw_coef(zt, bx, fam, form, q, k) * zjac(zt, bx, form, q) * yb[g.at(i, j, q)];
-      return acc;
-    }
-    for (int q = k0; q <= k1; ++q) acc += zw_coef(zt, bx, fam, form, q, k) * yb[g.at(i, j, q)];
-    return fam ? acc * hinv : acc;
-  }
-  const T t = sten(yb, g, bx, zt, ax, fam, 1 - form, i, j, k);
-  return fam ? -t : t;
-}
-
-// Second-order switch: whether cell (i, j, k) is rough (some axis's absolute
-// second difference of ln rho or ln e_m above lim), and whether a cell
-// touching position `kind` (0 centre, 1 x-edge, 2 y-edge, 3 z-edge of the
-// index) is.  On a wall-bounded z axis there is no z second difference on
-// the end planes, and a position on the lower end plane touches no cell
-// below it.
-template <class T>
-__device__ __forceinline__ bool rough_cell(const T* lr, const T* le, const Geo<T>& g, int i, int j, int k,
-                                           T lim) {
-  T m = T(0);
-  const bool zd = !g.wall || (k > 0 && k < g.nzt - 1);
-  for (int v = 0; v < 2; ++v) {
-    const T* a = v ? le : lr;
-    const T c = a[g.at(i, j, k)];
-    m = fmax(m, fabs(a[g.at(i + 1, j, k)] - T(2) * c + a[g.at(i - 1, j, k)]));
-    m = fmax(m, fabs(a[g.at(i, j + 1, k)] - T(2) * c + a[g.at(i, j - 1, k)]));
-    if (zd) m = fmax(m, fabs(a[g.at(i, j, k + 1)] - T(2) * c + a[g.at(i, j, k - 1)]));
-  }
-  return m > lim;
-}
-template <class T>
-__device__ __forceinline__ bool rough_at(const T* lr, const T* le, const Geo<T>& g, int i, int j, int k,
-                                         T lim, int kind) {
-  const int di = (kind == 2 || kind == 3) ? 1 : 0, dj = (kind == 1 || kind == 3) ? 1 : 0,
-            dk = (kind == 1 || kind == 2) ? 1 : 0;
-  bool r = false;
-  for (int a = 0; a <= dk; ++a) {
-    if (g.wall && k - a < 0) continue;
-    for (int b = 0; b <= dj; ++b)
-      for (int c = 0; c <= di; ++c) r = r || rough_cell(lr, le, g, i - c, j - b, k - a, lim);
-  }
-  return r;
-}
-
-// Value of a at offset m along z from (i, j, k) on a wall-bounded axis, or
-// -inf past an end (never chosen by a maximum).
-template <class T>
-__device__ __forceinline__ T zval_or_ninf(const T* a, const Geo<T>& g, int i, int j, int k, int m) {
-  const int q = k + m;
-  return (q >= 0 && q < g.nzt) ? a[g.at(i, j, q)] : T(-INFINITY);
+  return zt[b.zoff + ((long long)type * N + k) * 7 + (p - k) + 3];
 }
 
 // Which of (lo, mid, hi) is the first maximal one: 0, 1 or 2.
@@ -729,456 +126,940 @@ template <class T> __device__ __forceinline__ int first_max(T lo, T mid, T hi) {
   return s;
 }
 
-}  // namespace
-
-// One group of the forward run: the first operation may read neighbouring
-// cells from memory; the rest are pointwise, with operands from the group's
-// register file (LDS, one column per thread) or from memory.
-template <class T>
-__global__ __launch_bounds__(kBlock) void k_vm_group(const BoxDev* boxes, const Blk* tab,
-                                                     const VFused* __restrict__ code, int first,
-                                                     int count, T* base, long long stride,
-                                                     const T* __restrict__ zt) {
-  __shared__ T regs[kGroupMax * kBlock];
-  VM_PROLOGUE
-  auto R = [&](int r) -> T& { return regs[r * kBlock + threadIdx.x]; };
-  for (int jj = 0; jj < count; ++jj) {
-    const VFused G = code[first + jj];
-    const VInstr& I = G.f;
-    auto opnd = [&](int slot, int loc) -> T { return loc >= 0 ? R(loc) : base[slot * stride + o]; };
-    T r;
-    switch (I.op) {
-      case V_STEN: {
-        int i, j, k;
-        coords(i, j, k);
-        const Geo<T> g(bx_);
-        r = sten(base + I.a * stride, g, bx_, zt, I.ax, I.fam, I.form, i, j, k);
-        break;
-      }
-      case V_MAX3: {
-        // over the available cells at the ends of a wall axis
-        int i, j, k;
-        coords(i, j, k);
-        const Geo<T> g(bx_);
-        const T* a = base + I.a * stride;
-        const bool wz = wall_z(bx_, I.ax);
-        const T lo = wz ? zval_or_ninf(a, g, i, j, k, -1) : along(a, g, I.ax, i, j, k, -1);
-        const T hi = wz ? zval_or_ninf(a, g, i, j, k, 1) : along(a, g, I.ax, i, j, k, 1);
-        const T mid = a[o];
-        const int s = first_max(lo, mid, hi);
-        r = s == 0 ? lo : (s == 1 ? mid : hi);
-        break;
-      }
-      case V_MEAN3: {
-        int i, j, k;
-        coords(i, j, k);
-        const Geo<T> g(bx_);
-        const T* a = base + I.a * stride;
-        if (wall_z(bx_, I.ax)) {
-          // the mean of the available cells, summed in the order k-1, k, k+1
-          const bool lo = k > 0, hi = k < bx_.nzt - 1;
-          T s = lo ? a[g.at(i, j, k - 1)] + a[o] : a[o];
-          if (hi) s = s + a[g.at(i, j, k + 1)];
-          r = s / T(1 + (lo ? 1 : 0) + (hi ? 1 : 0));
-        } else {
-          r = (along(a, g, I.ax, i, j, k, -1) + a[o] + along(a, g, I.ax, i, j, k, 1)) / T(3);
-        }
-        break;
-      }
-      case V_D2: {
-        int i, j, k;
-        coords(i, j, k);
-        const Geo<T> g(bx_);
-        const T* a = base + I.a * stride;
-        // none across the ends of a wall axis
-        if (wall_z(bx_, I.ax) && (k == 0 || k == bx_.nzt - 1))
-          r = T(0);
-        else
-          r = along(a, g, I.ax, i, j, k, 1) - T(2) * a[o] + along(a, g, I.ax, i, j, k, -1);
-        break;
-      }
-      case V_ADD: r = opnd(I.a, G.la) + opnd(I.b, G.lb); break;
-      case V_SUB: r = opnd(I.a, G.la) - opnd(I.b, G.lb); break;
-      case V_MUL: r = opnd(I.a, G.la) * opnd(I.b, G.lb); break;
-      case V_DIV: r = opnd(I.a, G.la) / opnd(I.b, G.lb); break;
-      case V_SCALE: {
-        double gv;
-        if (bx_.stretched) {
-          int i, j, k;
-          coords(i, j, k);
-          gv = geo_at(bx_, I.geo, zt, k);
-        } else {
-          gv = geo_of(bx_, I.geo);
-        }
-        r = T(I.k * gv) * opnd(I.a, G.la);
-        break;
-      }
-      case V_DIVC: r = opnd(I.a, G.la) / T(I.k); break;
-      case V_SQRT: r = sqrt(opnd(I.a, G.la)); break;
-      case V_LOG: r = log(opnd(I.a, G.la)); break;
-      case V_EXP: r = exp(opnd(I.a, G.la)); break;
-      case V_RELU: {
-        const T x = opnd(I.a, G.la);
-        r = x > T(0) ? x : T(0);
-        break;
-      }
-      case V_FLOOR: {
-        const T x = opnd(I.a, G.la);
-        r = x > T(I.k) ? x : T(I.k);
-        break;
-      }
-      case V_NORM3: {
-        const T x = opnd(I.a, G.la), y = opnd(I.b, G.lb), z = opnd(I.c, G.lc);
-        const T s = x * x + y * y + z * z;
-        r = s > T(0) ? sqrt(s) : T(0);
-        break;
-      }
-      case V_FILL:
-        r = I.geo == G_HINV ? T(I.k / bx_.hmin) : T(I.k * geo_of(bx_, I.geo));
-        break;
-      case V_ABS: r = fabs(opnd(I.a, G.la)); break;
-      case V_SEL: r = opnd(I.c, G.lc) > T(0.5) ? opnd(I.b, G.lb) : opnd(I.a, G.la); break;
-      case V_SDIV: {
-        const T x = opnd(I.a, G.la), y = opnd(I.b, G.lb);
-        r = y > T(0) ? x / y : T(0);
-        break;
-      }
-      case V_CAP: {
-        const T x = opnd(I.a, G.la);
-        r = x < T(I.k) ? x : T(I.k);
-        break;
-      }
-      default: r = T(0); break;
+// One cell with its neighbours' byte offsets (periodic wrap applied; planes
+// past a wall take the cell itself and are never used).  Offsets are 32-bit
+// within the box, so that a load is a scalar base plus one register; a box
+// of 2^32 bytes or more would need a workspace beyond the device's memory.
+// W: some box has walls.
+template <class T, bool W> struct Cell {
+  const BoxDev& b;
+  const T* zt;
+  unsigned o, sz;
+  int k;
+  unsigned d[3][7];
+  __device__ __forceinline__ Cell(const BoxDev& b_, unsigned q, const T* zt_) : b(b_), zt(zt_) {
+    const unsigned nx = (unsigned)b.nx, ny = (unsigned)b.ny;
+    const unsigned qx = q / nx, qy = qx / ny;
+    const int i = (int)(q - qx * nx), j = (int)(qx - qy * ny);
+    k = (int)qy;
+    o = q * (unsigned)sizeof(T);
+    sz = nx * ny * (unsigned)sizeof(T);
+#pragma unroll
+    for (int m = -3; m <= 3; ++m) {
+      const int x = i + m, y = j + m, z = k + m, N = b.nzt;
+      const int dx = x < 0 ? m + b.nx : (x >= b.nx ? m - b.nx : m);
+      const int dy = y < 0 ? m + b.ny : (y >= b.ny ? m - b.ny : m);
+      int dz = z < 0 ? m + N : (z >= N ? m - N : m);
+      if (W && b.wall && (z < 0 || z >= N)) dz = 0;
+      d[X][m + 3] = (unsigned)dx * (unsigned)sizeof(T);
+      d[Y][m + 3] = (unsigned)dy * nx * (unsigned)sizeof(T);
+      d[Z][m + 3] = (unsigned)dz * sz;
     }
-    R(jj) = r;
-    if (I.out >= 0) base[I.out * stride + o] = r;
   }
+  __device__ __forceinline__ T ld(const T* a, unsigned off = 0u) const {
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(a) + (o + off));
+  }
+  __device__ __forceinline__ void st(T* a, T v) const {
+    *reinterpret_cast<T*>(reinterpret_cast<char*>(a) + o) = v;
+  }
+  __device__ __forceinline__ bool walled() const { return W && b.wall; }
+  // a z neighbour that exists
+  __device__ __forceinline__ bool has(int m) const { return !walled() || (k + m >= 0 && k + m < b.nzt); }
+  template <int AX> __device__ __forceinline__ bool hasax(int m) const { return AX != Z || has(m); }
+  __device__ __forceinline__ T plane(int e) const { return zt[b.joff + (long long)k * ZJ_COUNT + e]; }
+  __device__ __forceinline__ unsigned zoffs(int p) const { return (unsigned)(p - k) * sz; }
+
+  // S_AX of f, f(offset) the operand at a byte offset from the cell.  FAM 0
+  // interpolation, 1 derivative, 2 second-order derivative; FORM 0 dn, 1 up.
+  template <int AX, int FAM, int FORM, class F> __device__ __forceinline__ T op(const F& f) const {
+    T h = T(b.hinv[AX]);
+    if constexpr (W && AX == Z) {
+      if (b.wall) {
+        if (k < 3 || k > b.nzt - 4) {
+          T acc = T(0);
+          const int p0 = k - 3 > 0 ? k - 3 : 0, p1 = k + 3 < b.nzt - 1 ? k + 3 : b.nzt - 1;
+#pragma unroll 1
+          for (int p = p0; p <= p1; ++p) acc += zw_coef(zt, b, FAM, FORM, k, p) * f(zoffs(p));
+          return FAM ? acc * (b.stretched ? zjac(zt, b, FORM, k) : h) : acc;
+        }
+        if (FAM && b.stretched) h = zjac(zt, b, FORM, k);
+      }
+    }
+    auto at = [&](int m) { return f(d[AX][m + 3]); };
+    if constexpr (FAM == 2) return FORM ? (at(1) - at(0)) * h : (at(0) - at(-1)) * h;
+    else return op6<FAM, FORM, T>(at, h);
+  }
+  // Its transpose at this cell, applied to the outputs' cotangent f.
+  template <int AX, int FAM, int FORM, class F> __device__ __forceinline__ T opT(const F& f) const {
+    const T h = T(b.hinv[AX]);
+    if constexpr (W && AX == Z) {
+      if (b.wall) {
+        if (k < 6 || k >= b.nzt - 6) {
+          T acc = T(0);
+          const int k0 = k - 3 > 0 ? k - 3 : 0, k1 = k + 3 < b.nzt - 1 ? k + 3 : b.nzt - 1;
+#pragma unroll 1
+          for (int q = k0; q <= k1; ++q) {
+            T c = zw_coef(zt, b, FAM, FORM, q, k);
+            if (FAM && b.stretched) c *= zjac(zt, b, FORM, q);
+            acc += c * f(zoffs(q));
+          }
+          return FAM && !b.stretched ? acc * h : acc;
+        }
+        if (FAM && b.stretched) {
+          auto at = [&](int m) { return f(d[AX][m + 3]) * zjac(zt, b, FORM, k + m); };
+          if constexpr (FAM == 2) return FORM ? at(-1) - at(0) : at(0) - at(1);
+          else return -op6<1, 1 - FORM, T>(at, T(1));
+        }
+      }
+    }
+    auto at = [&](int m) { return f(d[AX][m + 3]); };
+    if constexpr (FAM == 2) return FORM ? (at(-1) - at(0)) * h : (at(0) - at(1)) * h;
+    else {
+      const T v = op6<FAM, 1 - FORM, T>(at, h);
+      return FAM ? -v : v;
+    }
+  }
+#define VJP_OP(name, FAM, FORM)                                                                          \
+  template <int AX> __device__ __forceinline__ T name(const T* a) const {                                \
+    return op<AX, FAM, FORM>([&](unsigned f) { return ld(a, f); });                                      \
+  }                                                                                                      \
+  template <int AX> __device__ __forceinline__ T name##T(const T* a) const {                             \
+    return opT<AX, FAM, FORM>([&](unsigned f) { return ld(a, f); });                                     \
+  }
+  VJP_OP(dn, 0, 0)
+  VJP_OP(up, 0, 1)
+  VJP_OP(ddn, 1, 0)
+  VJP_OP(dup, 1, 1)
+  VJP_OP(d2n, 2, 0)
+  VJP_OP(d2u, 2, 1)
+#undef VJP_OP
+  // interpolation (dn or up, forward or transposed) along A of that along B
+  template <int A, int FA, int B, int FB> __device__ __forceinline__ T ii(const T* a) const {
+    return op<A, 0, FA>([&](unsigned f) { return op<B, 0, FB>([&](unsigned g) { return ld(a, f + g); }); });
+  }
+  template <int A, int FA, int B, int FB> __device__ __forceinline__ T iiT(const T* a) const {
+    return opT<A, 0, FA>([&](unsigned f) { return opT<B, 0, FB>([&](unsigned g) { return ld(a, f + g); }); });
+  }
+  // value at offset m along AX, or -inf past a wall (never a maximum)
+  template <int AX> __device__ __forceinline__ T orninf(const T* a, int m) const {
+    return hasax<AX>(m) ? ld(a, d[AX][m + 3]) : T(-INFINITY);
+  }
+  template <int AX> __device__ __forceinline__ T max3(const T* a) const {
+    const T lo = orninf<AX>(a, -1), mid = ld(a), hi = orninf<AX>(a, 1);
+    const int s = first_max(lo, mid, hi);
+    return s == 0 ? lo : (s == 1 ? mid : hi);
+  }
+  // transpose of the maximum of a over three cells: the cell is the hi
+  // neighbour of the one below, the middle of its own, the lo of the one above
+  template <int AX> __device__ __forceinline__ T max3T(const T* a, const T* yb) const {
+    const T v2 = orninf<AX>(a, -2), v1 = orninf<AX>(a, -1), v0 = ld(a), p1 = orninf<AX>(a, 1),
+            p2 = orninf<AX>(a, 2);
+    const T w1 = ld(yb, d[AX][2]), w0 = ld(yb), wp = ld(yb, d[AX][4]);
+    T sum = T(0);
+    if (hasax<AX>(-1) && first_max(v2, v1, v0) == 2) sum += w1;
+    if (first_max(v1, v0, p1) == 1) sum += w0;
+    if (hasax<AX>(1) && first_max(v0, p1, p2) == 0) sum += wp;
+    return sum;
+  }
+  // second difference (0 on the end planes of a wall axis), at offset m
+  template <int AX> __device__ __forceinline__ T second(const T* a, int m = 0) const {
+    if (AX == Z && walled() && (k + m <= 0 || k + m >= b.nzt - 1)) return T(0);
+    return ld(a, d[AX][m + 4]) - T(2) * ld(a, d[AX][m + 3]) + ld(a, d[AX][m + 2]);
+  }
+};
+
+#define VJP_CELL                                                             \
+  const int per_ = (K.nblk + 7) >> 3;                                        \
+  const int bi_ = (int)(blockIdx.x & 7u) * per_ + (int)(blockIdx.x >> 3);    \
+  if (bi_ >= K.nblk) return;                                                 \
+  const Blk tb_ = K.tab[bi_];                                                \
+  if ((int)threadIdx.x >= tb_.n) return;                                     \
+  const BoxDev& b = K.boxes[tb_.box];                                        \
+  const Cell<T, W> c(b, (unsigned)tb_.start + threadIdx.x, K.zt);            \
+  auto A = [&](int id) -> T* { return K.base + (long long)id * K.stride + b.off; };   \
+  auto S = [&](int v) -> const T* { return K.s.p[v] + b.off; };              \
+  auto Wt = [&](int v) -> const T* { return K.w.p[v] + b.off; };             \
+  const unsigned tm = K.ph.terms;                                            \
+  (void)A; (void)S; (void)Wt; (void)tm;
+
+#define VJP_KERNEL template <class T, bool W> __global__ __launch_bounds__(kBlock) void
+
+template <class T> __device__ __forceinline__ T vnorm3(T x, T y, T z) {
+  const T s = x * x + y * y + z * z;
+  return s > T(0) ? sqrt(s) : T(0);
 }
 
-// Transposes.  Each thread owns the cotangents of its own cells, so the
-// gathers of the stencil, max and mean transposes need no atomics; the
-// pointwise rules update the input cotangents one after the other (an input
-// may appear twice, as in a * a: its first contribution overwrites, the
-// second adds).  A workgroup takes kBwdCells consecutive block-table entries
-// and a thread one cell of each: every transpose first gathers its inputs
-// for all of them, so that many loads are in flight per thread.
-constexpr int kBwdCells = 4;
+// Viscosity length of the centre component a, and of edge e's component.
+template <class T, bool W> __device__ __forceinline__ T len_c(const Cell<T, W>& c, int a) {
+  return (W && a == Z && c.b.stretched) ? c.plane(ZJ_LZZ) : T(c.b.lv[a]);
+}
+template <class T, bool W> __device__ __forceinline__ T len_e(const Cell<T, W>& c, int e) {
+  if (W && e != Z && c.b.stretched) return c.plane(e == X ? ZJ_LYZ : ZJ_LXZ);
+  return T(c.b.le[2 - e]);     // le: xy, xz, yz; edge z, y, x
+}
+template <class T, bool W> __device__ __forceinline__ double h_shock(const Cell<T, W>& c) {
+  return (W && c.b.stretched) ? double(c.plane(ZJ_H)) : c.b.hmin;
+}
 
-template <class T>
-__global__ __launch_bounds__(kBlock) void k_vm_bwd(const BoxDev* boxes, const Blk* tab, int nblk,
-                                                   const VStep* __restrict__ code, int first,
-                                                   int count, const T* base, T* cbase,
-                                                   long long stride, const T* __restrict__ zt) {
-  constexpr int R = kBwdCells;
-  long long o[R];
-  unsigned q[R];
-  int bi[R];
-  bool ok[R];
-  bool found = false;
-  long long o0 = 0;
-  unsigned q0 = 0;
-  int b0 = 0;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int e = (int)blockIdx.x * R + r;
-    ok[r] = false;
-    bi[r] = 0;
-    q[r] = 0;
-    o[r] = 0;
-    if (e < nblk) {
-      const Blk tb = tab[e];
-      ok[r] = (int)threadIdx.x < tb.n;
-      bi[r] = tb.box;
-      q[r] = (unsigned)tb.start + threadIdx.x;
-      o[r] = boxes[tb.box].off + q[r];
-      if (ok[r] && !found) {
-        found = true;
-        o0 = o[r];
-        q0 = q[r];
-        b0 = bi[r];
-      }
-    }
-  }
-  if (!found) return;
-  // cells past a table entry's end read a valid cell's data and store nothing
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-    if (!ok[r]) {
-      o[r] = o0;
-      q[r] = q0;
-      bi[r] = b0;
-    }
-  auto coords = [&](int r, int& i, int& j, int& k) {
-    const BoxDev& b = boxes[bi[r]];
-    const unsigned nx_ = (unsigned)b.nx, ny_ = (unsigned)b.ny;
-    const unsigned qx_ = q[r] / nx_, qy_ = qx_ / ny_;
-    i = (int)(q[r] - qx_ * nx_);
-    j = (int)(qx_ - qy_ * ny_);
-    k = (int)qy_;
+// ---------------------------------------------------------------------------
+// Face densities and velocities, e_m, ln e_m, and w_e's x and y transposes.
+VJP_KERNEL k_prim(VK<T> K) {
+  VJP_CELL
+  const T* rho = S(0);
+  const T rx = c.template dn<X>(rho), ry = c.template dn<Y>(rho), rz = c.template dn<Z>(rho);
+  const T em = c.ld(S(4)) / c.ld(rho);
+  c.st(A(VA_R), rx);
+  c.st(A(VA_R + 1), ry);
+  c.st(A(VA_R + 2), rz);
+  c.st(A(VA_U), c.ld(S(1)) / rx);
+  c.st(A(VA_U + 1), c.ld(S(2)) / ry);
+  c.st(A(VA_U + 2), c.ld(S(3)) / rz);
+  c.st(A(VA_EM), em);
+  c.st(A(VA_LEM), log(em));
+  c.st(A(VA_XWE), c.template upT<X>(Wt(4)));
+  c.st(A(VA_YWE), c.template upT<Y>(Wt(4)));
+  if ((tm & T_PRES) && (tm & T_LNP)) c.st(A(VA_LNP), log(K.ph.gamma1 * c.ld(S(4))));
+}
+
+// Second-order switch: rough cells, then the flags of the positions a rough
+// cell touches (bit 0 the centre, 1 + c the edge along axis c).
+VJP_KERNEL k_rough(VK<T> K) {
+  VJP_CELL
+  const T* rho = S(0);
+  const T* le = A(VA_LEM);
+  auto lr = [&](unsigned f) { return log(c.ld(rho, f)); };
+  auto lm = [&](unsigned f) { return c.ld(le, f); };
+  T m = T(0);
+  auto axis = [&](const auto& f, int ax) {
+    m = fmax(m, fabs(f(c.d[ax][4]) - T(2) * f(0u) + f(c.d[ax][2])));
   };
-  for (int jj = 0; jj < count; ++jj) {
-    const VStep S = code[first + jj];
-    const VInstr& I = S.f;
-    const T* a = I.a >= 0 ? base + I.a * stride : nullptr;
-    const T* b = I.b >= 0 ? base + I.b * stride : nullptr;
-    const T* c = I.c >= 0 ? base + I.c * stride : nullptr;
-    T* ca = S.ca >= 0 ? cbase + S.ca * stride : nullptr;
-    T* cb = S.cb >= 0 ? cbase + S.cb * stride : nullptr;
-    T* cc = S.cc >= 0 ? cbase + S.cc * stride : nullptr;
-    const T* yb = cbase + S.cout * stride;
-    // the contribution v[r] to dst: overwrite or add, all loads first
-    auto put = [&](T* dst, int bit, const T (&v)[R]) {
-      T cur[R];
-      const bool over = S.over & bit;
+  axis(lr, X);
+  axis(lr, Y);
+  axis(lm, X);
+  axis(lm, Y);
+  if (c.has(-1) && c.has(1)) {
+    axis(lr, Z);
+    axis(lm, Z);
+  }
+  c.st(A(VA_RGH), m > K.ph.d2_lim ? T(1) : T(0));
+}
+VJP_KERNEL k_rough_flags(VK<T> K) {
+  VJP_CELL
+  const T* r = A(VA_RGH);
+  auto at = [&](int x, int y, int z) {
+    if (z && !c.has(-1)) return false;
+    return c.ld(r, c.d[X][3 - x] + c.d[Y][3 - y] + c.d[Z][3 - z]) > T(0.5);
+  };
+  unsigned f = at(0, 0, 0) ? 1u : 0u;
+  if (at(0, 0, 0) || at(0, 1, 0) || at(0, 0, 1) || at(0, 1, 1)) f |= 2u;
+  if (at(0, 0, 0) || at(1, 0, 0) || at(0, 0, 1) || at(1, 0, 1)) f |= 4u;
+  if (at(0, 0, 0) || at(1, 0, 0) || at(0, 1, 0) || at(1, 1, 0)) f |= 8u;
+  c.st(A(VA_RGF), T(f));
+}
+
+template <class T> __device__ __forceinline__ bool order2(const VK<T>& K) {
+  return (K.ph.terms & T_ORDER2) && (K.ph.terms & T_VISC);
+}
+template <class T> __device__ __forceinline__ bool quenched(const VK<T>& K) {
+  return (K.ph.terms & T_QUENCH) && (K.ph.terms & T_VISC);
+}
+template <class T> __device__ __forceinline__ bool smag(const VK<T>& K) {
+  return (K.ph.terms & T_SMAG) && !(K.ph.nu_const > T(0));
+}
+
+// Shear on the edge along axis C (eq. itv): sixth order, or second (O2).
+template <int C, bool O2, class T, bool W, class F>
+__device__ __forceinline__ T shear(const Cell<T, W>& c, const F& A) {
+  constexpr int P = (C + 1) % 3, Q = (C + 2) % 3;
+  if constexpr (O2) return T(0.5) * (c.template d2n<Q>(A(VA_U + P)) + c.template d2n<P>(A(VA_U + Q)));
+  else return T(0.5) * (c.template ddn<Q>(A(VA_U + P)) + c.template ddn<P>(A(VA_U + Q)));
+}
+// The strain that the stress takes: second order where flagged.
+template <int C, class T, bool W, class F>
+__device__ __forceinline__ T strain_e(const Cell<T, W>& c, const VK<T>& K, const F& A) {
+  if (order2(K) && ((unsigned)c.ld(A(VA_RGF)) & (2u << C))) return shear<C, true>(c, A);
+  return shear<C, false>(c, A);
+}
+
+// T_SMAG: the shear on the edges (blockIdx.y: edge direction).
+VJP_KERNEL k_shear(VK<T> K) {
+  VJP_CELL
+  const int e = (int)blockIdx.y;
+  c.st(A(VA_SE + e), e == X ? shear<X, false>(c, A) : (e == Y ? shear<Y, false>(c, A) : shear<Z, false>(c, A)));
+}
+
+// The speed-like viscosity (eq. RMnu, eq. nusmag).  Each product and sum is
+// rounded on its own, whatever the surrounding expression, so that ties and
+// signs (max, relu) fall the same way wherever this is evaluated.
+VJP_KERNEL k_nus(VK<T> K) {
+  VJP_CELL
+  const Phys<T>& ph = K.ph;
+  const T sxx = c.template dup<X>(A(VA_U)), syy = c.template dup<Y>(A(VA_U + 1)), szz = c.template dup<Z>(A(VA_U + 2));
+  const T sxy_ = sxx + syy;
+  const T D = sxy_ + szz;
+  const T ub = vnorm3(c.template up<X>(A(VA_U)), c.template up<Y>(A(VA_U + 1)), c.template up<Z>(A(VA_U + 2)));
+  const T bb = vnorm3(c.template up<X>(S(5)), c.template up<Y>(S(6)), c.template up<Z>(S(7)));
+  const T rho = c.ld(S(0));
+  const T P = ph.gamma1 * c.ld(S(4));
+  const T gp = ph.gamma * P;
+  const T cs = sqrt(gp / rho);
+  const T mr = ph.mu * rho;
+  const T ca = bb / sqrt(mr);
+  const T v1 = ph.nu1 * ub;
+  const T cc = cs + ca;
+  const T v2 = ph.nu3 * cc;
+  const T relu = -D > T(0) ? -D : T(0);
+  const T v3 = T(K.nu2 * h_shock(c)) * relu;
+  const T v12 = v1 + v2;
+  T nus = v12 + v3;
+  if (smag(K)) {
+    // centre values of the shear, kept for the transpose
+    const T cyz = c.template ii<Z, 1, Y, 1>(A(VA_SE)), cxz = c.template ii<Z, 1, X, 1>(A(VA_SE + 1)),
+            cxy = c.template ii<Y, 1, X, 1>(A(VA_SE + 2));
+    c.st(A(VA_SC), cyz);
+    c.st(A(VA_SC + 1), cxz);
+    c.st(A(VA_SC + 2), cxy);
+    const T s2 = T(2) * (sxx * sxx + syy * syy + szz * szz - D * D * T(1.0 / 3.0) +
+                         T(2) * (cxy * cxy + cxz * cxz + cyz * cyz));
+    const T v4 = T(K.c_smag * h_shock(c)) * (s2 > T(0) ? sqrt(s2) : T(0));
+    nus = nus + v4;
+  }
+  c.st(A(VA_MX), nus);
+}
+
+// Id of the m-th array of the maximum chain (0: the viscosity itself).
+__host__ __device__ __forceinline__ int mx_id(int m) { return m < 4 ? VA_MX + m : VA_MX5 + (m - 4); }
+
+// Maximum over three cells along x, y, z in turn: the three stages.
+VJP_KERNEL k_max3(VK<T> K) {
+  VJP_CELL
+  const T* a = A(VA_MX);
+  auto mx = [&](unsigned f) {
+    return fmax(fmax(c.ld(a, f + c.d[X][2]), c.ld(a, f)), c.ld(a, f + c.d[X][4]));
+  };
+  auto my = [&](unsigned f, T own) { return fmax(fmax(mx(f + c.d[Y][2]), own), mx(f + c.d[Y][4])); };
+  const T m1 = mx(0u);
+  const T m2 = my(0u, m1);
+  T m3 = m2;
+  if (c.has(-1)) m3 = fmax(m3, my(c.d[Z][2], mx(c.d[Z][2])));
+  if (c.has(1)) m3 = fmax(m3, my(c.d[Z][4], mx(c.d[Z][4])));
+  c.st(A(VA_MX + 1), m1);
+  c.st(A(VA_MX + 2), m2);
+  c.st(A(VA_MX + 3), m3);
+}
+// One stage (five cells: each axis twice).
+template <class T, bool W, int AX> __global__ __launch_bounds__(kBlock) void k_max1(VK<T> K, int src, int dst) {
+  VJP_CELL
+  c.st(A(dst), c.template max3<AX>(A(src)));
+}
+// Transpose of one stage; blockIdx.y: component (quenching).
+template <class T, bool W, int AX>
+__global__ __launch_bounds__(kBlock) void k_max1T(VK<T> K, int prim, int yb, int dst) {
+  VJP_CELL
+  const int m = (int)blockIdx.y;
+  c.st(A(dst + m), c.template max3T<AX>(A(prim + m), A(yb + m)));
+}
+
+// <nu>: the mean over three cells along each axis (the available ones at
+// the ends of a wall axis), the floor, and ln.  nu_const: the constant.
+VJP_KERNEL k_mean(VK<T> K) {
+  VJP_CELL
+  T v;
+  if (K.ph.nu_const > T(0)) {
+    v = T(double(K.ph.nu_const) / b.hmin);
+  } else {
+    const T* a = A(mx_id(K.nmax));
+    auto row = [&](unsigned f) { return (c.ld(a, f + c.d[X][2]) + c.ld(a, f) + c.ld(a, f + c.d[X][4])) / T(3); };
+    auto pl = [&](unsigned f) { return (row(f + c.d[Y][2]) + row(f) + row(f + c.d[Y][4])) / T(3); };
+    const bool lo = c.has(-1), hi = c.has(1);
+    T s = pl(0u);
+    if (lo) s = pl(c.d[Z][2]) + s;
+    if (hi) s = s + pl(c.d[Z][4]);
+    v = s / T(1 + (lo ? 1 : 0) + (hi ? 1 : 0));
+  }
+  v = v > T(1e-30) ? v : T(1e-30);
+  c.st(A(VA_NT), v);
+  c.st(A(VA_LNT), log(v));
+}
+VJP_KERNEL k_lines(VK<T> K) {
+  VJP_CELL
+  c.st(A(VA_XL), c.template dn<X>(A(VA_LNT)));
+  c.st(A(VA_YL), c.template dn<Y>(A(VA_LNT)));
+}
+
+// Density, viscosity and w_e's heating cotangent on the edge along C.
+template <int C, class T, bool W, class F> struct EdgeBase {
+  T rho, nu, Qb;
+  __device__ __forceinline__ EdgeBase(const Cell<T, W>& c, const F& A) {
+    constexpr int Q = C == Z ? Y : Z;                    // the second axis
+    constexpr int first = C == X ? 1 : 0;                // interpolated along y (edge x) or x first
+    rho = c.template dn<Q>(A(VA_R + first));
+    nu = len_e(c, C) * exp(c.template dn<Q>(A(C == X ? VA_YL : VA_XL)));
+    Qb = c.template upT<Q>(A(C == X ? VA_YWE : VA_XWE));
+  }
+};
+
+// T_QUENCH: raw stress (roles 0..2 the edges, 3..5 the centre), q, the
+// maxima over 3x3x3 cells.
+template <int C, class T, bool W, class F>
+__device__ __forceinline__ T raw_edge(const Cell<T, W>& c, const VK<T>& K, const F& A) {
+  const EdgeBase<C, T, W, F> E(c, A);
+  return E.rho * E.nu * strain_e<C>(c, K, A);
+}
+// Strain and div u at the centre as the stress takes them (vs, vD), and the
+// sixth-order ones (s, D).
+template <class T, bool W, class F> struct Centre {
+  T s[3], D, vs[3], vD;
+  bool rough;
+  __device__ __forceinline__ Centre(const Cell<T, W>& c, const VK<T>& K, const F& A) {
+    s[0] = c.template dup<X>(A(VA_U));
+    s[1] = c.template dup<Y>(A(VA_U + 1));
+    s[2] = c.template dup<Z>(A(VA_U + 2));
+    const T xy = s[0] + s[1];
+    D = xy + s[2];
+    rough = order2(K) && ((unsigned)c.ld(A(VA_RGF)) & 1u);
+    vD = D;
 #pragma unroll
-      for (int r = 0; r < R; ++r) cur[r] = over ? T(0) : dst[o[r]];
-#pragma unroll
-      for (int r = 0; r < R; ++r)
-        if (ok[r]) dst[o[r]] = over ? v[r] : cur[r] + v[r];
-    };
-    T y[R], v1[R], v2[R], v3[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) y[r] = yb[o[r]];
-    switch (I.op) {
-      case V_STEN: {
-        // interpolation: S^T = the opposite stagger; derivative: minus it
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          int i, j, k;
-          coords(r, i, j, k);
-          const Geo<T> g(boxes[bi[r]]);
-          v1[r] = sten_t(yb, g, boxes[bi[r]], zt, I.ax, I.fam, I.form, i, j, k);
-        }
-        put(ca, 1, v1);
-        break;
-      }
-      case V_ADD:
-      case V_SUB:
-        put(ca, 1, y);
-#pragma unroll
-        for (int r = 0; r < R; ++r) v2[r] = I.op == V_SUB ? -y[r] : y[r];
-        put(cb, 2, v2);
-        break;
-      case V_MUL:
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          v1[r] = y[r] * b[o[r]];
-          v2[r] = y[r] * a[o[r]];
-        }
-        put(ca, 1, v1);
-        put(cb, 2, v2);
-        break;
-      case V_DIV:
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const T vb = b[o[r]], qv = base[I.out * stride + o[r]];
-          v1[r] = y[r] / vb;
-          v2[r] = -(y[r] * qv / vb);
-        }
-        put(ca, 1, v1);
-        put(cb, 2, v2);
-        break;
-      case V_SCALE:
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const BoxDev& b = boxes[bi[r]];
-          double gv;
-          if (b.stretched) {
-            int i, j, k;
-            coords(r, i, j, k);
-            gv = geo_at(b, I.geo, zt, k);
-          } else {
-            gv = geo_of(b, I.geo);
-          }
-          v1[r] = T(I.k * gv) * y[r];
-        }
-        put(ca, 1, v1);
-        break;
-      case V_DIVC:
-#pragma unroll
-        for (int r = 0; r < R; ++r) v1[r] = y[r] / T(I.k);
-        put(ca, 1, v1);
-        break;
-      case V_SQRT:
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const T s = base[I.out * stride + o[r]];
-          v1[r] = s > T(0) ? y[r] / (T(2) * s) : T(0);
-        }
-        put(ca, 1, v1);
-        break;
-      case V_LOG:
-#pragma unroll
-        for (int r = 0; r < R; ++r) v1[r] = y[r] / a[o[r]];
-        put(ca, 1, v1);
-        break;
-      case V_EXP:
-#pragma unroll
-        for (int r = 0; r < R; ++r) v1[r] = y[r] * base[I.out * stride + o[r]];
-        put(ca, 1, v1);
-        break;
-      case V_RELU:
-#pragma unroll
-        for (int r = 0; r < R; ++r) v1[r] = a[o[r]] > T(0) ? y[r] : T(0);
-        put(ca, 1, v1);
-        break;
-      case V_FLOOR:
-#pragma unroll
-        for (int r = 0; r < R; ++r) v1[r] = a[o[r]] > T(I.k) ? y[r] : T(0);
-        put(ca, 1, v1);
-        break;
-      case V_NORM3:
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const T nrm = base[I.out * stride + o[r]];
-          const T w = nrm > T(0) ? y[r] / nrm : T(0);
-          v1[r] = w * a[o[r]];
-          v2[r] = w * b[o[r]];
-          v3[r] = w * c[o[r]];
-        }
-        put(ca, 1, v1);
-        put(cb, 2, v2);
-        put(cc, 4, v3);
-        break;
-      case V_MAX3:
-        // cell (i) is the hi neighbour of i-1, the middle of i, the lo of i+1
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          int i, j, k;
-          coords(r, i, j, k);
-          const Geo<T> g(boxes[bi[r]]);
-          // on a wall axis: cells past an end are -inf, outputs past an end absent
-          const bool wz = wall_z(boxes[bi[r]], I.ax);
-          auto v = [&](int m) { return wz ? zval_or_ninf(a, g, i, j, k, m) : along(a, g, I.ax, i, j, k, m); };
-          auto w = [&](int m) { return along(yb, g, I.ax, i, j, k, m); };
-          const T vm2 = v(-2), vm1 = v(-1), v0 = a[o[r]], vp1 = v(1), vp2 = v(2);
-          const bool has_lo = !wz || k > 0, has_hi = !wz || k < g.nzt - 1;
-          T sum = T(0);
-          if (has_lo && first_max(vm2, vm1, v0) == 2) sum += w(-1);
-          if (first_max(vm1, v0, vp1) == 1) sum += y[r];
-          if (has_hi && first_max(v0, vp1, vp2) == 0) sum += w(1);
-          v1[r] = sum;
-        }
-        put(ca, 1, v1);
-        break;
-      case V_MEAN3:
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          int i, j, k;
-          coords(r, i, j, k);
-          const Geo<T> g(boxes[bi[r]]);
-          if (wall_z(boxes[bi[r]], I.ax)) {
-            // output q averages over 2 cells at an end of the axis, else 3
-            const int N = g.nzt;
-            auto cnt = [&](int q) { return T(q == 0 || q == N - 1 ? 2 : 3); };
-            T s = y[r] / cnt(k);
-            if (k > 0) s += yb[g.at(i, j, k - 1)] / cnt(k - 1);
-            if (k < N - 1) s += yb[g.at(i, j, k + 1)] / cnt(k + 1);
-            v1[r] = s;
-          } else {
-            v1[r] = (along(yb, g, I.ax, i, j, k, -1) + y[r] + along(yb, g, I.ax, i, j, k, 1)) / T(3);
-          }
-        }
-        put(ca, 1, v1);
-        break;
-      case V_D2:   // symmetric on a periodic axis
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          int i, j, k;
-          coords(r, i, j, k);
-          const Geo<T> g(boxes[bi[r]]);
-          if (wall_z(boxes[bi[r]], I.ax)) {
-            // outputs 1 .. N-2 only
-            const int N = g.nzt;
-            T s = (k >= 1 && k <= N - 2) ? T(-2) * y[r] : T(0);
-            if (k - 1 >= 1) s += yb[g.at(i, j, k - 1)];
-            if (k + 1 <= N - 2) s += yb[g.at(i, j, k + 1)];
-            v1[r] = s;
-          } else {
-            v1[r] = along(yb, g, I.ax, i, j, k, 1) - T(2) * y[r] + along(yb, g, I.ax, i, j, k, -1);
-          }
-        }
-        put(ca, 1, v1);
-        break;
-      case V_ABS:
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const T x = a[o[r]];
-          v1[r] = x > T(0) ? y[r] : (x < T(0) ? -y[r] : T(0));
-        }
-        put(ca, 1, v1);
-        break;
-      case V_SDIV:
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const T vb = b[o[r]], qv = base[I.out * stride + o[r]];
-          v1[r] = vb > T(0) ? y[r] / vb : T(0);
-          v2[r] = vb > T(0) ? -(y[r] * qv / vb) : T(0);
-        }
-        put(ca, 1, v1);
-        put(cb, 2, v2);
-        break;
-      case V_CAP:
-#pragma unroll
-        for (int r = 0; r < R; ++r) v1[r] = a[o[r]] < T(I.k) ? y[r] : T(0);
-        put(ca, 1, v1);
-        break;
-      case V_ROUGH:   // a mask: no derivative
-#pragma unroll
-        for (int r = 0; r < R; ++r) v1[r] = T(0);
-        put(ca, 1, v1);
-        put(cb, 2, v1);
-        break;
-      case V_SEL:
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const bool m = c[o[r]] > T(0.5);
-          v1[r] = m ? T(0) : y[r];
-          v2[r] = m ? y[r] : T(0);
-          v3[r] = T(0);
-        }
-        put(ca, 1, v1);
-        put(cb, 2, v2);
-        put(cc, 4, v3);
-        break;
-      default: break;
+    for (int a = 0; a < 3; ++a) vs[a] = s[a];
+    if (rough) {
+      vs[0] = c.template d2u<X>(A(VA_U));
+      vs[1] = c.template d2u<Y>(A(VA_U + 1));
+      vs[2] = c.template d2u<Z>(A(VA_U + 2));
+      vD = vs[0] + vs[1] + vs[2];
     }
   }
+};
+VJP_KERNEL k_tau(VK<T> K) {
+  VJP_CELL
+  const int m = (int)blockIdx.y;
+  T t;
+  if (m < 3) {
+    t = m == X ? raw_edge<X>(c, K, A) : (m == Y ? raw_edge<Y>(c, K, A) : raw_edge<Z>(c, K, A));
+    c.st(A(VA_TAU + m), t);
+  } else if (m == 3) {
+    const Centre<T, W, decltype(A)> E(c, K, A);
+    const T r = c.ld(S(0)), nt = c.ld(A(VA_NT));
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+      c.st(A(VA_TAU + 3 + a), r * (len_c(c, a) * nt) * (E.vs[a] + K.ph.c1 * E.vD));
+  }
+}
+VJP_KERNEL k_quench(VK<T> K) {
+  VJP_CELL
+  const int m = (int)blockIdx.y;
+  const T* t = A(VA_TAU + m);
+  const T s = fabs(c.template second<X>(t)) + fabs(c.template second<Y>(t)) + fabs(c.template second<Z>(t));
+  const T den = fabs(c.ld(t)) + s / K.ph.q_max;
+  c.st(A(VA_QQ + m), den > T(0) ? s / den : T(0));
+}
+VJP_KERNEL k_quench_max(VK<T> K) {
+  VJP_CELL
+  const int m = (int)blockIdx.y;
+  const T* a = A(VA_QQ + m);
+  auto mx = [&](unsigned f) {
+    return fmax(fmax(c.ld(a, f + c.d[X][2]), c.ld(a, f)), c.ld(a, f + c.d[X][4]));
+  };
+  auto my = [&](unsigned f, T own) { return fmax(fmax(mx(f + c.d[Y][2]), own), mx(f + c.d[Y][4])); };
+  const T m1 = mx(0u);
+  const T m2 = my(0u, m1);
+  T m3 = m2;
+  if (c.has(-1)) m3 = fmax(m3, my(c.d[Z][2], mx(c.d[Z][2])));
+  if (c.has(1)) m3 = fmax(m3, my(c.d[Z][4], mx(c.d[Z][4])));
+  c.st(A(VA_Q1 + m), m1);
+  c.st(A(VA_Q2 + m), m2);
+  c.st(A(VA_Q3 + m), m3);
+}
+// The factor of component m at the cell.
+template <class T, bool W, class F>
+__device__ __forceinline__ T qfac(const Cell<T, W>& c, const VK<T>& K, const F& A, int m) {
+  const T q = c.ld(A(VA_Q3 + m));
+  return q < K.ph.q_lim ? q : K.ph.q_lim;
 }
 
-template <class T>
-__global__ __launch_bounds__(kBlock) void k_axpby8(const BoxDev* boxes, const Blk* tab, P8<T> y,
-                                                   CP8<T> x, T a, T b) {
-  VM_PROLOGUE
-  (void)coords;
-  for (int v = 0; v < 8; ++v) {
-    const T xv = x.p[0] ? x.p[v][o] : T(0);
-    y.p[v][o] = (a == T(0) ? T(0) : a * y.p[v][o]) + b * xv;
+// Cotangents of the momentum fluxes on the edge along C (between the axes P
+// and Q): the flux of p_P enters dp_P through dup_Q, that of p_Q dp_Q
+// through dup_P.
+template <int C, class T, bool W, class F>
+__device__ __forceinline__ void flux_cot(const Cell<T, W>& c, const F& Wt, T& g1, T& g2) {
+  constexpr int P = (C + 1) % 3, Q = (C + 2) % 3;
+  g1 = c.template dupT<Q>(Wt(1 + P));
+  g2 = c.template dupT<P>(Wt(1 + Q));
+}
+// The quenched stress's cotangent, and through the cap that of the maximum
+// of q.
+template <int C, class T, bool W, class F, class G>
+__device__ __forceinline__ T taub_edge(const Cell<T, W>& c, const VK<T>& K, const F& A, const G& Wt) {
+  const EdgeBase<C, T, W, F> E(c, A);
+  T g1, g2;
+  flux_cot<C>(c, Wt, g1, g2);
+  return g1 + g2 + T(2) * strain_e<C>(c, K, A) * E.Qb;
+}
+VJP_KERNEL k_taub(VK<T> K) {
+  VJP_CELL
+  const int m = (int)blockIdx.y;
+  auto put = [&](int q, T tb) {
+    const T x = c.ld(A(VA_Q3 + q));
+    c.st(A(VA_TB + q), tb);
+    c.st(A(VA_QB0 + q), x < K.ph.q_lim ? c.ld(A(VA_TAU + q)) * tb : T(0));
+  };
+  if (m < 3) {
+    put(m, m == X ? taub_edge<X>(c, K, A, Wt) : (m == Y ? taub_edge<Y>(c, K, A, Wt) : taub_edge<Z>(c, K, A, Wt)));
+  } else if (m == 3) {
+    const Centre<T, W, decltype(A)> E(c, K, A);
+    const T we = c.ld(Wt(4));
+    put(3, c.template ddnT<X>(Wt(1)) + E.vs[0] * we);
+    put(4, c.template ddnT<Y>(Wt(2)) + E.vs[1] * we);
+    put(5, c.template ddnT<Z>(Wt(3)) + E.vs[2] * we);
+  }
+}
+// From the cotangent of q: that of D2 (into QB0), and the stress's own
+// through |tau| and the factor (into TB).
+VJP_KERNEL k_quenchT(VK<T> K) {
+  VJP_CELL
+  const int m = (int)blockIdx.y;
+  const T* t = A(VA_TAU + m);
+  const T qb = c.template max3T<X>(A(VA_QQ + m), A(VA_QB0 + m));
+  const T s = fabs(c.template second<X>(t)) + fabs(c.template second<Y>(t)) + fabs(c.template second<Z>(t));
+  const T tv = c.ld(t);
+  const T den = fabs(tv) + s / K.ph.q_max;
+  const T q = c.ld(A(VA_QQ + m));
+  const T sb = den > T(0) ? qb / den : T(0);
+  const T db = den > T(0) ? -(qb * q / den) : T(0);
+  c.st(A(VA_QB1 + m), sb + db / K.ph.q_max);
+  T tb = c.ld(A(VA_TB + m)) * qfac(c, K, A, m);
+  tb += tv > T(0) ? db : (tv < T(0) ? -db : T(0));
+  c.st(A(VA_TB + m), tb);
+}
+// The second differences' transposes, added to the stress's cotangent.
+VJP_KERNEL k_quenchT2(VK<T> K) {
+  VJP_CELL
+  const int m = (int)blockIdx.y;
+  const T* t = A(VA_TAU + m);
+  const T* sb = A(VA_QB1 + m);
+  T tb = c.ld(A(VA_TB + m));
+  auto axis = [&](auto ax) {
+    constexpr int AX = decltype(ax)::value;
+    auto z = [&](int q) {
+      if (!c.template hasax<AX>(q)) return T(0);
+      const T d = c.template second<AX>(t, q);
+      const T v = c.ld(sb, c.d[AX][q + 3]);
+      return d > T(0) ? v : (d < T(0) ? -v : T(0));
+    };
+    // outputs on the end planes of a wall axis are 0 whatever the stress
+    const bool wz = AX == Z && c.walled();
+    const int N = b.nzt;
+    T r = T(0);
+    if (!wz || (c.k >= 1 && c.k <= N - 2)) r += T(-2) * z(0);
+    if (!wz || c.k - 1 >= 1) r += z(-1);
+    if (!wz || c.k + 1 <= N - 2) r += z(1);
+    tb += r;
+  };
+  axis(std::integral_constant<int, X>{});
+  axis(std::integral_constant<int, Y>{});
+  axis(std::integral_constant<int, Z>{});
+  c.st(A(VA_TB + m), tb);
+}
+
+// ---------------------------------------------------------------------------
+// Edge along C, between the axes P and Q: stress, E_C, the Lorentz products
+// and the heating, backwards.  With u_P, p_P, B_P interpolated along Q and
+// u_Q, p_Q, B_Q along P:
+//   E = -(uP bQ - uQ bP) + eta J,  J = dd_P(B_Q) - dd_Q(B_P);
+//   dp_P += dup_Q(tau - pP uQ) - up_Q(J bQ) / mu,
+//   dp_Q += dup_P(tau - pQ uP) + up_P(J bP) / mu,
+//   dB_P -= dup_Q(E), dB_Q += dup_P(E), de += up_P up_Q(2 tau S + eta J^2 / mu).
+template <int C, class T, bool W, class F, class G, class H>
+__device__ __forceinline__ void edge_back(const Cell<T, W>& c, const VK<T>& K, const F& A, const G& Wt, const H& S) {
+  constexpr int P = (C + 1) % 3, Q = (C + 2) % 3;
+  const Phys<T>& ph = K.ph;
+  const unsigned tm = ph.terms;
+  const bool visc = tm & T_VISC, res = tm & T_RESIST, ind = tm & T_INDUCT, lor = tm & T_LORENTZ,
+             adv = tm & T_ADV;
+  const EdgeBase<C, T, W, F> E(c, A);
+  const T uP = c.template dn<Q>(A(VA_U + P)), uQ = c.template dn<P>(A(VA_U + Q));
+  const T bP = c.template dn<Q>(S(5 + P)), bQ = c.template dn<P>(S(5 + Q));
+  const T J = c.template ddn<P>(S(5 + Q)) - c.template ddn<Q>(S(5 + P));
+  T g1, g2;
+  flux_cot<C>(c, Wt, g1, g2);
+  T uPb = T(0), uQb = T(0), pPb = T(0), pQb = T(0), bPb = T(0), bQb = T(0), Jb = T(0), Sb = T(0), rb = T(0),
+    nb = T(0);
+  if (visc) {
+    const T st = strain_e<C>(c, K, A);
+    const T raw = E.rho * E.nu * st;
+    T tb = g1 + g2 + T(2) * st * E.Qb, tau = raw;
+    if (quenched(K)) {
+      tau = raw * qfac(c, K, A, C);
+      tb = c.ld(A(VA_TB + C));
+    }
+    Sb = T(2) * tau * E.Qb + E.rho * E.nu * tb;
+    rb = E.nu * st * tb;
+    nb = E.rho * st * tb;
+  }
+  if (adv) {
+    const T pP = c.template dn<Q>(S(1 + P)), pQ = c.template dn<P>(S(1 + Q));
+    pPb = -uQ * g1;
+    uQb = -pP * g1;
+    pQb = -uP * g2;
+    uPb = -pQ * g2;
+  }
+  const T Eb = c.template dupT<P>(Wt(5 + Q)) - c.template dupT<Q>(Wt(5 + P));
+  if (ind) {
+    uPb -= bQ * Eb;
+    bQb -= uP * Eb;
+    uQb += bP * Eb;
+    bPb += uQ * Eb;
+  }
+  if (res) {
+    const T eta = ph.eta_const > T(0) ? ph.eta_const : ph.nuB * E.nu;
+    const T jq = J * E.Qb * ph.inv_mu;
+    Jb += eta * (Eb + T(2) * jq);
+    if (!(ph.eta_const > T(0))) nb += ph.nuB * (J * (Eb + jq));
+  }
+  if (lor) {
+    const T l1 = -(c.template upT<Q>(Wt(1 + P)) * ph.inv_mu), l2 = c.template upT<P>(Wt(1 + Q)) * ph.inv_mu;
+    Jb += bQ * l1 + bP * l2;
+    bQb += J * l1;
+    bPb += J * l2;
+  }
+  auto put = [&](int q, T v) { c.st(A(VA_EDGE + C * EQ_COUNT + q), v); };
+  put(EQ_UAB, uPb);
+  put(EQ_UBA, uQb);
+  put(EQ_PAB, pPb);
+  put(EQ_PBA, pQb);
+  put(EQ_BAB, bPb);
+  put(EQ_BBA, bQb);
+  put(EQ_J, Jb);
+  put(EQ_RHO, rb);
+  put(EQ_LNU, E.nu * nb);
+  const T hs = T(0.5) * Sb;
+  if (order2(K)) {
+    const bool r = (unsigned)c.ld(A(VA_RGF)) & (2u << C);
+    put(EQ_HS, r ? T(0) : hs);
+    c.st(A(VA_HS2 + C), r ? hs : T(0));
+  } else {
+    put(EQ_HS, hs);
   }
 }
 
-// The second-order switch's mask (V_ROUGH), alone in its group: both
-// operands and the result in memory.
-template <class T>
-__global__ __launch_bounds__(kBlock) void k_vm_rough(const BoxDev* boxes, const Blk* tab,
-                                                     const VFused* __restrict__ code, int at, T* base,
-                                                     long long stride) {
-  VM_PROLOGUE
-  const VInstr I = code[at].f;
-  int i, j, k;
-  coords(i, j, k);
-  const Geo<T> g(bx_);
-  base[I.out * stride + o] =
-      rough_at(base + I.a * stride, base + I.b * stride, g, i, j, k, T(I.k), I.ax) ? T(1) : T(0);
+// Face normal to a: the energy flux H = -dn_a(e) u_a + nuE dn_a(rho) l
+// dn_a(nu) dn_a(e_m) ddn_a(ln e_m), backwards; with T_LNP the pressure
+// gradient exp(dn_a ln P) ddn_a ln P too (the plane mean of eq. pressure
+// drops out of the product and of its derivative).
+template <int AX, class T, bool W, class F, class G, class H>
+__device__ __forceinline__ void face_back(const Cell<T, W>& c, const VK<T>& K, const F& A, const G& Wt, const H& S) {
+  const Phys<T>& ph = K.ph;
+  const T Hb = c.template dupT<AX>(Wt(4));
+  T xe = T(0), uf = T(0), rf = T(0), xn = T(0), xm = T(0), dl = T(0);
+  if (ph.terms & T_ADV) {
+    xe = -(c.ld(A(VA_U + AX)) * Hb);
+    uf = -(c.template dn<AX>(S(4)) * Hb);
+  }
+  if (ph.terms & T_EDIFF) {
+    const T l = (W && AX == Z && c.b.stretched) ? c.plane(ZJ_LZF) : T(c.b.lv[AX]);
+    const T kr = ph.nuE * c.ld(A(VA_R + AX));
+    const T ln = l * c.template dn<AX>(A(VA_NT));
+    const T em = c.template dn<AX>(A(VA_EM));
+    T dv = c.template ddn<AX>(A(VA_LEM));
+    if (AX == Z && (ph.terms & T_EDIFFAV)) {
+      // ln <e_m> of the offset's plane
+      const double* pm = K.pm + c.b.poff;
+      dv -= c.template op<Z, 1, 0>([&](unsigned f) { return T(log(T(pm[(c.o + f) / c.sz]))); });
+    }
+    rf = ph.nuE * ln * em * dv * Hb;
+    xn = kr * l * em * dv * Hb;
+    xm = kr * ln * dv * Hb;
+    dl = kr * ln * em * Hb;
+  }
+  c.st(A(VA_XE + AX), xe);
+  c.st(A(VA_UF + AX), uf);
+  c.st(A(VA_RF + AX), rf);
+  c.st(A(VA_XNT + AX), xn);
+  c.st(A(VA_XEM + AX), xm);
+  c.st(A(VA_DLEM + AX), dl);
+  if ((ph.terms & T_PRES) && (ph.terms & T_LNP)) {
+    const T gb = -c.ld(Wt(1 + AX)) * exp(c.template dn<AX>(A(VA_LNP)));
+    c.st(A(VA_QI + AX), gb * c.template ddn<AX>(A(VA_LNP)));
+    c.st(A(VA_QD + AX), gb);
+  }
 }
 
-// V_PMEAN: the mean of src over each z plane of every box, in float64 and a
-// fixed order (one workgroup per plane), then its broadcast over the plane
-// into dst (overwriting, or added with over = 0).
+// Edges (blockIdx.y 0..2, the direction) and faces (3..5, the normal).
+VJP_KERNEL k_edge_face(VK<T> K) {
+  VJP_CELL
+  switch (blockIdx.y) {
+    case 0: edge_back<X>(c, K, A, Wt, S); break;
+    case 1: edge_back<Y>(c, K, A, Wt, S); break;
+    case 2: edge_back<Z>(c, K, A, Wt, S); break;
+    case 3: face_back<X>(c, K, A, Wt, S); break;
+    case 4: face_back<Y>(c, K, A, Wt, S); break;
+    default: face_back<Z>(c, K, A, Wt, S); break;
+  }
+}
+
+// The edges' ln nu gathered along their second axis, and with the optional
+// terms the cotangents of div B and of the plane means' log.
+VJP_KERNEL k_lines_back(VK<T> K) {
+  VJP_CELL
+  auto Eq = [&](int e, int q) { return A(VA_EDGE + e * EQ_COUNT + q); };
+  c.st(A(VA_XLB), c.template dnT<Y>(Eq(Z, EQ_LNU)) + c.template dnT<Z>(Eq(Y, EQ_LNU)));
+  c.st(A(VA_YLB), c.template dnT<Z>(Eq(X, EQ_LNU)));
+  if ((tm & T_DIVB) && K.dt > 0.0) {
+    const T kd = T(K.c_divb / K.dt * b.hmin) * T(b.hmin);
+    c.st(A(VA_DVB), kd * (c.template ddnT<X>(Wt(5)) + c.template ddnT<Y>(Wt(6)) + c.template ddnT<Z>(Wt(7))));
+  }
+  if ((tm & T_EDIFF) && (tm & T_EDIFFAV)) c.st(A(VA_EDX), c.template ddnT<Z>(A(VA_DLEM + Z)));
+}
+
+// Cotangent of a centre stress component: momentum flux and heating, or the
+// quenching's transpose.
+template <int AX, class T, bool W, class F, class G>
+__device__ __forceinline__ T taub_centre(const Cell<T, W>& c, const VK<T>& K, const F& A, const G& Wt, T vs, T we) {
+  if (quenched(K)) return c.ld(A(VA_TB + 3 + AX));
+  return c.template ddnT<AX>(Wt(1 + AX)) + vs * we;
+}
+
+// <nu>: from the centre stress, the faces and the edges' logs.
+VJP_KERNEL k_nu_back(VK<T> K) {
+  VJP_CELL
+  const T nt = c.ld(A(VA_NT));
+  T nb = T(0);
+  if (tm & T_VISC) {
+    const Centre<T, W, decltype(A)> E(c, K, A);
+    const T we = c.ld(Wt(4)), rho = c.ld(S(0));
+    const T tb[3] = {taub_centre<X>(c, K, A, Wt, E.vs[0], we), taub_centre<Y>(c, K, A, Wt, E.vs[1], we),
+                     taub_centre<Z>(c, K, A, Wt, E.vs[2], we)};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) nb += rho * len_c(c, a) * (E.vs[a] + K.ph.c1 * E.vD) * tb[a];
+  }
+  nb += c.template dnT<X>(A(VA_XNT)) + c.template dnT<Y>(A(VA_XNT + 1)) + c.template dnT<Z>(A(VA_XNT + 2));
+  nb += (c.template dnT<X>(A(VA_XLB)) + c.template dnT<Y>(A(VA_YLB))) / nt;
+  c.st(A(VA_NTB), nt > T(1e-30) ? nb : T(0));
+}
+
+// Transpose of the three-cell means: on a wall axis output q averages over
+// 2 cells at an end, else 3.
+VJP_KERNEL k_mean_back(VK<T> K) {
+  VJP_CELL
+  const T* a = A(VA_NTB);
+  const int N = b.nzt;
+  auto zc = [&](unsigned f) {
+    auto cnt = [&](int q) { return T(c.walled() && (q == 0 || q == N - 1) ? 2 : 3); };
+    T s = c.ld(a, f) / cnt(c.k);
+    if (c.has(-1)) s += c.ld(a, f + c.d[Z][2]) / cnt(c.k - 1);
+    if (c.has(1)) s += c.ld(a, f + c.d[Z][4]) / cnt(c.k + 1);
+    return s;
+  };
+  auto yc = [&](unsigned f) { return (zc(f + c.d[Y][2]) + zc(f) + zc(f + c.d[Y][4])) / T(3); };
+  c.st(A(VA_MB0), (yc(c.d[X][2]) + yc(0u) + yc(c.d[X][4])) / T(3));
+}
+
+// Centre: the stress, the diagonal momentum fluxes, -P div u and the
+// speed-like viscosity (mb: the cotangent of its first maximum), backwards.
+VJP_KERNEL k_centre_back(VK<T> K, int mb) {
+  VJP_CELL
+  const Phys<T>& ph = K.ph;
+  const Centre<T, W, decltype(A)> E(c, K, A);
+  const T rho = c.ld(S(0)), e = c.ld(S(4)), nt = c.ld(A(VA_NT)), we = c.ld(Wt(4));
+  const T P = ph.gamma1 * e;
+  T Db = T(0), vDb = T(0), rb = T(0), Pb = T(0);
+  T vsb[3] = {}, sb[3] = {}, cp[3] = {}, cu[3] = {}, cb[3] = {};
+  T uc[3] = {c.template up<X>(A(VA_U)), c.template up<Y>(A(VA_U + 1)), c.template up<Z>(A(VA_U + 2))};
+  const T gf[3] = {c.template ddnT<X>(Wt(1)), c.template ddnT<Y>(Wt(2)), c.template ddnT<Z>(Wt(3))};
+  if (tm & T_VISC) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const T rn = rho * (len_c(c, a) * nt), m = E.vs[a] + ph.c1 * E.vD;
+      T tb, t = rn * m;
+      if (quenched(K)) {
+        t = t * qfac(c, K, A, 3 + a);
+        tb = c.ld(A(VA_TB + 3 + a));
+      } else {
+        tb = gf[a] + E.vs[a] * we;
+      }
+      vsb[a] = t * we + rn * tb;
+      vDb += ph.c1 * rn * tb;
+      rb += len_c(c, a) * nt * m * tb;
+    }
+  }
+  if (tm & T_ADV) {
+    const T pc[3] = {c.template up<X>(S(1)), c.template up<Y>(S(2)), c.template up<Z>(S(3))};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      cp[a] = -(uc[a] * gf[a]);
+      cu[a] = -(pc[a] * gf[a]);
+    }
+  }
+  if (tm & T_PRES) {
+    Pb -= E.D * we;
+    Db -= P * we;
+  }
+  if (!(ph.nu_const > T(0))) {
+    const T nb = c.template max3T<X>(A(VA_MX), A(mb));
+    const T ub = vnorm3(uc[0], uc[1], uc[2]);
+    const T wu = ub > T(0) ? ph.nu1 * nb / ub : T(0);
+    const T bc[3] = {c.template up<X>(S(5)), c.template up<Y>(S(6)), c.template up<Z>(S(7))};
+    const T bb = vnorm3(bc[0], bc[1], bc[2]);
+    const T v3 = ph.nu3 * nb;
+    const T sr = sqrt(ph.mu * rho), ca = bb / sr, bbb = v3 / sr;
+    rb -= ph.mu * (v3 * ca / sr) / (T(2) * sr);
+    const T arg = ph.gamma * P / rho, cs = sqrt(arg);
+    const T ab = cs > T(0) ? v3 / (T(2) * cs) : T(0);
+    Pb += ph.gamma * (ab / rho);
+    rb -= ab * arg / rho;
+    const T wb = bb > T(0) ? bbb / bb : T(0);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      cu[a] += wu * uc[a];
+      cb[a] = wb * bc[a];
+    }
+    if (-E.D > T(0)) Db -= T(K.nu2 * h_shock(c)) * nb;
+    if (smag(K)) {
+      const T q[3] = {c.ld(A(VA_SC)), c.ld(A(VA_SC + 1)), c.ld(A(VA_SC + 2))};
+      const T s2 = T(2) * (E.s[0] * E.s[0] + E.s[1] * E.s[1] + E.s[2] * E.s[2] - E.D * E.D * T(1.0 / 3.0) +
+                           T(2) * (q[0] * q[0] + q[1] * q[1] + q[2] * q[2]));
+      const T s2b = s2 > T(0) ? T(K.c_smag * h_shock(c)) * nb / (T(2) * sqrt(s2)) : T(0);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        sb[a] = T(4) * E.s[a] * s2b;
+        c.st(A(VA_SC + a), T(8) * q[a] * s2b);
+      }
+      Db -= T(4.0 / 3.0) * E.D * s2b;
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    T v6 = sb[a] + Db, v2 = vsb[a] + vDb;
+    if (!E.rough) {
+      v6 += v2;
+      v2 = T(0);
+    }
+    c.st(A(VA_SD + a), v6);
+    if (order2(K)) c.st(A(VA_SD2 + a), v2);
+    c.st(A(VA_CP + a), cp[a]);
+    c.st(A(VA_CU + a), cu[a]);
+    c.st(A(VA_CB + a), cb[a]);
+  }
+  T eb = ph.gamma1 * Pb;
+  // Newtonian cooling (eq. NewtonCool, eq. rhocool): -(e - rho e_cool) / t
+  // times r2 / (1 + r2) or 1 / (1 + r2)
+  if (tm & T_COOL) {
+    T fac = T(1), dfac = T(0);
+    if (ph.cool_cut) {
+      const T r = rho * ph.inv_rho_cool, r2 = r * r, d = T(1) / (T(1) + r2);
+      fac = (ph.cool_cut == 1 ? r2 : T(1)) * d;
+      dfac = (ph.cool_cut == 1 ? T(2) : T(-2)) * r * d * d * ph.inv_rho_cool;
+    }
+    eb -= ph.inv_tcool * fac * we;
+    rb += (ph.e_cool * fac - (e - rho * ph.e_cool) * dfac) * ph.inv_tcool * we;
+  }
+  c.st(A(VA_RHOB), rb);
+  c.st(A(VA_EB), eb);
+}
+
+// T_SMAG: the centre shear's cotangents back on the edges.
+VJP_KERNEL k_smag_back(VK<T> K) {
+  VJP_CELL
+  const int e = (int)blockIdx.y;
+  const T v = e == X ? c.template iiT<Y, 1, Z, 1>(A(VA_SC))
+                     : (e == Y ? c.template iiT<X, 1, Z, 1>(A(VA_SC + 1)) : c.template iiT<X, 1, Y, 1>(A(VA_SC + 2)));
+  T* h = A(VA_EDGE + e * EQ_COUNT + EQ_HS);
+  c.st(h, c.ld(h) + T(0.5) * v);
+}
+
+template <class T, bool W>
+__device__ __forceinline__ void add_to(const Cell<T, W>& c, const VK<T>& K, int v, T x) {
+  T* g = K.g.p[v] + c.b.off;
+  c.st(g, K.acc ? c.ld(g) + x : x);
+}
+
+// Component a of the velocity: every gather, then the momentum and the face
+// density it came from.
+template <int AX, class T, bool W, class F, class G>
+__device__ __forceinline__ void vel_back(const Cell<T, W>& c, const VK<T>& K, const F& A, const G& Wt) {
+  constexpr int B1 = (AX + 1) % 3, A2 = (AX + 2) % 3;   // edges along A2 (as P) and along B1 (as Q)
+  const unsigned tm = K.ph.terms;
+  auto Eq = [&](int e, int q) { return A(VA_EDGE + e * EQ_COUNT + q); };
+  T ub = c.ld(A(VA_UF + AX)) + c.template dnT<B1>(Eq(A2, EQ_UAB)) + c.template ddnT<B1>(Eq(A2, EQ_HS)) +
+         c.template dnT<A2>(Eq(B1, EQ_UBA)) + c.template ddnT<A2>(Eq(B1, EQ_HS)) + c.template upT<AX>(A(VA_CU + AX)) +
+         c.template dupT<AX>(A(VA_SD + AX));
+  if (order2(K))
+    ub += c.template d2nT<B1>(A(VA_HS2 + A2)) + c.template d2nT<A2>(A(VA_HS2 + B1)) +
+          c.template d2uT<AX>(A(VA_SD2 + AX));
+  T pb = c.template dnT<B1>(Eq(A2, EQ_PAB)) + c.template dnT<A2>(Eq(B1, EQ_PBA)) + c.template upT<AX>(A(VA_CP + AX));
+  if (tm & T_CONT) pb -= c.template dupT<AX>(Wt(0));
+  if (tm & T_CORI) {
+    // p_AX drives dp_P and dp_Q (P, Q the next axes): -2 Omega x p
+    pb += K.ph.cor2[A2] * c.template iiT<AX, 1, B1, 0>(Wt(1 + B1)) * T(-1);
+    pb += K.ph.cor2[B1] * c.template iiT<AX, 1, A2, 0>(Wt(1 + A2));
+  }
+  const T r = c.ld(A(VA_R + AX));
+  const T q = ub / r;
+  T rb = c.ld(A(VA_RF + AX)) - q * c.ld(A(VA_U + AX));
+  if constexpr (AX == X) rb += c.template dnT<Y>(Eq(Z, EQ_RHO)) + c.template dnT<Z>(Eq(Y, EQ_RHO));
+  if constexpr (AX == Y) rb += c.template dnT<Z>(Eq(X, EQ_RHO));
+  c.st(A(VA_RB + AX), rb);
+  add_to(c, K, 1 + AX, pb + q);
+}
+template <int AX, class T, bool W, class F>
+__device__ __forceinline__ void field_back(const Cell<T, W>& c, const VK<T>& K, const F& A) {
+  constexpr int B1 = (AX + 1) % 3, A2 = (AX + 2) % 3;
+  auto Eq = [&](int e, int q) { return A(VA_EDGE + e * EQ_COUNT + q); };
+  T v = c.template dnT<B1>(Eq(A2, EQ_BAB)) - c.template ddnT<B1>(Eq(A2, EQ_J)) + c.template dnT<A2>(Eq(B1, EQ_BBA)) +
+        c.template ddnT<A2>(Eq(B1, EQ_J)) + c.template upT<AX>(A(VA_CB + AX));
+  if ((K.ph.terms & T_DIVB) && K.dt > 0.0) v += c.template dupT<AX>(A(VA_DVB));
+  add_to(c, K, 5 + AX, v);
+}
+// blockIdx.y 0..2 the velocities, 3..5 the magnetic field.
+VJP_KERNEL k_vector_back(VK<T> K) {
+  VJP_CELL
+  switch (blockIdx.y) {
+    case 0: vel_back<X>(c, K, A, Wt); break;
+    case 1: vel_back<Y>(c, K, A, Wt); break;
+    case 2: vel_back<Z>(c, K, A, Wt); break;
+    case 3: field_back<X>(c, K, A); break;
+    case 4: field_back<Y>(c, K, A); break;
+    default: field_back<Z>(c, K, A); break;
+  }
+}
+
+// e_m, the pressure gradient and gravity, then e and rho.
+VJP_KERNEL k_scalar_back(VK<T> K) {
+  VJP_CELL
+  const Phys<T>& ph = K.ph;
+  const T rho = c.ld(S(0)), em = c.ld(A(VA_EM));
+  T eb = c.ld(A(VA_EB)) + c.template dnT<X>(A(VA_XE)) + c.template dnT<Y>(A(VA_XE + 1)) +
+         c.template dnT<Z>(A(VA_XE + 2));
+  if (tm & T_PRES) {
+    if (tm & T_LNP)
+      eb += (c.template dnT<X>(A(VA_QI)) + c.template ddnT<X>(A(VA_QD)) + c.template dnT<Y>(A(VA_QI + 1)) +
+             c.template ddnT<Y>(A(VA_QD + 1)) + c.template dnT<Z>(A(VA_QI + 2)) + c.template ddnT<Z>(A(VA_QD + 2))) /
+            c.ld(S(4));
+    else
+      eb -= ph.gamma1 * (c.template ddnT<X>(Wt(1)) + c.template ddnT<Y>(Wt(2)) + c.template ddnT<Z>(Wt(3)));
+  }
+  T rb = c.ld(A(VA_RHOB)) + c.template dnT<X>(A(VA_RB)) + c.template dnT<Y>(A(VA_RB + 1)) +
+         c.template dnT<Z>(A(VA_RB + 2));
+  if (tm & T_GRAV) rb -= ph.gz * c.template dnT<Z>(Wt(3));
+  if (tm & T_EDIFF) {
+    T mb = c.template dnT<X>(A(VA_XEM)) + c.template dnT<Y>(A(VA_XEM + 1)) + c.template dnT<Z>(A(VA_XEM + 2)) +
+           (c.template ddnT<X>(A(VA_DLEM)) + c.template ddnT<Y>(A(VA_DLEM + 1)) + c.template ddnT<Z>(A(VA_DLEM + 2))) /
+               em;
+    if (tm & T_EDIFFAV)   // the plane mean's log: its cells' cotangents summed over the plane
+      mb -= T(K.pm[K.nplanes + b.poff + c.k]) / T(K.pm[b.poff + c.k]);
+    const T q = mb / rho;
+    eb += q;
+    rb -= q * em;
+  }
+  add_to(c, K, 4, eb);
+  add_to(c, K, 0, rb);
+}
+
+// The mean of src over each z plane of every box, in float64 and a fixed
+// order (one workgroup per plane).
 constexpr int kPlaneBlock = 256;
 template <class T>
-__global__ __launch_bounds__(kPlaneBlock) void k_vm_psum(const BoxDev* __restrict__ boxes, int nbox,
-                                                        const T* __restrict__ src, double* __restrict__ pm) {
+__global__ __launch_bounds__(kPlaneBlock) void k_plane_mean(const BoxDev* __restrict__ boxes, int nbox,
+                                                           const T* __restrict__ src, double* __restrict__ pm) {
   __shared__ double sh[kPlaneBlock];
   const int P = (int)blockIdx.x;
   int bi = 0;
@@ -1198,20 +1079,139 @@ __global__ __launch_bounds__(kPlaneBlock) void k_vm_psum(const BoxDev* __restric
 }
 
 template <class T>
-__global__ __launch_bounds__(kBlock) void k_vm_pbcast(const BoxDev* boxes, const Blk* tab,
-                                                      const double* __restrict__ pm, T* dst, int over) {
-  VM_PROLOGUE
-  int i, j, k;
-  coords(i, j, k);
-  const T v = T(pm[bx_.poff + k]);
-  dst[o] = over ? v : dst[o] + v;
+__global__ __launch_bounds__(kBlock) void k_axpby8(const BoxDev* boxes, const Blk* tab, P8<T> y, CP8<T> x, T a, T bx,
+                                                   int mask) {
+  const Blk t = tab[blockIdx.x];
+  if ((int)threadIdx.x >= t.n) return;
+  const BoxDev& b = boxes[t.box];
+  const unsigned q = (unsigned)t.start + threadIdx.x;
+  const long long o = b.off + q;
+  const int k = (int)(q / ((unsigned)b.nx * (unsigned)b.ny));
+  const bool cen = !mask || !b.wall || (k >= b.g0 && k < b.g1);
+  T yv[8], xv[8];
+#pragma unroll
+  for (int v = 0; v < 8; ++v) {
+    yv[v] = a == T(0) ? T(0) : a * y.p[v][o];
+    xv[v] = bx * x.p[v][o];
+  }
+#pragma unroll
+  for (int v = 0; v < 8; ++v) {
+    bool keep = cen;
+    if (mask && b.wall && v == 3) keep = k > b.g0 && k < b.g1;
+    if (mask && b.wall && v == 7) keep = k >= b.g0 && k <= b.g1;
+    y.p[v][o] = keep ? yv[v] + xv[v] : T(0);
+  }
+}
+
+template <class T, bool W>
+void run(const VjpLaunch& L, const VK<T>& K) {
+  const unsigned tm = K.ph.terms;
+  const int g = 8 * ((L.nblk + 7) / 8);
+  const dim3 blk(kBlock);
+  auto go = [&](void (*kern)(VK<T>), int roles) { hipLaunchKernelGGL(kern, dim3(g, roles), blk, 0, L.stream, K); };
+  auto max1 = [&](int ax, int src, int dst) {
+    auto* kern = ax == X ? k_max1<T, W, X> : (ax == Y ? k_max1<T, W, Y> : k_max1<T, W, Z>);
+    hipLaunchKernelGGL(kern, dim3(g), blk, 0, L.stream, K, src, dst);
+  };
+  auto max1T = [&](int ax, int prim, int yb, int dst, int comps) {
+    auto* kern = ax == X ? k_max1T<T, W, X> : (ax == Y ? k_max1T<T, W, Y> : k_max1T<T, W, Z>);
+    hipLaunchKernelGGL(kern, dim3(g, comps), blk, 0, L.stream, K, prim, yb, dst);
+  };
+  auto plane_mean = [&](int id, double* pm) {
+    hipLaunchKernelGGL(k_plane_mean<T>, dim3(L.nplanes), dim3(kPlaneBlock), 0, L.stream, L.boxes, L.nbox,
+                       (const T*)(K.base + (long long)id * K.stride), pm);
+  };
+  const bool visc = tm & T_VISC, cst = K.ph.nu_const > T(0);
+  const bool av = (tm & T_EDIFF) && (tm & T_EDIFFAV);
+  go(k_prim<T, W>, 1);
+  if (av) plane_mean(VA_EM, L.pm);
+  if (visc && (tm & T_ORDER2)) {
+    go(k_rough<T, W>, 1);
+    go(k_rough_flags<T, W>, 1);
+  }
+  if (!cst) {
+    if (tm & T_SMAG) go(k_shear<T, W>, 3);
+    go(k_nus<T, W>, 1);
+    if (tm & T_MAX5)
+      for (int m = 0; m < 6; ++m) max1(m / 2, mx_id(m), mx_id(m + 1));
+    else
+      go(k_max3<T, W>, 1);
+  }
+  go(k_mean<T, W>, 1);
+  go(k_lines<T, W>, 1);
+  if (visc && (tm & T_QUENCH)) {
+    go(k_tau<T, W>, 4);
+    go(k_quench<T, W>, 6);
+    go(k_quench_max<T, W>, 6);
+    go(k_taub<T, W>, 4);
+    max1T(Z, VA_Q2, VA_QB0, VA_QB1, 6);
+    max1T(Y, VA_Q1, VA_QB1, VA_QB0, 6);
+    go(k_quenchT<T, W>, 6);
+    go(k_quenchT2<T, W>, 6);
+  }
+  go(k_edge_face<T, W>, 6);
+  go(k_lines_back<T, W>, 1);
+  if (av) plane_mean(VA_EDX, L.pm + L.nplanes);
+  int mb = VA_MB0;
+  if (!cst) {
+    go(k_nu_back<T, W>, 1);
+    go(k_mean_back<T, W>, 1);
+    // back through the maxima but the first, which the centre pass takes
+    for (int m = K.nmax - 1; m > 0; --m) {
+      const int to = mb == VA_MB0 ? VA_MB1 : VA_MB0;
+      max1T(K.nmax == 6 ? m / 2 : m, mx_id(m), mb, to, 1);
+      mb = to;
+    }
+  }
+  hipLaunchKernelGGL((k_centre_back<T, W>), dim3(g), blk, 0, L.stream, K, mb);
+  if (!cst && (tm & T_SMAG)) go(k_smag_back<T, W>, 3);
+  go(k_vector_back<T, W>, 6);
+  go(k_scalar_back<T, W>, 1);
+}
+
+}  // namespace
+
+int vjp_arrays(unsigned terms) {
+  int n = VA_CORE;
+  if (terms & T_MAX5) n = VA_LNP;
+  if (terms & T_LNP) n = VA_DVB;
+  if (terms & T_DIVB) n = VA_EDX;
+  if (terms & T_EDIFFAV) n = VA_SE;
+  if (terms & T_SMAG) n = VA_TAU;
+  if (terms & T_QUENCH) n = VA_RGH;
+  if (terms & T_ORDER2) n = VA_COUNT;
+  return n;
 }
 
 template <class T>
-static void vm_pmean(const VLaunch& L, const T* src, T* dst, int over) {
-  hipLaunchKernelGGL(k_vm_psum<T>, dim3(L.nplanes), dim3(kPlaneBlock), 0, L.stream, L.boxes, L.nbox, src, L.pm);
-  hipLaunchKernelGGL(k_vm_pbcast<T>, dim3(L.nblk), dim3(kBlock), 0, L.stream, L.boxes, L.tab,
-                     (const double*)L.pm, dst, over);
+void vjp_rhs(const VjpLaunch& L, const Phys<T>& ph, double nu2, double c_smag, double c_divb, CP8<T> s, CP8<T> w,
+             P8<T> g, bool acc, T* base, long long stride, double dt) {
+  VK<T> K;
+  K.boxes = L.boxes;
+  K.tab = L.tab;
+  K.nblk = L.nblk;
+  K.s = s;
+  K.w = w;
+  K.g = g;
+  K.base = base;
+  K.stride = stride;
+  K.zt = static_cast<const T*>(L.ztab);
+  K.pm = L.pm;
+  K.nplanes = L.nplanes;
+  K.ph = ph;
+  K.nu2 = nu2;
+  K.c_smag = c_smag;
+  K.c_divb = c_divb;
+  K.dt = dt;
+  K.acc = acc ? 1 : 0;
+  K.nmax = (ph.terms & T_MAX5) ? 6 : 3;
+  if (L.wall) run<T, true>(L, K);
+  else run<T, false>(L, K);
+}
+
+template <class T> void vjp_axpby8(const VjpLaunch& L, P8<T> y, CP8<T> x, double a, double b, bool mask) {
+  hipLaunchKernelGGL(k_axpby8<T>, dim3(L.nblk), dim3(kBlock), 0, L.stream, L.boxes, L.tab, y, x, T(a), T(b),
+                     mask ? 1 : 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -1345,26 +1345,7 @@ __global__ __launch_bounds__(kBlock) void k_fill_vjp3(const BoxDev* boxes, const
     if (!(v == 7 && k == b.g1)) g.p[v][o] = T(0);
 }
 
-// Zero where the right-hand side is zeroed on a wall box: the ghost planes
-// of centred fields, p_z outside the open interior faces, B_z outside the
-// faces from wall to wall.
-template <class T>
-__global__ __launch_bounds__(kBlock) void k_wall_mask8(const BoxDev* boxes, const Blk* tab, P8<T> y) {
-  VM_PROLOGUE
-  if (!bx_.wall) return;
-  int i, j, k;
-  coords(i, j, k);
-  (void)i;
-  (void)j;
-  const bool cen = k >= bx_.g0 && k < bx_.g1;
-#pragma unroll
-  for (int v = 0; v < 8; ++v) {
-    const bool keep = v == 3 ? (k > bx_.g0 && k < bx_.g1) : (v == 7 ? (k >= bx_.g0 && k <= bx_.g1) : cen);
-    if (!keep) y.p[v][o] = T(0);
-  }
-}
-
-template <class T> void vm_fill_vjp(const VLaunch& L, CP8<T> s, P8<T> g, T* tmp, long long stride) {
+template <class T> void vjp_fill(const VjpLaunch& L, CP8<T> s, P8<T> g, T* tmp, long long stride) {
   if (L.nghost_blk == 0) return;
   T* t[6];
   for (int q = 0; q < 6; ++q) t[q] = tmp + (long long)q * stride;
@@ -1378,56 +1359,13 @@ template <class T> void vm_fill_vjp(const VLaunch& L, CP8<T> s, P8<T> g, T* tmp,
   }
 }
 
-template <class T> void vm_wall_mask(const VLaunch& L, P8<T> g) {
-  hipLaunchKernelGGL(k_wall_mask8<T>, dim3(L.nblk), dim3(kBlock), 0, L.stream, L.boxes, L.tab, g);
-}
-
-template <class T>
-void vm_forward(const VLaunch& L, const VPlan& P, const VFused* d_fused, T* base, long long stride) {
-  for (const VGroup& G : P.groups) {
-    const VInstr& I = P.fused[G.first].f;
-    if (I.op == V_ROUGH)
-      hipLaunchKernelGGL(k_vm_rough<T>, dim3(L.nblk), dim3(kBlock), 0, L.stream, L.boxes, L.tab, d_fused,
-                         G.first, base, stride);
-    else if (I.op == V_PMEAN)
-      vm_pmean<T>(L, base + I.a * stride, base + I.out * stride, 1);
-    else
-      hipLaunchKernelGGL(k_vm_group<T>, dim3(L.nblk), dim3(kBlock), 0, L.stream, L.boxes, L.tab, d_fused,
-                         G.first, G.count, base, stride, (const T*)L.ztab);
-  }
-}
-
-template <class T>
-void vm_backward(const VLaunch& L, const VPlan& P, const VStep* d_bsteps, const T* base, T* cbase,
-                 long long stride) {
-  const int grid = (L.nblk + kBwdCells - 1) / kBwdCells;
-  for (const VGroup& G : P.bgroups) {
-    const VStep& S = P.bsteps[G.first];
-    if (S.f.op == V_PMEAN) {
-      vm_pmean<T>(L, (const T*)(cbase + S.cout * stride), cbase + S.ca * stride, S.over & 1);
-      continue;
-    }
-    hipLaunchKernelGGL(k_vm_bwd<T>, dim3(grid), dim3(kBlock), 0, L.stream, L.boxes, L.tab, L.nblk,
-                       d_bsteps, G.first, G.count, base, cbase, stride, (const T*)L.ztab);
-  }
-}
-
-template <class T> void vm_axpby8(const VLaunch& L, P8<T> y, CP8<T> x, double a, double b) {
-  hipLaunchKernelGGL(k_axpby8<T>, dim3(L.nblk), dim3(kBlock), 0, L.stream, L.boxes, L.tab, y, x, T(a),
-                     T(b));
-}
-
-template void vm_forward<float>(const VLaunch&, const VPlan&, const VFused*, float*, long long);
-template void vm_forward<double>(const VLaunch&, const VPlan&, const VFused*, double*, long long);
-template void vm_backward<float>(const VLaunch&, const VPlan&, const VStep*, const float*, float*,
-                                 long long);
-template void vm_backward<double>(const VLaunch&, const VPlan&, const VStep*, const double*, double*,
-                                  long long);
-template void vm_axpby8<float>(const VLaunch&, P8<float>, CP8<float>, double, double);
-template void vm_axpby8<double>(const VLaunch&, P8<double>, CP8<double>, double, double);
-template void vm_fill_vjp<float>(const VLaunch&, CP8<float>, P8<float>, float*, long long);
-template void vm_fill_vjp<double>(const VLaunch&, CP8<double>, P8<double>, double*, long long);
-template void vm_wall_mask<float>(const VLaunch&, P8<float>);
-template void vm_wall_mask<double>(const VLaunch&, P8<double>);
+template void vjp_rhs<float>(const VjpLaunch&, const Phys<float>&, double, double, double, CP8<float>, CP8<float>,
+                            P8<float>, bool, float*, long long, double);
+template void vjp_rhs<double>(const VjpLaunch&, const Phys<double>&, double, double, double, CP8<double>,
+                             CP8<double>, P8<double>, bool, double*, long long, double);
+template void vjp_axpby8<float>(const VjpLaunch&, P8<float>, CP8<float>, double, double, bool);
+template void vjp_axpby8<double>(const VjpLaunch&, P8<double>, CP8<double>, double, double, bool);
+template void vjp_fill<float>(const VjpLaunch&, CP8<float>, P8<float>, float*, long long);
+template void vjp_fill<double>(const VjpLaunch&, CP8<double>, P8<double>, double*, long long);
 
 }  // namespace smhd

@@ -15,9 +15,9 @@
 #include <vector>
 
 #include "../../include/mhd.h"
-#include "mhd_adjoint.hpp"
 #include "mhd_clean.hpp"
 #include "mhd_kernels.hpp"
+#include "mhd_adjoint.hpp"
 #include "mhd_zmarch_api.hpp"
 
 using namespace smhd;
@@ -44,11 +44,7 @@ struct mhd_ctx {
   RedTotal* d_tot = nullptr;       // their fold
   void* adj = nullptr;             // adjoint workspace (allocated on first use)
   size_t adj_bytes = 0;
-  VPlan* prog = nullptr;           // the right-hand side as a program (adjoint)
-  double prog_dt = 0.0;            // the dt it was built for (div B diffusion; 0: without)
-  double* d_pm = nullptr;          // plane means of the program (V_PMEAN), per plane
-  VFused* d_fused = nullptr;       // prog->fused in device memory
-  VStep* d_bsteps = nullptr;       // prog->bsteps in device memory
+  double* d_pm = nullptr;          // the adjoint's plane means, two per plane
   // z-march stage kernels: work items, tile shape, Courant partials, dt
   ZItem* d_items[ZC_COUNT] = {};   // one table per class of passes
   int nitems[ZC_COUNT] = {};
@@ -559,10 +555,7 @@ void mhd_destroy(mhd_ctx* c) {
   (void)hipFree(c->d_red);
   (void)hipFree(c->d_tot);
   (void)hipFree(c->adj);
-  delete c->prog;
   (void)hipFree(c->d_pm);
-  (void)hipFree(c->d_fused);
-  (void)hipFree(c->d_bsteps);
   for (ZItem* d : c->d_items) (void)hipFree(d);
   (void)hipFree(c->d_cpart);
   (void)hipFree(c->d_dt);
@@ -693,6 +686,9 @@ int mhd_init(const mhd_params* p, void* hip_stream, mhd_ctx** out) {
     d.hmin = std::min(d.dx, std::min(d.dy, dzmin));
     d.hmax = std::max(d.dx, std::max(d.dy, dzmax));
     d.stretched = x.zc ? 1 : 0;
+    d.hinv[0] = 1.0 / d.dx;
+    d.hinv[1] = 1.0 / d.dy;
+    d.hinv[2] = 1.0 / d.dz;
     d.joff = -1;
     if (p->nu_const > 0.0) {
       for (int a = 0; a < 3; ++a) d.lv[a] = d.le[a] = d.hmin;
@@ -898,56 +894,35 @@ static int do_step(mhd_ctx* c, void* const f[8], void* const t1[8], void* const 
   return check_launch(c, "mhd_step launch");
 }
 
-// The right-hand side as a planned program, built once per context, and
-// again when the div B diffusion's dt changes (dt 0: without that term).
-static int ensure_program(mhd_ctx* c, double dt) {
-  if (!(c->p.terms & MHD_T_DIVB)) dt = 0.0;
-  if (c->prog && c->prog_dt == dt) return MHD_OK;
-  if (c->prog) {
-    delete c->prog;
-    c->prog = nullptr;
-    (void)hipFree(c->d_fused);
-    (void)hipFree(c->d_bsteps);
-    c->d_fused = nullptr;
-    c->d_bsteps = nullptr;
-  }
-  if (!c->d_pm && hipMalloc(&c->d_pm, sizeof(double) * std::max(1, c->nplanes)) != hipSuccess)
-    return fail(c, MHD_ENOMEM, "adjoint plane means");
-  VPlan* P = nullptr;
-  try {
-    P = new VPlan(plan_program(build_rhs_program(c->p, dt)));
-  } catch (...) {
-    return fail(c, MHD_ENOMEM, "adjoint program");
-  }
-  const size_t bytes = sizeof(VFused) * P->fused.size(), bbytes = sizeof(VStep) * P->bsteps.size();
-  hipError_t e = hipMalloc(&c->d_fused, bytes);
-  if (e == hipSuccess) e = hipMemcpy(c->d_fused, P->fused.data(), bytes, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMalloc(&c->d_bsteps, bbytes);
-  if (e == hipSuccess) e = hipMemcpy(c->d_bsteps, P->bsteps.data(), bbytes, hipMemcpyHostToDevice);
-  if (e != hipSuccess) {
-    (void)hipFree(c->d_fused);
-    (void)hipFree(c->d_bsteps);
-    c->d_fused = nullptr;
-    c->d_bsteps = nullptr;
-    delete P;
-    return fail(c, MHD_ENOMEM, "adjoint program upload");
-  }
-  c->prog = P;
-  c->prog_dt = dt;
-  return MHD_OK;
-}
-
 // Adjoint of one RK step (dt fixed).  With f_s the stage inputs, U_s the
 // 2N-storage derivative and F_s = F(f_s):
 //   U_s = alpha_s U_{s-1} + F_s,  f_{s+1} = f_s + beta_s dt U_s,
 // so, backwards from gbar = gbar_in (the cotangent of f_3):
 //   Ubar_s = alpha_{s+1} Ubar_{s+1} + beta_s dt gbar,
 //   gbar  += (dF/df at f_s)^T Ubar_s.
-// f_1 and f_2 come from the fused stage kernels; F's intermediates at each
-// f_s from the program's forward run, just before its transpose.
-static VLaunch make_vlaunch(mhd_ctx* c) {
-  return VLaunch{c->d_boxes, c->d_tab, c->nblk, c->stream, (int)c->h_boxes.size(), c->nplanes, c->d_pm,
-                 c->d_ztab, c->d_gtab, c->ngblk};
+// f_1 and f_2 come from the fused stage kernels; the transpose recomputes
+// the intermediates it needs at each f_s.
+static VjpLaunch make_vjp(mhd_ctx* c, bool walls) {
+  VjpLaunch L;
+  L.boxes = c->d_boxes;
+  L.tab = c->d_tab;
+  L.nblk = c->nblk;
+  L.stream = c->stream;
+  L.nbox = (int)c->h_boxes.size();
+  L.nplanes = c->nplanes;
+  L.wall = walls ? 1 : 0;
+  L.pm = c->d_pm;
+  L.ztab = c->d_ztab;
+  L.gtab = c->d_gtab;
+  L.nghost_blk = c->ngblk;
+  return L;
+}
+
+// g (+)= (dF/df)^T w at s (dt 0: F without the div B diffusion).
+template <class T>
+static void rhs_transpose(mhd_ctx* c, bool walls, CP8<T> s, CP8<T> w, P8<T> g, bool acc, T* base, double dt) {
+  vjp_rhs<T>(make_vjp(c, walls), make_phys<T>(c->p), c->p.nu2, c->p.c_smag, c->p.c_divb, s, w, g, acc, base, c->nelem,
+             dt);
 }
 
 static bool any_wall(const mhd_ctx* c) {
@@ -956,14 +931,24 @@ static bool any_wall(const mhd_ctx* c) {
   return false;
 }
 
-// The adjoint workspace: the program's value and cotangent slots, then the
-// stage states and dU (25 arrays; 16 more with walls: the filled input and
-// the step's end state).
-template <class T> static T* adjoint_workspace(mhd_ctx* c, const VPlan& P, bool walls, int& rc) {
+// The adjoint workspace: the transpose's arrays, then the stage states and
+// dU (24 arrays; 16 more with walls: the filled input and the step's end
+// state).  A box of 2^32 bytes per field would need more than any device
+// holds (and the transpose addresses a box with 32-bit offsets).
+template <class T> static T* adjoint_workspace(mhd_ctx* c, bool walls, int& rc) {
   const long long n = c->nelem;
-  const size_t narr = (size_t)P.nval + P.ncot + 25 + (walls ? 16 : 0);
+  const size_t narr = (size_t)vjp_arrays(c->p.terms) + 24 + (walls ? 16 : 0);
   const size_t need = narr * (size_t)n * c->esize;
   rc = MHD_OK;
+  for (const BoxDev& b : c->h_boxes)
+    if ((unsigned long long)b.ncell * c->esize >= (1ULL << 32)) {
+      rc = fail(c, MHD_ENOMEM, "adjoint workspace");
+      return nullptr;
+    }
+  if (!c->d_pm && hipMalloc(&c->d_pm, 2 * sizeof(double) * std::max(1, c->nplanes)) != hipSuccess) {
+    rc = fail(c, MHD_ENOMEM, "adjoint plane means");
+    return nullptr;
+  }
   if (c->adj_bytes < need) {
     (void)hipFree(c->adj);
     c->adj = nullptr;
@@ -979,33 +964,28 @@ template <class T> static T* adjoint_workspace(mhd_ctx* c, const VPlan& P, bool 
 
 // One RK step's adjoint at fixed dt.  The stage states are recomputed with
 // the stage kernels; then, stage by stage backwards, Ubar = alpha Ubar +
-// beta dt G, the program's forward run at the stage state and its reverse
-// sweep seeded with Ubar give G += (dF/df)^T Ubar.  With walls the states
-// are filled (the step fills before every F and after the last stage),
-// Ubar is masked like F, and G passes through the fill's transpose after
-// each stage (and first through that of the end state's fill).
+// beta dt G and G += (dF/df)^T Ubar.  With walls the states are filled (the
+// step fills before every F and after the last stage), Ubar is masked like
+// F, and G passes through the fill's transpose after each stage (and first
+// through that of the end state's fill).
 template <class T>
 static int do_adjoint(mhd_ctx* c, void* const fn[8], double dt, void* const gin[8],
                       void* const gout[8]) {
-  if (int rc = ensure_program(c, dt)) return rc;
-  const VPlan& P = *c->prog;
   const long long n = c->nelem;
   const bool walls = any_wall(c);
   int rc = MHD_OK;
-  T* base = adjoint_workspace<T>(c, P, walls, rc);
+  T* base = adjoint_workspace<T>(c, walls, rc);
   if (!base) return rc;
-  T* cbase = base + (long long)P.nval * n;
-  T* rest = cbase + (long long)P.ncot * n;
+  T* rest = base + (long long)vjp_arrays(c->p.terms) * n;
   auto set8 = [&](int first) {
     P8<T> q;
     for (int v = 0; v < 8; ++v) q.p[v] = rest + (long long)(first + v) * n;
     return q;
   };
   const P8<T> F1 = set8(0), F2 = set8(8), U = set8(16);
-  const P8<T> S0 = walls ? set8(25) : p8<T>(fn), F3 = set8(walls ? 33 : 0);
+  const P8<T> S0 = walls ? set8(24) : p8<T>(fn), F3 = set8(walls ? 32 : 0);
   const P8<T> G = p8<T>(gout);
   const size_t bytes = (size_t)n * c->esize;
-  T* zeros = rest + 24LL * n;   // the cotangent of an input F does not read
   const Launch L = make_launch(c);
   hipError_t e = hipSuccess;
   if (walls) {
@@ -1030,94 +1010,57 @@ static int do_adjoint(mhd_ctx* c, void* const fn[8], double dt, void* const gin[
     if (walls) launch_ghost<T>(L, a.f_out);
   }
   L.at(PASS_ADJOINT);
-  const VLaunch V = make_vlaunch(c);
-  e = hipMemsetAsync(zeros, 0, bytes, c->stream);
+  const VjpLaunch V = make_vjp(c, walls);
   for (int v = 0; v < 8 && e == hipSuccess; ++v)
     e = hipMemcpyAsync(G.p[v], gin[v], bytes, hipMemcpyDeviceToDevice, c->stream);
-  // (value slots are free outside the program's runs: the fill's transpose
+  if (e != hipSuccess) return fail(c, MHD_EHIP, hipGetErrorString(e));
+  // (the transpose's arrays are free between its runs: the fill's transpose
   // keeps its temporaries there)
-  if (walls && e == hipSuccess) vm_fill_vjp<T>(V, cp8<T>(F3), G, base, n);
+  if (walls) vjp_fill<T>(V, cp8<T>(F3), G, base, n);
   const P8<T> Ub = U;   // U is free again: it becomes Ubar
-  for (int s = 2; s >= 0 && e == hipSuccess; --s) {
-    vm_axpby8<T>(V, Ub, cp8<T>(G), s == 2 ? 0.0 : kAlpha[s + 1], kBeta[s] * dt);
-    if (walls) vm_wall_mask<T>(V, Ub);
+  for (int s = 2; s >= 0; --s) {
+    vjp_axpby8<T>(V, Ub, cp8<T>(G), s == 2 ? 0.0 : kAlpha[s + 1], kBeta[s] * dt, walls);
     const P8<T> fs = s == 0 ? S0 : (s == 1 ? F1 : F2);
-    for (int v = 0; v < 8 && e == hipSuccess; ++v)
-      e = hipMemcpyAsync(base + (long long)v * n, fs.p[v], bytes, hipMemcpyDeviceToDevice, c->stream);
-    if (e != hipSuccess) break;
-    vm_forward<T>(V, P, c->d_fused, base, n);
-    for (int v = 0; v < 8 && e == hipSuccess; ++v)
-      e = hipMemcpyAsync(cbase + (long long)P.cout[v] * n, Ub.p[v], bytes, hipMemcpyDeviceToDevice,
-                         c->stream);
-    if (e != hipSuccess) break;
-    vm_backward<T>(V, P, c->d_bsteps, base, cbase, n);
-    CP8<T> cin;
-    bool any = false;
-    for (int v = 0; v < 8; ++v) {
-      cin.p[v] = P.cin[v] >= 0 ? cbase + (long long)P.cin[v] * n : zeros;
-      any |= P.cin[v] >= 0;
-    }
-    if (any) vm_axpby8<T>(V, G, cin, 1.0, 1.0);
-    if (walls) vm_fill_vjp<T>(V, cp8<T>(fs), G, base, n);
+    rhs_transpose<T>(c, walls, cp8<T>(fs), cp8<T>(Ub), G, true, base, dt);
+    if (walls) vjp_fill<T>(V, cp8<T>(fs), G, base, n);
   }
   L.at(PASS_END);
-  if (e != hipSuccess) return fail(c, MHD_EHIP, hipGetErrorString(e));
   return check_launch(c, "mhd_step_adjoint launch");
 }
 
-// (dF/df)^T wbar at the state f: the program's forward run at f, its
-// reverse sweep seeded with wbar.  With walls, F is the right-hand side of
-// mhd_rhs, which fills the ghost planes first: the run is at the filled
-// state, the seed is masked like F, and the result passes through the
-// fill's transpose.
+// (dF/df)^T wbar at the state f.  With walls, F is the right-hand side of
+// mhd_rhs, which fills the ghost planes first: the transpose is taken at the
+// filled state, the seed is masked like F, and the result passes through
+// the fill's transpose.
 template <class T>
 static int do_rhs_adjoint(mhd_ctx* c, void* const f[8], void* const wbar[8],
                           void* const fbar[8]) {
-  if (int rc = ensure_program(c, 0.0)) return rc;
-  const VPlan& P = *c->prog;
   const long long n = c->nelem;
   const bool walls = any_wall(c);
   int rc = MHD_OK;
-  T* base = adjoint_workspace<T>(c, P, walls, rc);
+  T* base = adjoint_workspace<T>(c, walls, rc);
   if (!base) return rc;
-  T* cbase = base + (long long)P.nval * n;
-  T* rest = cbase + (long long)P.ncot * n;
+  T* rest = base + (long long)vjp_arrays(c->p.terms) * n;
   const size_t bytes = (size_t)n * c->esize;
   const Launch L = make_launch(c);
   L.at(PASS_ADJOINT);
-  const VLaunch V = make_vlaunch(c);
-  P8<T> S, W;
-  for (int v = 0; v < 8; ++v) {
-    S.p[v] = rest + (long long)v * n;          // the filled state (walls)
-    W.p[v] = rest + (long long)(8 + v) * n;    // the masked seed (walls)
-  }
-  hipError_t e = hipSuccess;
-  for (int v = 0; v < 8 && e == hipSuccess; ++v)
-    e = hipMemcpyAsync(base + (long long)v * n, f[v], bytes, hipMemcpyDeviceToDevice, c->stream);
+  const VjpLaunch V = make_vjp(c, walls);
+  P8<T> S = p8<T>(f), Wb = p8<T>(wbar);
+  const P8<T> G = p8<T>(fbar);
   if (walls) {
-    for (int v = 0; v < 8 && e == hipSuccess; ++v) {
-      e = hipMemcpyAsync(S.p[v], f[v], bytes, hipMemcpyDeviceToDevice, c->stream);
-      if (e == hipSuccess) e = hipMemcpyAsync(W.p[v], wbar[v], bytes, hipMemcpyDeviceToDevice, c->stream);
+    hipError_t e = hipSuccess;
+    for (int v = 0; v < 8; ++v) {
+      S.p[v] = rest + (long long)v * n;          // the filled state
+      Wb.p[v] = rest + (long long)(8 + v) * n;   // the masked seed
+      if (e == hipSuccess) e = hipMemcpyAsync(S.p[v], f[v], bytes, hipMemcpyDeviceToDevice, c->stream);
     }
-    if (e == hipSuccess) {
-      launch_ghost<T>(L, S);
-      vm_wall_mask<T>(V, W);
-    }
-    for (int v = 0; v < 8 && e == hipSuccess; ++v)
-      e = hipMemcpyAsync(base + (long long)v * n, S.p[v], bytes, hipMemcpyDeviceToDevice, c->stream);
+    if (e != hipSuccess) return fail(c, MHD_EHIP, hipGetErrorString(e));
+    launch_ghost<T>(L, S);
+    vjp_axpby8<T>(V, Wb, cp8<T>(p8<T>(wbar)), 0.0, 1.0, true);
   }
-  if (e == hipSuccess) vm_forward<T>(V, P, c->d_fused, base, n);
-  for (int v = 0; v < 8 && e == hipSuccess; ++v)
-    e = hipMemcpyAsync(cbase + (long long)P.cout[v] * n, walls ? W.p[v] : wbar[v], bytes,
-                       hipMemcpyDeviceToDevice, c->stream);
-  if (e == hipSuccess) vm_backward<T>(V, P, c->d_bsteps, base, cbase, n);
-  for (int v = 0; v < 8 && e == hipSuccess; ++v)
-    e = P.cin[v] >= 0 ? hipMemcpyAsync(fbar[v], cbase + (long long)P.cin[v] * n, bytes,
-                                       hipMemcpyDeviceToDevice, c->stream)
-                      : hipMemsetAsync(fbar[v], 0, bytes, c->stream);
-  if (walls && e == hipSuccess) vm_fill_vjp<T>(V, cp8<T>(S), p8<T>(fbar), base, n);
+  rhs_transpose<T>(c, walls, cp8<T>(S), cp8<T>(Wb), G, false, base, 0.0);
+  if (walls) vjp_fill<T>(V, cp8<T>(S), G, base, n);
   L.at(PASS_END);
-  if (e != hipSuccess) return fail(c, MHD_EHIP, hipGetErrorString(e));
   return check_launch(c, "mhd_rhs_adjoint launch");
 }
 

@@ -55,6 +55,7 @@ struct BoxDev {
   // array, for every box; stretched: a stretched z axis
   long long joff;
   int stretched;
+  double hinv[3];            // 1 / dx, 1 / dy, 1 / dz
 };
 
 // Per-plane z quantities (Section 4.2: derivatives in index space times the
