@@ -66,6 +66,8 @@ struct mhd_ctx {
   // (empty for a uniform box)
   std::vector<std::vector<double>> dzc, dzf;
   int stretched = 0;
+  int cells = 0;                   // the stage runs one thread per cell (mhd_zcell.hip)
+  bool cells_ok = false;           // ... can (workspace and terms)
   // timing of kernel passes (mhd_profile)
   bool prof = false;
   std::vector<std::pair<int, hipEvent_t>> marks;
@@ -165,7 +167,8 @@ static double divb_limit(double dx, double dy, double dz) {
 }
 // Stage workspace arrays: 34, 6 more for the quenched stress, and 2 more
 // for the second-order switch.
-static int work_arrays(const mhd_params& p) {
+static int work_arrays(const mhd_params& p, bool cells = false) {
+  if (cells) return WC_COUNT;
   if (p.terms & MHD_T_ORDER2) return WS_COUNT_ALL;
   return (p.terms & MHD_T_QUENCH) ? WS_COUNT_QUENCH : WS_COUNT;
 }
@@ -279,10 +282,11 @@ struct Scratch {
   void* lnpav;
   double* lnpart;
   int* queue;
+  int cells;       // the cell-parallel stage, whose arrays are in work too
 };
 
 static Scratch own_scratch(const mhd_ctx* c) {
-  return Scratch{c->work, c->d_lnavg, c->d_lnpav, c->d_lnpart, c->d_queue};
+  return Scratch{c->work, c->d_lnavg, c->d_lnpav, c->d_lnpart, c->d_queue, c->cells};
 }
 
 template <class T> static ZWork<T> make_zwork(const mhd_ctx* c, const Scratch& s) {
@@ -293,6 +297,12 @@ template <class T> static ZWork<T> make_zwork(const mhd_ctx* c, const Scratch& s
   return w;
 }
 template <class T> static ZWork<T> make_zwork(const mhd_ctx* c) { return make_zwork<T>(c, own_scratch(c)); }
+
+static bool any_wall(const mhd_ctx* c) {
+  for (const auto& b : c->boxes)
+    if (b.bc_z == MHD_BC_WALL) return true;
+  return false;
+}
 
 static ZLaunch make_zlaunch(const mhd_ctx* c, const Scratch& s) {
   ZLaunch L;
@@ -309,6 +319,10 @@ static ZLaunch make_zlaunch(const mhd_ctx* c, const Scratch& s) {
   L.nbox = (int)c->h_boxes.size();
   L.nplanes = c->nplanes;
   L.stretched = c->stretched;
+  L.wall = any_wall(c) ? 1 : 0;
+  L.tab = c->d_tab;
+  L.nblk = c->nblk;
+  L.cells = s.cells;
   L.stream = c->stream;
   L.mark = c->prof ? prof_mark : nullptr;
   L.mark_ctx = const_cast<mhd_ctx*>(c);
@@ -405,7 +419,8 @@ static int upload_items(mhd_ctx* c, int tile, int c0, int c1) {
     build_items(c, tile, q, items);
     n[q] = (int)items.size();
     e = hipMalloc(&di[q], sizeof(ZItem) * items.size());
-    if (e == hipSuccess && q == ZC_A) e = hipMalloc(&dp, sizeof(CPart) * items.size());
+    // (the cell-parallel stage has one partial per block of cells)
+    if (e == hipSuccess && q == ZC_A) e = hipMalloc(&dp, sizeof(CPart) * std::max(items.size(), (size_t)c->nblk));
     if (e == hipSuccess && q == ZC_A) e = hipMalloc(&dr, sizeof(RedItem) * items.size());
     if (e == hipSuccess)
       e = hipMemcpy(di[q], items.data(), sizeof(ZItem) * items.size(), hipMemcpyHostToDevice);
@@ -444,6 +459,16 @@ static int set_tile(mhd_ctx* c, int tile) {
   const int rc = upload_items(c, tile, 0, ZC_COUNT);
   if (rc == MHD_OK) c->tile = c->ftile = tile;
   return rc;
+}
+
+// Whether a context runs its stages one thread per cell: the terms that
+// path has, and few enough cells.  us per RK stage, one thread per cell
+// against the march: float32 32^3 33.5 / 89, 64^3 74 / 133, 96^3 202 / 220,
+// 112^3 344 / 315, 128^3 518 / 380; with walls 64^3 121 / 179.  float64 24^3
+// 40.5 / 94, 48^3 72.5 / 131, 64^3 128 / 170, 80^3 237 / 222; with walls
+// 64^3 189 / 210.
+static bool cells_fit(const mhd_ctx* c) {
+  return c->nelem <= (c->esize == 4 ? 1000000 : 400000) && (c->p.terms & ~kCellTerms) == 0;
 }
 
 // The tiles a context starts with, from the columns they pad and the size.
@@ -746,6 +771,8 @@ int mhd_init(const mhd_params* p, void* hip_stream, mhd_ctx** out) {
       for (int q = 0; q < ZJ_COUNT; ++q) ztab.push_back(e[q]);
     }
   }
+  c->cells_ok = cells_fit(c);
+  c->cells = c->cells_ok ? 1 : 0;
   std::vector<Blk> tab, gtab;
   build_tables(c, tab, gtab);
   c->nblk = (int)tab.size();
@@ -755,7 +782,7 @@ int mhd_init(const mhd_params* p, void* hip_stream, mhd_ctx** out) {
       (e = hipMalloc(&c->d_tab, sizeof(Blk) * tab.size())) != hipSuccess ||
       (c->ngblk && (e = hipMalloc(&c->d_gtab, sizeof(Blk) * gtab.size())) != hipSuccess) ||
       (e = hipMalloc(&c->d_tot, sizeof(RedTotal))) != hipSuccess ||
-      (e = hipMalloc(&c->work, (size_t)work_arrays(c->p) * c->nelem * c->esize)) != hipSuccess) {
+      (e = hipMalloc(&c->work, (size_t)work_arrays(c->p, c->cells_ok) * c->nelem * c->esize)) != hipSuccess) {
     g_init_err = std::string("device allocation failed: ") + hipGetErrorString(e);
     mhd_destroy(c);
     return MHD_ENOMEM;
@@ -925,11 +952,6 @@ static void rhs_transpose(mhd_ctx* c, bool walls, CP8<T> s, CP8<T> w, P8<T> g, b
              dt);
 }
 
-static bool any_wall(const mhd_ctx* c) {
-  for (const auto& b : c->boxes)
-    if (b.bc_z == MHD_BC_WALL) return true;
-  return false;
-}
 
 // The adjoint workspace: the transpose's arrays, then the stage states and
 // dU (24 arrays; 16 more with walls: the filled input and the step's end
@@ -1134,17 +1156,19 @@ int mhd_rhs(mhd_ctx* c, void* const f[8], void* const dfdt[8]) {
 }
 
 // Layout of a context's per-call scratch inside the static array: returns
-// the bytes it needs, and fills *s only when they fit.
-static size_t static_layout(const mhd_ctx* c, Scratch* s) {
+// the bytes it needs, and fills *s only when they fit.  The march takes
+// over where the cell-parallel stage's own arrays would not fit.
+static size_t static_layout(const mhd_ctx* c, Scratch* s, bool cells) {
   auto a256 = [](size_t n) { return (n + 255) & ~size_t(255); };
-  const size_t work = a256((size_t)work_arrays(c->p) * c->nelem * c->esize);
+  const size_t work = a256((size_t)work_arrays(c->p, cells) * c->nelem * c->esize);
   const size_t tab = a256(c->esize * (size_t)c->nplanes);
   const size_t part = a256(sizeof(double) * kPlaneSlices * (size_t)c->nplanes);
   const size_t need = work + 2 * tab + part + a256(sizeof(int) * kQueueInts);
+  if (cells && need > kScratchBytes) return static_layout(c, s, false);
   if (s && c->scratch && need <= kScratchBytes) {
     char* b = static_cast<char*>(c->scratch);
     *s = Scratch{b, b + work, b + work + tab, reinterpret_cast<double*>(b + work + 2 * tab),
-                 reinterpret_cast<int*>(b + work + 2 * tab + part)};
+                 reinterpret_cast<int*>(b + work + 2 * tab + part), cells ? 1 : 0};
   }
   return need;
 }
@@ -1158,7 +1182,7 @@ int mhd_rhs_noalloc(mhd_ctx* c, void* const f[8], void* const dfdt[8]) {
       if (f[a] == dfdt[b]) return fail(c, MHD_EINVAL, "f and dfdt overlap");
   if (!c->scratch) return fail(c, MHD_EHIP, "mhd_rhs_noalloc: the static scratch is not available on this device");
   Scratch s;
-  const size_t need = static_layout(c, &s);
+  const size_t need = static_layout(c, &s, c->cells != 0);
   if (need > kScratchBytes)
     return fail(c, MHD_EINVAL, "mhd_rhs_noalloc: these boxes need " + std::to_string(need) +
                                    " bytes of scratch, above the static limit of " +
@@ -1273,7 +1297,9 @@ int mhd_set_tile(mhd_ctx* c, int32_t tile) {
   if (!c) return fail(nullptr, MHD_EINVAL, "ctx is NULL");
   if (tile < 0 || tile >= ZTILE_COUNT) return fail(c, MHD_EINVAL, "unknown tile shape");
   if (!ztile_ok(tile, c->esize)) return fail(c, MHD_EUNSUPPORTED, "tile shape not built for this dtype");
-  return set_tile(c, tile);
+  const int rc = set_tile(c, tile);
+  if (rc == MHD_OK) c->cells = 0;
+  return rc;
 }
 
 int mhd_set_launch(mhd_ctx* c, int32_t tile, int32_t persistent) {
@@ -1282,7 +1308,10 @@ int mhd_set_launch(mhd_ctx* c, int32_t tile, int32_t persistent) {
   if (persistent != 0 && persistent != 1) return fail(c, MHD_EINVAL, "persistent must be 0 or 1");
   if (!ztile_ok(tile, c->esize)) return fail(c, MHD_EUNSUPPORTED, "tile shape not built for this dtype");
   int rc = set_tile(c, tile);
-  if (rc == MHD_OK) c->persistent = persistent;
+  if (rc == MHD_OK) {
+    c->persistent = persistent;
+    c->cells = 0;
+  }
   return rc;
 }
 
@@ -1297,7 +1326,9 @@ int mhd_set_final_tile(mhd_ctx* c, int32_t tile) {
   if (!c) return fail(nullptr, MHD_EINVAL, "ctx is NULL");
   if (tile < 0 || tile >= ZTILE_COUNT) return fail(c, MHD_EINVAL, "unknown tile shape");
   if (!ztile_ok(tile, c->esize)) return fail(c, MHD_EUNSUPPORTED, "tile shape not built for this dtype");
-  return set_ftile(c, tile);
+  const int rc = set_ftile(c, tile);
+  if (rc == MHD_OK) c->cells = 0;
+  return rc;
 }
 
 int mhd_get_final_tile(const mhd_ctx* c, int32_t* tile) {
@@ -1402,12 +1433,27 @@ int mhd_autotune(mhd_ctx* c, void* const f[8], void* const dfdt[8], int32_t reps
         }
     rc = mhd_set_launch(c, bt, bm);
   }
+  // and the cell-parallel stage against the best of them
+  bool cells = false;
+  if (rc == MHD_OK && c->cells_ok) {
+    double tc = -1.0;
+    c->cells = 1;
+    for (int round = 0; round < kRounds && rc == MHD_OK; ++round) {
+      double per = 0.0;
+      rc = timed(per);
+      if (rc == MHD_OK && (tc < 0.0 || per < tc)) tc = per;
+    }
+    cells = rc == MHD_OK && tc < std::min(best, tf[bm][bf]);
+    c->cells = 0;
+  }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   (void)hipFree(next);
   c->prof = prof;
   if (rc != MHD_OK) return rc;
-  return set_ftile(c, bf);
+  if ((rc = set_ftile(c, bf)) != MHD_OK) return rc;
+  c->cells = cells ? 1 : 0;
+  return MHD_OK;
 }
 
 }  // extern "C"

@@ -133,7 +133,7 @@ template <class T> struct Geo {
       : nx(b.nx), ny(b.ny), nzt(b.nzt), wall(b.wall), g0(b.g0), g1(b.g1),
         off(b.off), sxy((long long)b.nx * b.ny),
         dx(T(b.dx)), dy(T(b.dy)), dz(T(b.dz)), h(T(b.hmin)), hmax(T(b.hmax)),
-        hxi(T(1.0 / b.dx)), hyi(T(1.0 / b.dy)), hzi(T(1.0 / b.dz)),
+        hxi(T(b.hinv[0])), hyi(T(b.hinv[1])), hzi(T(b.hinv[2])),
         lx(T(b.lv[0])), ly(T(b.lv[1])), lz(T(b.lv[2])),
         lxy(T(b.le[0])), lxz(T(b.le[1])), lyz(T(b.le[2])) {}
   __device__ long long at(int i, int j, int k) const {

@@ -1248,8 +1248,9 @@ __global__ __launch_bounds__(256) void k_plane_lnmean(const BoxDev* __restrict__
 
 // Courant time step of the current state from the per-item maxima of A1 / A2
 // (eq. courantcond, wave and diffusion limits), into dt_dev[0].
+template <class I>   // ZItem or Blk
 __global__ __launch_bounds__(256) void k_dt(const BoxDev* __restrict__ boxes,
-                                            const ZItem* __restrict__ items, int nitems,
+                                            const I* __restrict__ items, int nitems,
                                             const CPart* __restrict__ cpart, double Cdt,
                                             double Cdtd, double nuB, double eta_const,
                                             double* __restrict__ dt_dev) {
@@ -1428,6 +1429,35 @@ __global__ __launch_bounds__(128) void k_qreset(int* q) {
   if ((int)threadIdx.x < kQueueInts) q[threadIdx.x] = 0;
 }
 
+template <class T> void launch_courant(const ZLaunch& L, const ZStageArgs<T>& a) {
+  if (L.cells)
+    hipLaunchKernelGGL(k_dt<Blk>, dim3(1), dim3(256), 0, L.stream, L.boxes, L.tab, L.nblk, a.cpart, a.Cdt, a.Cdtd,
+                       a.nuB, a.eta_const, a.dt_dev);
+  else
+    hipLaunchKernelGGL(k_dt<ZItem>, dim3(1), dim3(256), 0, L.stream, L.boxes, L.items[ZC_A], L.nitems[ZC_A], a.cpart,
+                       a.Cdt, a.Cdtd, a.nuB, a.eta_const, a.dt_dev);
+}
+template void launch_courant<float>(const ZLaunch&, const ZStageArgs<float>&);
+template void launch_courant<double>(const ZLaunch&, const ZStageArgs<double>&);
+
+template <class T> void launch_plane_means(const ZLaunch& L, const ZStageArgs<T>& a) {
+  if ((a.ph.terms & T_EDIFF) && (a.ph.terms & T_EDIFFAV)) {
+    hipLaunchKernelGGL(k_plane_sum<T>, dim3(L.nplanes * kPlaneSlices), dim3(256), 0, L.stream, L.boxes, L.nbox,
+                       a.f.p[0], a.f.p[4], a.lnpart);
+    hipLaunchKernelGGL(k_plane_lnmean<T>, dim3((L.nplanes + 255) / 256), dim3(256), 0, L.stream, L.boxes,
+                       L.nbox, L.nplanes, a.lnpart, 1.0, a.lnavg);
+  }
+  const bool lnp = (a.ph.terms & T_PRES) && (a.ph.terms & T_LNP);
+  if (lnp) {   // ln P_aver, P = (gamma - 1) e
+    hipLaunchKernelGGL(k_plane_sum<T>, dim3(L.nplanes * kPlaneSlices), dim3(256), 0, L.stream, L.boxes, L.nbox,
+                       (const T*)nullptr, a.f.p[4], a.lnpart);
+    hipLaunchKernelGGL(k_plane_lnmean<T>, dim3((L.nplanes + 255) / 256), dim3(256), 0, L.stream, L.boxes,
+                       L.nbox, L.nplanes, a.lnpart, (double)a.ph.gamma1, a.w.lnpav);
+  }
+}
+template void launch_plane_means<float>(const ZLaunch&, const ZStageArgs<float>&);
+template void launch_plane_means<double>(const ZLaunch&, const ZStageArgs<double>&);
+
 template <class T, int TX, int TY, bool PERS>
 static void launch_zstage_m(const ZLaunch& L, const ZStageArgs<T>& a) {
   const int na = L.nitems[ZC_A], nq = L.nitems[ZC_Q], np = L.nitems[ZC_P];
@@ -1459,23 +1489,11 @@ static void launch_zstage_m(const ZLaunch& L, const ZStageArgs<T>& a) {
                        L.boxes, ia, na, a.ztab, q ? q + 8 : q, a.w, a.cpart);
   if (a.cpart) {
     L.at(PASS_REDUCE);
-    hipLaunchKernelGGL(k_dt, dim3(1), dim3(256), 0, L.stream, L.boxes, ia, na, a.cpart, a.Cdt,
-                       a.Cdtd, a.nuB, a.eta_const, a.dt_dev);
+    launch_courant(L, a);
     L.at(PASS_MEAN3);   // the plane means below are booked with A2 in every stage
   }
-  if ((a.ph.terms & T_EDIFF) && (a.ph.terms & T_EDIFFAV)) {
-    hipLaunchKernelGGL(k_plane_sum<T>, dim3(L.nplanes * kPlaneSlices), dim3(256), 0, L.stream, L.boxes, L.nbox,
-                       a.f.p[0], a.f.p[4], a.lnpart);
-    hipLaunchKernelGGL(k_plane_lnmean<T>, dim3((L.nplanes + 255) / 256), dim3(256), 0, L.stream, L.boxes,
-                       L.nbox, L.nplanes, a.lnpart, 1.0, a.lnavg);
-  }
+  launch_plane_means<T>(L, a);
   const bool lnp = (a.ph.terms & T_PRES) && (a.ph.terms & T_LNP);
-  if (lnp) {   // ln P_aver, P = (gamma - 1) e
-    hipLaunchKernelGGL(k_plane_sum<T>, dim3(L.nplanes * kPlaneSlices), dim3(256), 0, L.stream, L.boxes, L.nbox,
-                       (const T*)nullptr, a.f.p[4], a.lnpart);
-    hipLaunchKernelGGL(k_plane_lnmean<T>, dim3((L.nplanes + 255) / 256), dim3(256), 0, L.stream, L.boxes,
-                       L.nbox, L.nplanes, a.lnpart, (double)a.ph.gamma1, a.w.lnpav);
-  }
   L.at(PASS_EDGES);
   // the optional passes run in grid mode (their own launches, no queue)
   const dim3 gq(8 * ((nq + 7) / 8)), gp(8 * ((np + 7) / 8));
@@ -1535,6 +1553,10 @@ static void launch_zstage_t(const ZLaunch& L, const ZStageArgs<T>& a) {
 
 template <class T>
 void launch_zstage(const ZLaunch& L, const ZStageArgs<T>& a) {
+  if (L.cells) {
+    launch_cellstage<T>(L, a);
+    return;
+  }
   switch (L.tile) {
     case ZTILE_32x8: launch_zstage_t<T, 32, 8>(L, a); break;
     case ZTILE_16x16: launch_zstage_t<T, 16, 16>(L, a); break;

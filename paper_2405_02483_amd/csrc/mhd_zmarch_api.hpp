@@ -46,7 +46,11 @@ inline int ztile_y(int t) { return t == ZTILE_64x4 ? 4 : ((t == ZTILE_16x16 || t
 enum WsArr : int { WS_NUS = 0, WS_D, WS_UZ, WS_LNT, WS_Q0, WS_P0 = WS_Q0 + QOUT_COUNT,
                    WS_DIVB = WS_P0 + POUT_COUNT, WS_COUNT, WS_TQ0 = WS_COUNT,
                    WS_COUNT_QUENCH = WS_TQ0 + 6, WS_RGH = WS_COUNT_QUENCH, WS_D2,
-                   WS_COUNT_ALL };
+                   WS_COUNT_ALL,
+                   // the cell-parallel stage's own (it runs without the quench and
+                   // second-order passes): face velocities and densities, e_m and its
+                   // log, <nu>, the maximum, x and y interpolations of ln <nu>
+                   WC_UX = WS_COUNT, WC_UY, WC_RX, WC_RY, WC_EM, WC_LEM, WC_NU, WC_M, WC_XL, WC_YL, WC_COUNT };
 
 // Viscous stress components (eq. itv) and where they live: tau_xz on the
 // y-edge, tau_yz on the x-edge, tau_zz, tau_xx, tau_yy at the centre, tau_xy
@@ -100,6 +104,10 @@ struct ZLaunch {
   int ncu;                // compute units of the device
   int nbox, nplanes;      // boxes; z planes of all boxes
   int stretched;          // some box has a stretched z axis (pass F's STR instantiation)
+  int wall;               // some box has closed walls
+  const Blk* tab;         // device: blocks over every cell (the cell-parallel stage)
+  int nblk;
+  int cells;              // the cell-parallel stage instead of the march
   hipStream_t stream;
   void (*mark)(void*, int);
   void* mark_ctx;
@@ -126,7 +134,15 @@ template <class T> struct ZStageArgs {
   double Cdt, Cdtd, nuB, eta_const;
 };
 
+// One RK stage: the z-march, or with L.cells one thread per cell
+// (mhd_zcell.hip; the terms must be among kCellTerms).
 template <class T> void launch_zstage(const ZLaunch& L, const ZStageArgs<T>& a);
+template <class T> void launch_cellstage(const ZLaunch& L, const ZStageArgs<T>& a);
+constexpr unsigned kCellTerms = ~(T_SMAG | T_QUENCH | T_ORDER2);
+// The Courant dt from the per-item (per-block) maxima of a.cpart, and the
+// plane means' logs of the optional terms that take them.
+template <class T> void launch_courant(const ZLaunch& L, const ZStageArgs<T>& a);
+template <class T> void launch_plane_means(const ZLaunch& L, const ZStageArgs<T>& a);
 
 // Pass F (mhd_zfinal.hip) in its tile shape L.ftile.
 template <class T, bool PERS> void launch_final(const ZLaunch& L, const ZStageArgs<T>& a, int* q);
