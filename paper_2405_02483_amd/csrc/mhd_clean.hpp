@@ -11,8 +11,8 @@
 
 namespace smhd {
 
-// rocFFT plans per box shape and the scratch of the transforms; made on the
-// first call (for the context's boxes and precision) and kept.
+// Transforms per box shape (their passes, or rocFFT plans) and the scratch;
+// made on the first call (for the context's boxes and precision) and kept.
 struct CleanState;
 void clean_free(CleanState* s);
 
