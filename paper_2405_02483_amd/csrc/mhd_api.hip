@@ -68,6 +68,7 @@ struct mhd_ctx {
   int stretched = 0;
   int cells = 0;                   // the stage runs one thread per cell (mhd_zcell.hip)
   bool cells_ok = false;           // ... can (workspace and terms)
+  int stream_f = 0;                // pass F streams
   // timing of kernel passes (mhd_profile)
   bool prof = false;
   std::vector<std::pair<int, hipEvent_t>> marks;
@@ -323,6 +324,7 @@ static ZLaunch make_zlaunch(const mhd_ctx* c, const Scratch& s) {
   L.tab = c->d_tab;
   L.nblk = c->nblk;
   L.cells = s.cells;
+  L.fstream = c->stream_f;
   L.stream = c->stream;
   L.mark = c->prof ? prof_mark : nullptr;
   L.mark_ctx = const_cast<mhd_ctx*>(c);
@@ -469,6 +471,20 @@ static int set_tile(mhd_ctx* c, int tile) {
 // 64^3 189 / 210.
 static bool cells_fit(const mhd_ctx* c) {
   return c->nelem <= (c->esize == 4 ? 1000000 : 400000) && (c->p.terms & ~kCellTerms) == 0;
+}
+
+// Whether pass F streams the data it reads or writes once, so that the
+// tiles' shared halo lines stay in the caches instead: where every row starts
+// on a cache line (elsewhere a wave's 256 bytes are partial lines, which
+// streaming writes out one by one) and the arrays do not stay in the caches
+// from pass to pass.  Pass F, us per stage without and with: float32 128^3
+// 153 / 149, 256^3 1016 / 922, 512^3 7480 / 7386; float64 128^3 255 / 241,
+// 256^3 1879 / 1788; but float32 96^3 72 / 78, 150x132x150 233 / 263, float64
+// 200x180x225 1007 / 1032.
+static bool streams(const mhd_ctx* c) {
+  for (const BoxDev& d : c->h_boxes)
+    if ((size_t)d.nx * c->esize % 128 != 0) return false;
+  return (size_t)c->nelem * c->esize >= 6000000;
 }
 
 // The tiles a context starts with, from the columns they pad and the size.
@@ -771,6 +787,7 @@ int mhd_init(const mhd_params* p, void* hip_stream, mhd_ctx** out) {
       for (int q = 0; q < ZJ_COUNT; ++q) ztab.push_back(e[q]);
     }
   }
+  c->stream_f = streams(c) ? 1 : 0;
   c->cells_ok = cells_fit(c);
   c->cells = c->cells_ok ? 1 : 0;
   std::vector<Blk> tab, gtab;

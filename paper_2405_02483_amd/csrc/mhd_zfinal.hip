@@ -32,6 +32,16 @@ __host__ __device__ constexpr int strip_slot(const int (&own)[9], int q) {
 }
 __host__ __device__ constexpr int at_least1(int n) { return n > 0 ? n : 1; }
 
+// Accesses to data that is read or written once in a stage.
+template <bool NT, class T> __device__ __forceinline__ void put(T* p, T v) {
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+template <bool NT, class T> __device__ __forceinline__ T get(const T* p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+
 template <class T, int TX, int TY, bool PERS, unsigned FM>
 __global__ __launch_bounds__(TX * TY) void zF(const BoxDev* __restrict__ boxes,
                                               const ZItem* __restrict__ items, int nitems,
@@ -54,6 +64,9 @@ __global__ __launch_bounds__(TX * TY) void zF(const BoxDev* __restrict__ boxes,
   // a stretched z axis (bit 9): z derivatives scattered with each output
   // plane's Jacobian
   constexpr bool kStr = hasf<FM>(9);
+  // streaming (bit 10): what is read and written once bypasses the caches'
+  // retention
+  constexpr bool kNT = hasf<FM>(10);
   // only the strips of this launch's fields occupy LDS
   __shared__ T sx[at_least1(strip_slot<FM>(kXOwn, 9)) * PXs::NP];
   __shared__ T sy[at_least1(strip_slot<FM>(kYOwn, 9)) * PYs::NP];
@@ -104,8 +117,8 @@ __global__ __launch_bounds__(TX * TY) void zF(const BoxDev* __restrict__ boxes,
   // RK stage update of one field at plane k, given its dU and f there
   auto update = [&](int v, long long o, T Fv, T uin, T fin) {
     const T U = (du_mode & DU_READ) ? alpha * uin + Fv : Fv;
-    if (du_mode & DU_WRITE) du.p[v][o] = U;
-    f_out.p[v][o] = fin + bdt * U;
+    if (du_mode & DU_WRITE) put<kNT>(du.p[v] + o, U);
+    put<kNT>(f_out.p[v] + o, T(fin + bdt * U));
   };
   // the seven z-accumulated fields at plane k: every load first, so they
   // share one round trip to memory
@@ -126,7 +139,7 @@ __global__ __launch_bounds__(TX * TY) void zF(const BoxDev* __restrict__ boxes,
       uin[a] = T(0);
       fin[a] = T(0);
       if (hasf<FM>(a)) {
-        uin[a] = (du_mode & DU_READ) ? du.p[a][o] : T(0);
+        uin[a] = (du_mode & DU_READ) ? get<kNT>(du.p[a] + o) : T(0);
         fin[a] = f.p[a][o];
       }
     }
@@ -181,18 +194,18 @@ __global__ __launch_bounds__(TX * TY) void zF(const BoxDev* __restrict__ boxes,
       const T* cols[7] = {f.p[3], ws.q(QOUT_GXZ), ws.q(QOUT_GYZ), ws.q(QOUT_GZZ), ws.q(QOUT_HZ),
                           ws.q(QOUT_EY), ws.q(QOUT_EX)};
 #pragma unroll
-      for (int a = 0; a < 7; ++a) cur[a] = hasf<FM>(a) ? cols[a][o] : T(0);
-      const T lxy = hasf<FM>(1) ? ws.q(QOUT_LXY)[o] : T(0);
-      const T lyx = hasf<FM>(2) ? ws.q(QOUT_LYX)[o] : T(0);
+      for (int a = 0; a < 7; ++a) cur[a] = hasf<FM>(a) ? (a > 0 && a < 5 ? get<kNT>(cols[a] + o) : cols[a][o]) : T(0);
+      const T lxy = hasf<FM>(1) ? get<kNT>(ws.q(QOUT_LXY) + o) : T(0);
+      const T lyx = hasf<FM>(2) ? get<kNT>(ws.q(QOUT_LYX) + o) : T(0);
       const T rho_o = (hasf<FM>(3) && grav) ? f.p[0][o] : T(0);
       // own-cell terms of the own planes
       T dpx = T(0), dpy = T(0), qc = T(0), dpz = T(0), czz_ = T(0);
       if (inch) {
-        if (hasf<FM>(3)) dpz = ws.q(QOUT_DPZ)[o];
-        if (hasf<FM>(4)) czz_ = ws.q(QOUT_CZZ)[o];
-        if (hasf<FM>(1)) dpx = ws.pq(POUT_DPX)[o];
-        if (hasf<FM>(2)) dpy = ws.pq(POUT_DPY)[o];
-        if (hasf<FM>(4)) qc = ws.pq(POUT_QC)[o];
+        if (hasf<FM>(3)) dpz = get<kNT>(ws.q(QOUT_DPZ) + o);
+        if (hasf<FM>(4)) czz_ = get<kNT>(ws.q(QOUT_CZZ) + o);
+        if (hasf<FM>(1)) dpx = get<kNT>(ws.pq(POUT_DPX) + o);
+        if (hasf<FM>(2)) dpy = get<kNT>(ws.pq(POUT_DPY) + o);
+        if (hasf<FM>(4)) qc = get<kNT>(ws.pq(POUT_QC) + o);
       }
       // Bz's dU and f at this plane, fetched with the planes
       T bz_u = T(0), bz_f = T(0);
@@ -374,6 +387,13 @@ static void zF_launch(const G& grid, dim3 block, const ZLaunch& L, const ZStageA
         (zF_one<T, TX, TY, false, kFMasks[I] | 0x200u>(grid, block, L, a, nullptr), ...);
       return;
     }
+  }
+  if (L.fstream) {
+    if (a.ph.terms & T_CORI)
+      (zF_one<T, TX, TY, PERS, with_cori<kFMasks[I]>() | 0x400u>(grid, block, L, a, q ? q + 32 + 8 * int(I) : q), ...);
+    else
+      (zF_one<T, TX, TY, PERS, kFMasks[I] | 0x400u>(grid, block, L, a, q ? q + 32 + 8 * int(I) : q), ...);
+    return;
   }
   if (a.ph.terms & T_CORI)
     (zF_one<T, TX, TY, PERS, with_cori<kFMasks[I]>()>(grid, block, L, a, q ? q + 32 + 8 * int(I) : q), ...);

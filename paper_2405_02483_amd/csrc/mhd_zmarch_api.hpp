@@ -108,6 +108,7 @@ struct ZLaunch {
   const Blk* tab;         // device: blocks over every cell (the cell-parallel stage)
   int nblk;
   int cells;              // the cell-parallel stage instead of the march
+  int fstream;            // pass F streams what it reads and writes once (its bit 10)
   hipStream_t stream;
   void (*mark)(void*, int);
   void* mark_ctx;
