@@ -22,9 +22,9 @@
 // terms, some 190 reads and writes per cell and stage, against 1700 of an
 // operation-by-operation program, which this replaced (each operation a
 // pass over 2 to 5 arrays, 160 launches a stage).  One step's adjoint:
-// 128^3 float32 23.06 -> 3.33 ms, 64^3 float32 with walls and every
+// 128^3 float32 23.06 -> 3.14 ms, 64^3 float32 with walls and every
 // optional term 14.37 -> 2.35 ms; a 6-step float64 rollout of 48^3 with its
-// gradient 63.2 -> 9.54 ms.
+// gradient 63.2 -> 6.5 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -107,6 +107,18 @@ template <class T> struct VK {
   (void)A; (void)S; (void)Wt; (void)tm;
 
 #define VJP_KERNEL template <class T, bool W> __global__ __launch_bounds__(kBlock) void
+
+// The same with at least `f32` waves a SIMD in float32.  The kernels that
+// gather most wait for the caches; left alone the compiler hoists loads until
+// 98 to 113 registers hold them and 4 waves fit.  128^3 float32: edges and
+// faces 266 us at 4 waves, 254 at 5, 270 at 6 (spilling); vectors 217 at 4,
+// 192 at 5, 176 at 6, 185 at 8; centre 74 at 4, 70 at 5, 84 at 6.  In float64
+// every such bound spills (edges and faces 25 -> 41 us at 48^3), so there the
+// compiler's choice stands.
+#define VJP_KERNEL_WAVES(f32)                                    \
+  template <class T, bool W>                                     \
+  __global__ __launch_bounds__(kBlock)                           \
+      __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? f32 : 1))) void
 
 template <class T> __device__ __forceinline__ T vnorm3(T x, T y, T z) {
   const T s = x * x + y * y + z * z;
@@ -608,7 +620,7 @@ __device__ __forceinline__ void face_back(const Cell<T, W>& c, const VK<T>& K, c
 }
 
 // Edges (blockIdx.y 0..2, the direction) and faces (3..5, the normal).
-VJP_KERNEL k_edge_face(VK<T> K) {
+VJP_KERNEL_WAVES(5) k_edge_face(VK<T> K) {
   VJP_CELL
   switch (blockIdx.y) {
     case 0: edge_back<X>(c, K, A, Wt, S); break;
@@ -679,7 +691,7 @@ VJP_KERNEL k_mean_back(VK<T> K) {
 
 // Centre: the stress, the diagonal momentum fluxes, -P div u and the
 // speed-like viscosity (mb: the cotangent of its first maximum), backwards.
-VJP_KERNEL k_centre_back(VK<T> K, int mb) {
+VJP_KERNEL_WAVES(5) k_centre_back(VK<T> K, int mb) {
   VJP_CELL
   const Phys<T>& ph = K.ph;
   const Centre<T, W, decltype(A)> E(c, K, A);
@@ -834,7 +846,7 @@ __device__ __forceinline__ void field_back(const Cell<T, W>& c, const VK<T>& K, 
   add_to(c, K, 5 + AX, v);
 }
 // blockIdx.y 0..2 the velocities, 3..5 the magnetic field.
-VJP_KERNEL k_vector_back(VK<T> K) {
+VJP_KERNEL_WAVES(6) k_vector_back(VK<T> K) {
   VJP_CELL
   switch (blockIdx.y) {
     case 0: vel_back<X>(c, K, A, Wt); break;
