@@ -31,6 +31,14 @@ namespace smhd {
 // in short per-thread queues; u_z (plane r-2) and the z stencils (plane r-5)
 // come from register windows.
 //
+// The five planes before and after the item's own feed only the z windows of
+// rho, u_z and B_z, so there the loop reads the own column (prefetched one
+// plane ahead) and skips the planes.  4 waves a SIMD in float32 (3 persistent), 2 in
+// float64: without the bound 32x8 tiles take 129 registers and 3 waves.
+// Against planes loaded throughout, per stage: 128^3 66 -> 49 us, 24 boxes of
+// 48^3 to 96^3 806 -> 764, 150x132x140 79 -> 64, 256^3 295 -> 290, 512^3 2036 ->
+// 2058; float64 128^3 94 -> 80, 200x180x215 300 -> 293, 256^3 536 -> 543.
+//
 // RED (the reduction instantiation of mhd_reductions): also accumulates, in
 // float64 over the item's interior cells, the totals of the state, div B and
 // the maxima, the wave speed c_s + c_A + |u_perp| and the rate
@@ -40,12 +48,13 @@ namespace smhd {
 // viscosity into the workspace of pass Q (free until then): the centred
 // velocities aup(u_a) and the diagonal strain ddaup(u_a).
 template <class T, int TX, int TY, bool PERS, bool RED = false, bool SMAG = false>
-__global__ __launch_bounds__(TX * TY) void zA1(const BoxDev* __restrict__ boxes,
-                                               const ZItem* __restrict__ items, int nitems, const T* __restrict__ ztab,
-                                               int* __restrict__ queue,
-                                               CP8<T> f, Phys<T> ph, ZWork<T> ws,
-                                               CPart* __restrict__ cpart,
-                                               CP8<T> dfdt = CP8<T>{}, RedItem* __restrict__ red = nullptr) {
+__global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(RED ? 1 : sizeof(T) == 8 ? 2 : PERS ? 3 : 4)))
+void zA1(const BoxDev* __restrict__ boxes,
+         const ZItem* __restrict__ items, int nitems, const T* __restrict__ ztab,
+         int* __restrict__ queue,
+         CP8<T> f, Phys<T> ph, ZWork<T> ws,
+         CPart* __restrict__ cpart,
+         CP8<T> dfdt = CP8<T>{}, RedItem* __restrict__ red = nullptr) {
   T* __restrict__ nus_out = ws.arr(WS_NUS);
   T* __restrict__ D_out = ws.arr(WS_D);
   T* __restrict__ divb_out = ws.arr(WS_DIVB);
@@ -75,23 +84,37 @@ __global__ __launch_bounds__(TX * TY) void zA1(const BoxDev* __restrict__ boxes,
   double rs[8] = {}, rdiv = 0.0, rbm = 0.0, rum = 0.0, rc = 0.0, rrate = 0.0;
   long long rca = 0x7fffffffffffffffLL, rra = 0x7fffffffffffffffLL, rnf = 0, rnp = 0;
   auto packed = [&](int k_) { return b.off + ((long long)k_ * b.ny + gy) * b.nx + gx; };
-  // rho (halo 5) of plane r is fetched into registers one iteration ahead;
-  // the last fetch repeats the last valid plane
+  // rho (halo 5) of plane r is fetched into registers one iteration ahead
+  // (the last fetch repeats the last plane), and so are the own column's
+  // rho, p_z and B_z, which the z windows need 5 planes further at both ends
   constexpr int N5 = PlaneIdx<TX, TY, 5>::NPER;
   static_assert(N5 * NT == PR::NP, "plane padding");
-  const int rfirst = wall ? max(it.z0 - 5, 0) : it.z0 - 5;
   const int rlast = wall ? min(it.z1 + 4, N - 1) : it.z1 + 4;
-  T gR5[N5];
+  T gR5[N5], nr = T(0), np_ = T(0), nb = T(0);
   auto fetch = [&](int r_) {
     const long long pk = b.off + (long long)kk(r_) * pstride;
 #pragma unroll
     for (int i = 0; i < N5; ++i) gR5[i] = f.p[0][pk + i5.off[i]];
   };
-  fetch(rfirst);
+  auto ahead = [&](int r_) {
+    const long long o = col(wall ? max(min(r_, rlast), 0) : min(r_, rlast));
+    nr = f.p[0][o];
+    np_ = f.p[3][o];
+    nb = f.p[7][o];
+  };
+  ahead(it.z0 - 5);
+  fetch(it.z0);
   for (int r = it.z0 - 5; r <= it.z1 + 4; ++r) {
     T rr = T(0), pz = T(0), e = T(0), bz = T(0);
     T ubx = T(0), uby = T(0), bbx = T(0), bby = T(0), dxy = T(0), dxb = T(0);
     if (valid(r)) {
+      rr = nr;
+      pz = np_;
+      bz = nb;
+    }
+    if (r < it.z0 || r >= it.z1) {
+      ahead(r + 1);
+    } else {
       const int k = kk(r);
       __syncthreads();
 #pragma unroll
@@ -100,14 +123,10 @@ __global__ __launch_bounds__(TX * TY) void zA1(const BoxDev* __restrict__ boxes,
       load_plane(sPY, f.p[2], b, i3, k);
       load_plane(sBX, f.p[5], b, i3, k);
       load_plane(sBY, f.p[6], b, i3, k);
-      // the own column's values, in flight with the planes
-      const long long o = col(r);
-      pz = f.p[3][o];
-      e = f.p[4][o];
-      bz = f.p[7][o];
-      fetch(r < rlast ? r + 1 : r);
+      e = f.p[4][col(r)];
+      ahead(r + 1);
+      fetch(r + 1 < it.z1 ? r + 1 : r);
       __syncthreads();
-      rr = sR[PR::at(tx, ty)];
       // u_x = p_x / xdn(rho) on x-faces -2..3 of the own rows and u_y on
       // y-faces -2..3 of the own columns, one face per thread and pass
       for (int t = threadIdx.x; t < PP::N; t += NT) {
@@ -125,7 +144,7 @@ __global__ __launch_bounds__(TX * TY) void zA1(const BoxDev* __restrict__ boxes,
             op6<1, 1, T>([&](int m) { return sUY[PP::at(tx, ty + m)]; }, g.hyi);
       bbx = op6<0, 1, T>([&](int m) { return sBX[PP::at(tx + m, ty)]; }, T(0));
       bby = op6<0, 1, T>([&](int m) { return sBY[PP::at(tx, ty + m)]; }, T(0));
-      if (SMAG && own && r >= it.z0 && r < it.z1) {
+      if (SMAG && own) {
         const long long o = col(r);
         ws.q(3)[o] = op6<1, 1, T>([&](int m) { return sUX[PP::at(tx + m, ty)]; }, g.hxi);
         ws.q(4)[o] = op6<1, 1, T>([&](int m) { return sUY[PP::at(tx, ty + m)]; }, g.hyi);
@@ -135,7 +154,7 @@ __global__ __launch_bounds__(TX * TY) void zA1(const BoxDev* __restrict__ boxes,
         dxb = op6<1, 1, T>([&](int m) { return sBX[PP::at(tx + m, ty)]; }, g.hxi) +
               op6<1, 1, T>([&](int m) { return sBY[PP::at(tx, ty + m)]; }, g.hyi);
       // totals over the own cell of an interior plane (faces at the lower side)
-      if (RED && own && r >= it.z0 && r < it.z1 && interior(r)) {
+      if (RED && own && interior(r)) {
         const double rd = rr, pxd = sPX[PP::at(tx, ty)], pyd = sPY[PP::at(tx, ty)], pzd = pz;
         const double ed = e, bxd = sBX[PP::at(tx, ty)], byd = sBY[PP::at(tx, ty)], bzd = bz;
         const double uxd = sUX[PP::at(tx, ty)], uyd = sUY[PP::at(tx, ty)];
