@@ -465,12 +465,17 @@ static int set_tile(mhd_ctx* c, int tile) {
 
 // Whether a context runs its stages one thread per cell: the terms that
 // path has, and few enough cells.  us per RK stage, one thread per cell
-// against the march: float32 32^3 33.5 / 89, 64^3 74 / 133, 96^3 202 / 220,
-// 112^3 344 / 315, 128^3 518 / 380; with walls 64^3 121 / 179.  float64 24^3
-// 40.5 / 94, 48^3 72.5 / 131, 64^3 128 / 170, 80^3 237 / 222; with walls
-// 64^3 189 / 210.
+// against the march: float32 32^3 33 / 89, 64^3 75 / 115, 80^3 125 / 150,
+// 96^3 202 / 202, 100^3 235 / 244, 112^3 344 / 315; float64 48^3 71 / 114, 64^3
+// 129 / 154, 72^3 174 / 202, 80^3 205 / 206.  With walls every z stencil
+// also decides for the table or the constants, cell by cell: float32 64x64x74
+// 122 / 163, 80x80x90 197 / 195, 96x96x106 317 / 239; float64 48x48x58 108 /
+// 155, 64x64x74 189 / 195, 72x72x82 234 / 234.
 static bool cells_fit(const mhd_ctx* c) {
-  return c->nelem <= (c->esize == 4 ? 1000000 : 400000) && (c->p.terms & ~kCellTerms) == 0;
+  bool walls = false;
+  for (const BoxDev& d : c->h_boxes) walls |= d.wall != 0;
+  const long long most = c->esize == 4 ? (walls ? 550000 : 1000000) : 400000;
+  return c->nelem <= most && (c->p.terms & ~kCellTerms) == 0;
 }
 
 // Whether pass F streams the data it reads or writes once, so that the
