@@ -357,7 +357,7 @@ def run_ensemble(nbox=96, nsteps=20, ncheck=None):
 
 def run_clean(n=256, reps=5):
     """div B cleaning (mhd_divb_clean) of the n^3 periodic turbulent box in
-    float32 with seeded noise added to B: the first call (rocFFT plans,
+    float32 with seeded noise added to B: the first call (tables and
     scratch) and the mean of `reps` more, and the div B before and after."""
     import numpy as np
     import torch

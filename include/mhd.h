@@ -319,9 +319,10 @@ int mhd_reductions(mhd_ctx* ctx, void* const f[8], void* const dfdt[8],
  * down derivative is minus the transpose of the up one), so it is its own
  * adjoint.
  * Needs periodic boxes (MHD_EUNSUPPORTED with walls).  The first call
- * makes rocFFT plans per box shape and allocates scratch for the largest
- * box (about 3 of its fields), kept until mhd_destroy (MHD_ENOMEM,
- * MHD_EHIP on failure).  Returns without waiting.                          */
+ * allocates scratch for the largest box (2 to 3 of its fields) and tables,
+ * and makes rocFFT plans for box shapes whose edges the library's own
+ * transforms do not take; all kept until mhd_destroy (MHD_ENOMEM, MHD_EHIP
+ * on failure).  Returns without waiting.                                   */
 int mhd_divb_clean(mhd_ctx* ctx, void* const f[8]);
 
 /* The dt of the last step taken with dt == 0 (waits for the stream).      */

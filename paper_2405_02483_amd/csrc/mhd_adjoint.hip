@@ -18,7 +18,7 @@
 // consecutive workgroups of an XCD take consecutive cells, so that the
 // stencils' repeated reads hit in L1 (x, y) and in that XCD's L2 (z).
 //
-// The passes are bound by the arrays they stream: about 95 with the core
+// The passes are bound by the arrays they stream: 88 with the core
 // terms, some 190 reads and writes per cell and stage, against 1700 of an
 // operation-by-operation program, which this replaced (each operation a
 // pass over 2 to 5 arrays, 160 launches a stage).  One step's adjoint:

@@ -4,7 +4,7 @@
 //
 // A march is a serial chain: every plane costs a workgroup two or three
 // barriers and as many trips to memory (2.5 us a plane), and each chunk
-// recomputes up to 9 planes of lead-in, 8 launches a stage.  While the
+// recomputes some planes of lead-in, 8 launches a stage.  While the
 // arrays fit in the caches, the same quantities are cheaper read by every
 // cell from its neighbours: 7 launches without a barrier.  Each expression is
 // the march's own, in its order (z divergences summed over planes k-3..k+3

@@ -35,7 +35,7 @@ namespace smhd {
 // rho, u_z and B_z, so there the loop reads the own column (prefetched one
 // plane ahead) and skips the planes.  4 waves a SIMD in float32 (3 persistent), 2 in
 // float64: without the bound 32x8 tiles take 129 registers and 3 waves.
-// Against planes loaded throughout, per stage: 128^3 66 -> 49 us, 24 boxes of
+// Against planes loaded throughout, per stage: 128^3 66 -> 49 us, 96 boxes of
 // 48^3 to 96^3 806 -> 764, 150x132x140 79 -> 64, 256^3 295 -> 290, 512^3 2036 ->
 // 2058; float64 128^3 94 -> 80, 200x180x215 300 -> 293, 256^3 536 -> 543.
 //
