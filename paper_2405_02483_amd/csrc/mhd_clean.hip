@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 #include <rocfft/rocfft.h>
 
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
@@ -36,10 +37,14 @@ __device__ __forceinline__ void clean_coords(unsigned q, unsigned nx, unsigned n
 
 // The stencil kernels march along z: one thread per (x, y) column and
 // chunk of kCleanZ planes, the z operand in a register window of six
-// planes, so each plane of it is read once per chunk (plus the window's
-// warm-up) instead of six times.  A workgroup covers kCleanTX x kCleanTY
-// columns, so the rows of a y stencil are mostly shared within it.
-constexpr int kCleanZ = 32;
+// planes.  A workgroup covers kCleanTX x kCleanTY columns, so the rows of a y
+// stencil are mostly shared within it.  Short chunks: the window's five
+// warm-up planes hit in the caches that the neighbouring chunk fills, and a
+// march costs a trip to memory a plane.  us per call with chunks of 32, 16, 8
+// and 4 planes: float32 64^3 60 / 51 / 47 / 45, 128^3 108 / 93 / 90 / 87,
+// 256^3 422 / 413 / 410 / 403; float64 64^3 72 / 55 / 47 / 43, 128^3 147 /
+// 122 / 113 / 116, 256^3 788 / 762 / 760 / 757.
+constexpr int kCleanZ = 4;
 constexpr int kCleanTX = 64, kCleanTY = kCleanBlock / kCleanTX;
 
 __device__ __forceinline__ int wrapz(int k, int n) { return k < 0 ? k + n : (k >= n ? k - n : k); }
@@ -48,13 +53,13 @@ __device__ __forceinline__ int wrapz(int k, int n) { return k < 0 ? k + n : (k >
 template <class T>
 __global__ __launch_bounds__(kCleanBlock) void k_clean_div(BoxDev b, const T* __restrict__ bx,
                                                            const T* __restrict__ by,
-                                                           const T* __restrict__ bz, T* __restrict__ div) {
+                                                           const T* __restrict__ bz, T* __restrict__ div, int zc) {
   const int i = (int)(blockIdx.x * kCleanTX + threadIdx.x % kCleanTX);
   const int j = (int)(blockIdx.y * kCleanTY + threadIdx.x / kCleanTX);
   if (i >= b.nx || j >= b.ny) return;
   const unsigned nxy = (unsigned)b.nx * (unsigned)b.ny;
   const unsigned q = (unsigned)j * (unsigned)b.nx + (unsigned)i;
-  const int z0 = (int)blockIdx.z * kCleanZ, z1 = min(z0 + kCleanZ, b.nzt);
+  const int z0 = (int)blockIdx.z * zc, z1 = min(z0 + zc, b.nzt);
   const Geo<T> g(b);
   // window of bz at planes k-2 .. k+3 (the up derivative's samples)
   T w[6];
@@ -94,13 +99,13 @@ __global__ __launch_bounds__(kCleanBlock) void k_clean_solve(C* __restrict__ F, 
 template <class T>
 __global__ __launch_bounds__(kCleanBlock) void k_clean_apply(BoxDev b, const T* __restrict__ phi,
                                                              T* __restrict__ bx, T* __restrict__ by,
-                                                             T* __restrict__ bz) {
+                                                             T* __restrict__ bz, int zc) {
   const int i = (int)(blockIdx.x * kCleanTX + threadIdx.x % kCleanTX);
   const int j = (int)(blockIdx.y * kCleanTY + threadIdx.x / kCleanTX);
   if (i >= b.nx || j >= b.ny) return;
   const unsigned nxy = (unsigned)b.nx * (unsigned)b.ny;
   const unsigned q = (unsigned)j * (unsigned)b.nx + (unsigned)i;
-  const int z0 = (int)blockIdx.z * kCleanZ, z1 = min(z0 + kCleanZ, b.nzt);
+  const int z0 = (int)blockIdx.z * zc, z1 = min(z0 + zc, b.nzt);
   const Geo<T> g(b);
   auto at = [&](int x, int y, int z) {
     x = x < 0 ? x + b.nx : (x >= b.nx ? x - b.nx : x);
@@ -146,7 +151,7 @@ void symbol_sq(int n, int count, double h, std::vector<double>& out) {
 // classes of radices: with 11 and 13 in the same kernel as the powers of two
 // its registers (244) would leave 2 waves a SIMD.  us per call, these
 // transforms against rocFFT with kernels of their own for div B and the
-// solve: float32 24^3 45 / 50, 64^3 60 / 64, 100x120x84 101 / 110, 128^3 108 /
+// solve (stencils in chunks of 32 planes in both): float32 24^3 45 / 50, 64^3 60 / 64, 100x120x84 101 / 110, 128^3 108 /
 // 114, 256^3 416 / 506, but 160^3 189 / 162, 200^3 319 / 268 (170 registers);
 // float64 24^3 52 / 76, 96^3 110 / 159, 128^3 146 / 183, 256^3 775 / 914,
 // 160^3 244 / 249, 216x220x208 733 / 624.  The first call of a context:
@@ -609,17 +614,19 @@ int clean_boxes(CleanState** sp, const std::vector<BoxDev>& boxes, P8<T> f, hipS
     for (const auto& q : s->plans)
       if (q.nx == b.nx && q.ny == b.ny && q.nz == b.nzt) p = &q;
     const int nxh = b.nx / 2 + 1;
+    const int zc = std::max(kCleanZ, (b.nzt + 65534) / 65535);   // the grid's limit
     const dim3 gc((unsigned)((b.nx + kCleanTX - 1) / kCleanTX), (unsigned)((b.ny + kCleanTY - 1) / kCleanTY),
-                  (unsigned)((b.nzt + kCleanZ - 1) / kCleanZ));
+                  (unsigned)((b.nzt + zc - 1) / zc));
     const long long nc = (long long)nxh * b.ny * b.nzt;
     const dim3 gk((unsigned)((nc + kCleanBlock - 1) / kCleanBlock));
     if (!p->own || b.ncell > kCleanFuse)
-      hipLaunchKernelGGL(k_clean_div<T>, gc, dim3(kCleanBlock), 0, stream, b, f.p[5], f.p[6], f.p[7], real);
+      hipLaunchKernelGGL(k_clean_div<T>, gc, dim3(kCleanBlock), 0, stream, b, f.p[5], f.p[6], f.p[7], real,
+                         zc);
     if (p->own) {
       own_transforms<T>(b, f, p->ax, reinterpret_cast<const Cx<T>*>(s->twid), reinterpret_cast<Cx<T>*>(cplx), real,
                         kt + s->koff[bi], stream);
       hipLaunchKernelGGL(k_clean_apply<T>, gc, dim3(kCleanBlock), 0, stream, b, (const T*)real, f.p[5], f.p[6],
-                         f.p[7]);
+                         f.p[7], zc);
       continue;
     }
     void* in1[1] = {real};
@@ -638,7 +645,7 @@ int clean_boxes(CleanState** sp, const std::vector<BoxDev>& boxes, P8<T> f, hipS
       return 1;
     }
     hipLaunchKernelGGL(k_clean_apply<T>, gc, dim3(kCleanBlock), 0, stream, b, (const T*)real, f.p[5], f.p[6],
-                       f.p[7]);
+                       f.p[7], zc);
   }
   return 0;
 }
