@@ -359,10 +359,11 @@ int mhd_get_final_tile(const mhd_ctx* ctx, int32_t* tile);
  * shape and launch mode, in three rounds over all of them, keeps the
  * fastest (each candidate's best round) and, if ms is not NULL, writes the
  * milliseconds per stage to ms[2 * tile + persistent] (12 entries; 0 for a
- * shape not built for the context's dtype).  Then, with that shape for the
- * other passes, times every shape for pass F alone in both modes (three
- * rounds again), and keeps the fastest combination if it beats the uniform
- * launch by more than 1 % (mhd_get_launch, mhd_get_final_tile).  dfdt is
+ * shape not built for the context's dtype).  Then, with that shape (and any
+ * within 2 % of it) for the other passes, times every shape for pass F alone
+ * in both modes (three rounds again), and keeps the fastest combination if
+ * it beats the uniform launch by more than 1 % (mhd_get_launch,
+ * mhd_get_final_tile).  dfdt is
  * overwritten; with walls the ghost planes of f are filled.  Allocates 8
  * fields of scratch for the call (MHD_ENOMEM).  Waits for the stream.      */
 int mhd_autotune(mhd_ctx* ctx, void* const f[8], void* const dfdt[8], int32_t reps,
