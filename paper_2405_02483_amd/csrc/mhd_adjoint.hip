@@ -65,16 +65,116 @@ enum VArr : int {
   VA_EDX,                   // T_EDIFFAV: of the plane mean's log, cell by cell
   VA_SE,                    // T_SMAG: shear on the edges, then its centre value and cotangent
   VA_SC = VA_SE + 3,
-  VA_TAU = VA_SC + 3,       // T_QUENCH: raw stress, q, its maxima, cotangents (6 each)
+  VA_RGH = VA_SC + 3,       // T_ORDER2: rough cells, flags, second-order parts of the strain's cotangents
+  VA_RGF, VA_HS2, VA_SD2 = VA_HS2 + 3,
+  VA_TAU = VA_SD2 + 3,      // T_QUENCH: raw stress, q, its maxima, cotangents (6 each)
   VA_QQ = VA_TAU + 6, VA_Q1 = VA_QQ + 6, VA_Q2 = VA_Q1 + 6, VA_Q3 = VA_Q2 + 6, VA_TB = VA_Q3 + 6,
   VA_QB0 = VA_TB + 6, VA_QB1 = VA_QB0 + 6,
-  VA_RGH = VA_QB1 + 6,      // T_ORDER2: rough cells, flags, second-order parts of the strain's cotangents
-  VA_RGF, VA_HS2, VA_SD2 = VA_HS2 + 3,
-  VA_COUNT = VA_SD2 + 3
+  VA_COUNT = VA_QB1 + 6
 };
 enum EdgeQ : int { EQ_UAB = 0, EQ_UBA, EQ_HS, EQ_PAB, EQ_PBA, EQ_BAB, EQ_BBA, EQ_J, EQ_RHO, EQ_LNU, EQ_COUNT };
 
-template <class T> struct VK {
+constexpr int kFillTmp = 6;   // arrays that vjp_fill takes of the workspace
+constexpr unsigned kCoreTerms = T_CONT | T_ADV | T_PRES | T_VISC | T_LORENTZ | T_INDUCT | T_RESIST | T_EDIFF;
+
+// What a set of terms takes of the transpose: the workspace arrays, the
+// launches and, within a launch, the operands.
+struct Need {
+  unsigned tm;
+  bool cst, etac;           // constant viscosity, constant resistivity
+  template <class T>
+  __host__ __device__ __forceinline__ explicit Need(const Phys<T>& ph)
+      : tm(ph.terms), cst(ph.nu_const > T(0)), etac(ph.eta_const > T(0)) {}
+  __host__ __device__ __forceinline__ bool any(unsigned t) const { return tm & t; }
+  __host__ __device__ __forceinline__ bool heat() const { return any(T_VISC | T_RESIST); }
+  // the viscosity on the edges; anywhere; as the maximum of the speed-like one
+  __host__ __device__ __forceinline__ bool enu() const { return any(T_VISC) || (any(T_RESIST) && !etac); }
+  __host__ __device__ __forceinline__ bool nu() const { return enu() || any(T_EDIFF); }
+  __host__ __device__ __forceinline__ bool chain() const { return nu() && !cst; }
+  __host__ __device__ __forceinline__ bool smag() const { return any(T_SMAG) && chain(); }
+  __host__ __device__ __forceinline__ bool quench() const { return any(T_QUENCH) && any(T_VISC); }
+  __host__ __device__ __forceinline__ bool order2() const { return any(T_ORDER2) && any(T_VISC); }
+  __host__ __device__ __forceinline__ bool lnp() const { return any(T_LNP) && any(T_PRES); }
+  __host__ __device__ __forceinline__ bool ediffav() const { return any(T_EDIFFAV) && any(T_EDIFF); }
+  // face velocities and densities, edges, the faces' fluxes, the centre
+  __host__ __device__ __forceinline__ bool faces() const {
+    return any(T_ADV | T_VISC | T_INDUCT | T_PRES | T_EDIFF) || chain();
+  }
+  __host__ __device__ __forceinline__ bool edges() const {
+    return any(T_ADV | T_VISC | T_INDUCT | T_RESIST | T_LORENTZ) || smag();
+  }
+  __host__ __device__ __forceinline__ bool fluxes() const { return any(T_ADV | T_EDIFF) || lnp(); }
+  __host__ __device__ __forceinline__ bool strain() const { return any(T_VISC | T_PRES) || chain(); }
+  __host__ __device__ __forceinline__ bool centre() const { return strain() || any(T_ADV | T_COOL); }
+  __host__ __device__ __forceinline__ bool shear() const { return any(T_VISC) || smag(); }
+  __host__ __device__ __forceinline__ bool cu() const { return any(T_ADV) || chain(); }
+  __host__ __device__ __forceinline__ bool rhob() const { return any(T_VISC | T_COOL) || chain(); }
+  __host__ __device__ __forceinline__ bool eb() const { return any(T_PRES | T_COOL) || chain(); }
+};
+
+// A set of terms that needs more than kLeanArrays of the 88 core arrays, and
+// leaves at most kFullSpare of the full layout unused, runs with every array
+// (ALL): its kernels know where they lie and branch less.  Others take only
+// what they need, through a table.  Measured, us of one transpose, every
+// array against what is needed: 128^3 float32 continuity alone 614 / 106,
+// viscous stress (44 arrays) 641 / 513, ideal MHD (46) 656 / 491, Lorentz force
+// 608 / 192; but constant coefficients without energy diffusion (64) 553 / 640,
+// without energy diffusion (74) 697 / 795, hydrodynamics (79) 736 / 771, and
+// the core terms through the table 752 / 1088 (the gathers' 40 and more base
+// pointers fill the scalar registers).  The spare of 40 keeps every set below
+// the workspace that an operation-by-operation program took for it.
+constexpr int kLeanArrays = 50, kFullSpare = 40;
+
+// Where each array lies in the workspace (at[id], in arrays; all: at[id] =
+// id); returns the number of arrays (none with the continuity alone, 44 with
+// the viscous stress alone, 88 with the core terms).
+int layout(const Need& nd, unsigned char (&at)[VA_COUNT], bool& all) {
+  int n = 0;
+  auto take = [&](bool need, int id, int count) {
+    for (int q = 0; need && q < count; ++q) at[id + q] = (unsigned char)n++;
+  };
+  for (unsigned char& a : at) a = 0;
+  take(nd.faces(), VA_U, 6);           // with VA_R
+  take(nd.any(T_EDIFF), VA_EM, 1);
+  take(nd.any(T_EDIFF) || nd.order2(), VA_LEM, 1);
+  take(nd.heat(), VA_XWE, 2);
+  take(nd.nu(), VA_NT, 1);
+  take(nd.enu(), VA_LNT, 3);           // with VA_XL, VA_YL
+  const bool eq[EQ_COUNT] = {nd.any(T_ADV | T_INDUCT), nd.any(T_ADV | T_INDUCT), nd.shear(), nd.any(T_ADV),
+                             nd.any(T_ADV), nd.any(T_INDUCT | T_LORENTZ), nd.any(T_INDUCT | T_LORENTZ),
+                             nd.any(T_RESIST | T_LORENTZ), nd.any(T_VISC), nd.enu()};
+  for (int e = 0; e < 3; ++e)
+    for (int q = 0; q < EQ_COUNT; ++q) take(eq[q], VA_EDGE + e * EQ_COUNT + q, 1);
+  take(nd.any(T_ADV), VA_XE, 3);
+  take(nd.any(T_EDIFF), VA_XNT, 12);   // with VA_XEM, VA_DLEM, VA_RF
+  take(nd.any(T_ADV), VA_UF, 3);
+  take(nd.enu(), VA_XLB, 2);
+  take(nd.chain(), VA_NTB, 3);         // with VA_MB0, VA_MB1
+  take(nd.any(T_ADV), VA_CP, 3);
+  take(nd.cu(), VA_CU, 3);
+  take(nd.strain(), VA_SD, 3);
+  take(nd.chain(), VA_CB, 3);
+  take(nd.rhob(), VA_RHOB, 1);
+  take(nd.eb(), VA_EB, 1);
+  take(nd.faces(), VA_RB, 3);
+  take(nd.chain(), VA_MX, 4);
+  const bool most = n > kLeanArrays;
+  take(nd.chain() && nd.any(T_MAX5), VA_MX5, 3);
+  take(nd.lnp(), VA_LNP, 7);           // with VA_QI, VA_QD
+  take(nd.any(T_DIVB), VA_DVB, 1);
+  take(nd.ediffav(), VA_EDX, 1);
+  take(nd.smag(), VA_SE, 6);           // with VA_SC
+  take(nd.order2(), VA_RGH, VA_TAU - VA_RGH);
+  take(nd.quench(), VA_TAU, VA_COUNT - VA_TAU);
+  const int full = nd.quench() ? VA_COUNT : nd.order2() ? VA_TAU : nd.any(T_SMAG) ? VA_RGH : nd.ediffav() ? VA_SE :
+                   nd.any(T_DIVB) ? VA_EDX : nd.lnp() ? VA_DVB : nd.any(T_MAX5) ? VA_LNP : VA_CORE;
+  all = most && full <= n + kFullSpare;
+  if (!all) return n;
+  for (int q = 0; q < VA_COUNT; ++q) at[q] = (unsigned char)q;
+  return full;
+}
+
+template <class T> struct VArgs {
   const BoxDev* boxes;
   const Blk* tab;
   int nblk;
@@ -91,7 +191,17 @@ template <class T> struct VK {
   int acc;
   int nmax;                 // maxima in the chain (3, or 6 with T_MAX5)
 };
+// (with every array the table stays out of the launches' arguments)
+template <class T, bool ALL> struct VK : VArgs<T> {
+  __host__ __device__ __forceinline__ int slot(int id) const { return id; }
+};
+template <class T> struct VK<T, false> : VArgs<T> {
+  unsigned char at[VA_COUNT];   // layout()
+  __host__ __device__ __forceinline__ int slot(int id) const { return at[id]; }
+};
 
+// ALL: every core term's arrays are kept, at addresses known to the compiler,
+// and read and written without a look at the terms.
 #define VJP_CELL                                                             \
   const int per_ = (K.nblk + 7) >> 3;                                        \
   const int bi_ = (int)(blockIdx.x & 7u) * per_ + (int)(blockIdx.x >> 3);    \
@@ -100,13 +210,16 @@ template <class T> struct VK {
   if ((int)threadIdx.x >= tb_.n) return;                                     \
   const BoxDev& b = K.boxes[tb_.box];                                        \
   const Cell<T, W> c(b, (unsigned)tb_.start + threadIdx.x, K.zt);            \
-  auto A = [&](int id) -> T* { return K.base + (long long)id * K.stride + b.off; };   \
+  auto An = [&](int slot) -> T* { return K.base + (long long)slot * K.stride + b.off; };   \
+  auto A = [&](int id) -> T* { return An(K.slot(id)); };                      \
+  auto Am = [&](int id, int m) -> T* { return An(K.slot(id) + m); };   \
   auto S = [&](int v) -> const T* { return K.s.p[v] + b.off; };              \
   auto Wt = [&](int v) -> const T* { return K.w.p[v] + b.off; };             \
   const unsigned tm = K.ph.terms;                                            \
-  (void)A; (void)S; (void)Wt; (void)tm;
+  const Need nd(K.ph);                                                       \
+  (void)A; (void)An; (void)Am; (void)S; (void)Wt; (void)tm; (void)nd;
 
-#define VJP_KERNEL template <class T, bool W> __global__ __launch_bounds__(kBlock) void
+#define VJP_KERNEL template <class T, bool W, bool ALL> __global__ __launch_bounds__(kBlock) void
 
 // The same with at least `f32` waves a SIMD in float32.  The kernels that
 // gather most wait for the caches; left alone the compiler hoists loads until
@@ -116,7 +229,7 @@ template <class T> struct VK {
 // every such bound spills (edges and faces 25 -> 41 us at 48^3), so there the
 // compiler's choice stands.
 #define VJP_KERNEL_WAVES(f32)                                    \
-  template <class T, bool W>                                     \
+  template <class T, bool W, bool ALL>                           \
   __global__ __launch_bounds__(kBlock)                           \
       __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? f32 : 1))) void
 
@@ -139,27 +252,33 @@ template <class T, bool W> __device__ __forceinline__ double h_shock(const Cell<
 
 // ---------------------------------------------------------------------------
 // Face densities and velocities, e_m, ln e_m, and w_e's x and y transposes.
-VJP_KERNEL k_prim(VK<T> K) {
+VJP_KERNEL k_prim(VK<T, ALL> K) {
   VJP_CELL
   const T* rho = S(0);
-  const T rx = c.template dn<X>(rho), ry = c.template dn<Y>(rho), rz = c.template dn<Z>(rho);
-  const T em = c.ld(S(4)) / c.ld(rho);
-  c.st(A(VA_R), rx);
-  c.st(A(VA_R + 1), ry);
-  c.st(A(VA_R + 2), rz);
-  c.st(A(VA_U), c.ld(S(1)) / rx);
-  c.st(A(VA_U + 1), c.ld(S(2)) / ry);
-  c.st(A(VA_U + 2), c.ld(S(3)) / rz);
-  c.st(A(VA_EM), em);
-  c.st(A(VA_LEM), log(em));
-  c.st(A(VA_XWE), c.template upT<X>(Wt(4)));
-  c.st(A(VA_YWE), c.template upT<Y>(Wt(4)));
-  if ((tm & T_PRES) && (tm & T_LNP)) c.st(A(VA_LNP), log(K.ph.gamma1 * c.ld(S(4))));
+  if (ALL || nd.faces()) {
+    const T rx = c.template dn<X>(rho), ry = c.template dn<Y>(rho), rz = c.template dn<Z>(rho);
+    c.st(A(VA_R), rx);
+    c.st(A(VA_R + 1), ry);
+    c.st(A(VA_R + 2), rz);
+    c.st(A(VA_U), c.ld(S(1)) / rx);
+    c.st(A(VA_U + 1), c.ld(S(2)) / ry);
+    c.st(A(VA_U + 2), c.ld(S(3)) / rz);
+  }
+  if (ALL || nd.any(T_EDIFF) || nd.order2()) {
+    const T em = c.ld(S(4)) / c.ld(rho);
+    if (ALL || nd.any(T_EDIFF)) c.st(A(VA_EM), em);
+    c.st(A(VA_LEM), log(em));
+  }
+  if (ALL || nd.heat()) {
+    c.st(A(VA_XWE), c.template upT<X>(Wt(4)));
+    c.st(A(VA_YWE), c.template upT<Y>(Wt(4)));
+  }
+  if (nd.lnp()) c.st(A(VA_LNP), log(K.ph.gamma1 * c.ld(S(4))));
 }
 
 // Second-order switch: rough cells, then the flags of the positions a rough
 // cell touches (bit 0 the centre, 1 + c the edge along axis c).
-VJP_KERNEL k_rough(VK<T> K) {
+VJP_KERNEL k_rough(VK<T, ALL> K) {
   VJP_CELL
   const T* rho = S(0);
   const T* le = A(VA_LEM);
@@ -179,7 +298,7 @@ VJP_KERNEL k_rough(VK<T> K) {
   }
   c.st(A(VA_RGH), m > K.ph.d2_lim ? T(1) : T(0));
 }
-VJP_KERNEL k_rough_flags(VK<T> K) {
+VJP_KERNEL k_rough_flags(VK<T, ALL> K) {
   VJP_CELL
   const T* r = A(VA_RGH);
   auto at = [&](int x, int y, int z) {
@@ -193,13 +312,13 @@ VJP_KERNEL k_rough_flags(VK<T> K) {
   c.st(A(VA_RGF), T(f));
 }
 
-template <class T> __device__ __forceinline__ bool order2(const VK<T>& K) {
+template <class T> __device__ __forceinline__ bool order2(const VArgs<T>& K) {
   return (K.ph.terms & T_ORDER2) && (K.ph.terms & T_VISC);
 }
-template <class T> __device__ __forceinline__ bool quenched(const VK<T>& K) {
+template <class T> __device__ __forceinline__ bool quenched(const VArgs<T>& K) {
   return (K.ph.terms & T_QUENCH) && (K.ph.terms & T_VISC);
 }
-template <class T> __device__ __forceinline__ bool smag(const VK<T>& K) {
+template <class T> __device__ __forceinline__ bool smag(const VArgs<T>& K) {
   return (K.ph.terms & T_SMAG) && !(K.ph.nu_const > T(0));
 }
 
@@ -212,22 +331,22 @@ __device__ __forceinline__ T shear(const Cell<T, W>& c, const F& A) {
 }
 // The strain that the stress takes: second order where flagged.
 template <int C, class T, bool W, class F>
-__device__ __forceinline__ T strain_e(const Cell<T, W>& c, const VK<T>& K, const F& A) {
+__device__ __forceinline__ T strain_e(const Cell<T, W>& c, const VArgs<T>& K, const F& A) {
   if (order2(K) && ((unsigned)c.ld(A(VA_RGF)) & (2u << C))) return shear<C, true>(c, A);
   return shear<C, false>(c, A);
 }
 
 // T_SMAG: the shear on the edges (blockIdx.y: edge direction).
-VJP_KERNEL k_shear(VK<T> K) {
+VJP_KERNEL k_shear(VK<T, ALL> K) {
   VJP_CELL
   const int e = (int)blockIdx.y;
-  c.st(A(VA_SE + e), e == X ? shear<X, false>(c, A) : (e == Y ? shear<Y, false>(c, A) : shear<Z, false>(c, A)));
+  c.st(Am(VA_SE, e), e == X ? shear<X, false>(c, A) : (e == Y ? shear<Y, false>(c, A) : shear<Z, false>(c, A)));
 }
 
 // The speed-like viscosity (eq. RMnu, eq. nusmag).  Each product and sum is
 // rounded on its own, whatever the surrounding expression, so that ties and
 // signs (max, relu) fall the same way wherever this is evaluated.
-VJP_KERNEL k_nus(VK<T> K) {
+VJP_KERNEL k_nus(VK<T, ALL> K) {
   VJP_CELL
   const Phys<T>& ph = K.ph;
   const T sxx = c.template dup<X>(A(VA_U)), syy = c.template dup<Y>(A(VA_U + 1)), szz = c.template dup<Z>(A(VA_U + 2));
@@ -267,7 +386,7 @@ VJP_KERNEL k_nus(VK<T> K) {
 __host__ __device__ __forceinline__ int mx_id(int m) { return m < 4 ? VA_MX + m : VA_MX5 + (m - 4); }
 
 // Maximum over three cells along x, y, z in turn: the three stages.
-VJP_KERNEL k_max3(VK<T> K) {
+VJP_KERNEL k_max3(VK<T, ALL> K) {
   VJP_CELL
   const T* a = A(VA_MX);
   auto mx = [&](unsigned f) {
@@ -284,27 +403,27 @@ VJP_KERNEL k_max3(VK<T> K) {
   c.st(A(VA_MX + 3), m3);
 }
 // One stage (five cells: each axis twice).
-template <class T, bool W, int AX> __global__ __launch_bounds__(kBlock) void k_max1(VK<T> K, int src, int dst) {
+template <class T, bool W, bool ALL, int AX> __global__ __launch_bounds__(kBlock) void k_max1(VK<T, ALL> K, int src, int dst) {
   VJP_CELL
-  c.st(A(dst), c.template max3<AX>(A(src)));
+  c.st(An(dst), c.template max3<AX>(An(src)));
 }
 // Transpose of one stage; blockIdx.y: component (quenching).
-template <class T, bool W, int AX>
-__global__ __launch_bounds__(kBlock) void k_max1T(VK<T> K, int prim, int yb, int dst) {
+template <class T, bool W, bool ALL, int AX>
+__global__ __launch_bounds__(kBlock) void k_max1T(VK<T, ALL> K, int prim, int yb, int dst) {
   VJP_CELL
   const int m = (int)blockIdx.y;
-  c.st(A(dst + m), c.template max3T<AX>(A(prim + m), A(yb + m)));
+  c.st(An(dst + m), c.template max3T<AX>(An(prim + m), An(yb + m)));
 }
 
 // <nu>: the mean over three cells along each axis (the available ones at
 // the ends of a wall axis), the floor, and ln.  nu_const: the constant.
-VJP_KERNEL k_mean(VK<T> K) {
+VJP_KERNEL k_mean(VK<T, ALL> K, int mx) {
   VJP_CELL
   T v;
   if (K.ph.nu_const > T(0)) {
     v = T(double(K.ph.nu_const) / b.hmin);
   } else {
-    const T* a = A(mx_id(K.nmax));
+    const T* a = An(mx);
     auto row = [&](unsigned f) { return (c.ld(a, f + c.d[X][2]) + c.ld(a, f) + c.ld(a, f + c.d[X][4])) / T(3); };
     auto pl = [&](unsigned f) { return (row(f + c.d[Y][2]) + row(f) + row(f + c.d[Y][4])) / T(3); };
     const bool lo = c.has(-1), hi = c.has(1);
@@ -315,39 +434,41 @@ VJP_KERNEL k_mean(VK<T> K) {
   }
   v = v > T(1e-30) ? v : T(1e-30);
   c.st(A(VA_NT), v);
-  c.st(A(VA_LNT), log(v));
+  if (ALL || nd.enu()) c.st(A(VA_LNT), log(v));
 }
-VJP_KERNEL k_lines(VK<T> K) {
+VJP_KERNEL k_lines(VK<T, ALL> K) {
   VJP_CELL
   c.st(A(VA_XL), c.template dn<X>(A(VA_LNT)));
   c.st(A(VA_YL), c.template dn<Y>(A(VA_LNT)));
 }
 
 // Density, viscosity and w_e's heating cotangent on the edge along C.
-template <int C, class T, bool W, class F> struct EdgeBase {
-  T rho, nu, Qb;
-  __device__ __forceinline__ EdgeBase(const Cell<T, W>& c, const F& A) {
+template <bool ALL, int C, class T, bool W, class F> struct EdgeBase {
+  T rho = T(0), nu = T(0), Qb = T(0);
+  __device__ __forceinline__ EdgeBase(const Cell<T, W>& c, const F& A, const Need& nd) {
     constexpr int Q = C == Z ? Y : Z;                    // the second axis
     constexpr int first = C == X ? 1 : 0;                // interpolated along y (edge x) or x first
-    rho = c.template dn<Q>(A(VA_R + first));
-    nu = len_e(c, C) * exp(c.template dn<Q>(A(C == X ? VA_YL : VA_XL)));
-    Qb = c.template upT<Q>(A(C == X ? VA_YWE : VA_XWE));
+    if (ALL || nd.any(T_VISC)) rho = c.template dn<Q>(A(VA_R + first));
+    if (ALL || nd.enu()) nu = len_e(c, C) * exp(c.template dn<Q>(A(C == X ? VA_YL : VA_XL)));
+    if (ALL || nd.heat()) Qb = c.template upT<Q>(A(C == X ? VA_YWE : VA_XWE));
   }
 };
 
 // T_QUENCH: raw stress (roles 0..2 the edges, 3..5 the centre), q, the
 // maxima over 3x3x3 cells.
 template <int C, class T, bool W, class F>
-__device__ __forceinline__ T raw_edge(const Cell<T, W>& c, const VK<T>& K, const F& A) {
-  const EdgeBase<C, T, W, F> E(c, A);
+__device__ __forceinline__ T raw_edge(const Cell<T, W>& c, const VArgs<T>& K, const F& A) {
+  const EdgeBase<true, C, T, W, F> E(c, A, Need(K.ph));   // (with T_VISC)
   return E.rho * E.nu * strain_e<C>(c, K, A);
 }
 // Strain and div u at the centre as the stress takes them (vs, vD), and the
 // sixth-order ones (s, D).
 template <class T, bool W, class F> struct Centre {
-  T s[3], D, vs[3], vD;
-  bool rough;
-  __device__ __forceinline__ Centre(const Cell<T, W>& c, const VK<T>& K, const F& A) {
+  T s[3] = {}, D = T(0), vs[3] = {}, vD = T(0);
+  bool rough = false;
+  // (need false: nothing takes them)
+  __device__ __forceinline__ Centre(const Cell<T, W>& c, const VArgs<T>& K, const F& A, bool need = true) {
+    if (!need) return;
     s[0] = c.template dup<X>(A(VA_U));
     s[1] = c.template dup<Y>(A(VA_U + 1));
     s[2] = c.template dup<Z>(A(VA_U + 2));
@@ -365,13 +486,13 @@ template <class T, bool W, class F> struct Centre {
     }
   }
 };
-VJP_KERNEL k_tau(VK<T> K) {
+VJP_KERNEL k_tau(VK<T, ALL> K) {
   VJP_CELL
   const int m = (int)blockIdx.y;
   T t;
   if (m < 3) {
     t = m == X ? raw_edge<X>(c, K, A) : (m == Y ? raw_edge<Y>(c, K, A) : raw_edge<Z>(c, K, A));
-    c.st(A(VA_TAU + m), t);
+    c.st(Am(VA_TAU, m), t);
   } else if (m == 3) {
     const Centre<T, W, decltype(A)> E(c, K, A);
     const T r = c.ld(S(0)), nt = c.ld(A(VA_NT));
@@ -380,18 +501,18 @@ VJP_KERNEL k_tau(VK<T> K) {
       c.st(A(VA_TAU + 3 + a), r * (len_c(c, a) * nt) * (E.vs[a] + K.ph.c1 * E.vD));
   }
 }
-VJP_KERNEL k_quench(VK<T> K) {
+VJP_KERNEL k_quench(VK<T, ALL> K) {
   VJP_CELL
   const int m = (int)blockIdx.y;
-  const T* t = A(VA_TAU + m);
+  const T* t = Am(VA_TAU, m);
   const T s = fabs(c.template second<X>(t)) + fabs(c.template second<Y>(t)) + fabs(c.template second<Z>(t));
   const T den = fabs(c.ld(t)) + s / K.ph.q_max;
-  c.st(A(VA_QQ + m), den > T(0) ? s / den : T(0));
+  c.st(Am(VA_QQ, m), den > T(0) ? s / den : T(0));
 }
-VJP_KERNEL k_quench_max(VK<T> K) {
+VJP_KERNEL k_quench_max(VK<T, ALL> K) {
   VJP_CELL
   const int m = (int)blockIdx.y;
-  const T* a = A(VA_QQ + m);
+  const T* a = Am(VA_QQ, m);
   auto mx = [&](unsigned f) {
     return fmax(fmax(c.ld(a, f + c.d[X][2]), c.ld(a, f)), c.ld(a, f + c.d[X][4]));
   };
@@ -401,14 +522,14 @@ VJP_KERNEL k_quench_max(VK<T> K) {
   T m3 = m2;
   if (c.has(-1)) m3 = fmax(m3, my(c.d[Z][2], mx(c.d[Z][2])));
   if (c.has(1)) m3 = fmax(m3, my(c.d[Z][4], mx(c.d[Z][4])));
-  c.st(A(VA_Q1 + m), m1);
-  c.st(A(VA_Q2 + m), m2);
-  c.st(A(VA_Q3 + m), m3);
+  c.st(Am(VA_Q1, m), m1);
+  c.st(Am(VA_Q2, m), m2);
+  c.st(Am(VA_Q3, m), m3);
 }
 // The factor of component m at the cell.
 template <class T, bool W, class F>
-__device__ __forceinline__ T qfac(const Cell<T, W>& c, const VK<T>& K, const F& A, int m) {
-  const T q = c.ld(A(VA_Q3 + m));
+__device__ __forceinline__ T qfac(const Cell<T, W>& c, const VArgs<T>& K, const F& A, int m) {
+  const T q = c.ld(A(VA_Q3) + (long long)m * K.stride);
   return q < K.ph.q_lim ? q : K.ph.q_lim;
 }
 
@@ -424,19 +545,19 @@ __device__ __forceinline__ void flux_cot(const Cell<T, W>& c, const F& Wt, T& g1
 // The quenched stress's cotangent, and through the cap that of the maximum
 // of q.
 template <int C, class T, bool W, class F, class G>
-__device__ __forceinline__ T taub_edge(const Cell<T, W>& c, const VK<T>& K, const F& A, const G& Wt) {
-  const EdgeBase<C, T, W, F> E(c, A);
+__device__ __forceinline__ T taub_edge(const Cell<T, W>& c, const VArgs<T>& K, const F& A, const G& Wt) {
+  const EdgeBase<true, C, T, W, F> E(c, A, Need(K.ph));   // (with T_VISC)
   T g1, g2;
   flux_cot<C>(c, Wt, g1, g2);
   return g1 + g2 + T(2) * strain_e<C>(c, K, A) * E.Qb;
 }
-VJP_KERNEL k_taub(VK<T> K) {
+VJP_KERNEL k_taub(VK<T, ALL> K) {
   VJP_CELL
   const int m = (int)blockIdx.y;
   auto put = [&](int q, T tb) {
-    const T x = c.ld(A(VA_Q3 + q));
-    c.st(A(VA_TB + q), tb);
-    c.st(A(VA_QB0 + q), x < K.ph.q_lim ? c.ld(A(VA_TAU + q)) * tb : T(0));
+    const T x = c.ld(Am(VA_Q3, q));
+    c.st(Am(VA_TB, q), tb);
+    c.st(Am(VA_QB0, q), x < K.ph.q_lim ? c.ld(Am(VA_TAU, q)) * tb : T(0));
   };
   if (m < 3) {
     put(m, m == X ? taub_edge<X>(c, K, A, Wt) : (m == Y ? taub_edge<Y>(c, K, A, Wt) : taub_edge<Z>(c, K, A, Wt)));
@@ -450,29 +571,29 @@ VJP_KERNEL k_taub(VK<T> K) {
 }
 // From the cotangent of q: that of D2 (into QB0), and the stress's own
 // through |tau| and the factor (into TB).
-VJP_KERNEL k_quenchT(VK<T> K) {
+VJP_KERNEL k_quenchT(VK<T, ALL> K) {
   VJP_CELL
   const int m = (int)blockIdx.y;
-  const T* t = A(VA_TAU + m);
-  const T qb = c.template max3T<X>(A(VA_QQ + m), A(VA_QB0 + m));
+  const T* t = Am(VA_TAU, m);
+  const T qb = c.template max3T<X>(Am(VA_QQ, m), Am(VA_QB0, m));
   const T s = fabs(c.template second<X>(t)) + fabs(c.template second<Y>(t)) + fabs(c.template second<Z>(t));
   const T tv = c.ld(t);
   const T den = fabs(tv) + s / K.ph.q_max;
-  const T q = c.ld(A(VA_QQ + m));
+  const T q = c.ld(Am(VA_QQ, m));
   const T sb = den > T(0) ? qb / den : T(0);
   const T db = den > T(0) ? -(qb * q / den) : T(0);
-  c.st(A(VA_QB1 + m), sb + db / K.ph.q_max);
-  T tb = c.ld(A(VA_TB + m)) * qfac(c, K, A, m);
+  c.st(Am(VA_QB1, m), sb + db / K.ph.q_max);
+  T tb = c.ld(Am(VA_TB, m)) * qfac(c, K, A, m);
   tb += tv > T(0) ? db : (tv < T(0) ? -db : T(0));
-  c.st(A(VA_TB + m), tb);
+  c.st(Am(VA_TB, m), tb);
 }
 // The second differences' transposes, added to the stress's cotangent.
-VJP_KERNEL k_quenchT2(VK<T> K) {
+VJP_KERNEL k_quenchT2(VK<T, ALL> K) {
   VJP_CELL
   const int m = (int)blockIdx.y;
-  const T* t = A(VA_TAU + m);
-  const T* sb = A(VA_QB1 + m);
-  T tb = c.ld(A(VA_TB + m));
+  const T* t = Am(VA_TAU, m);
+  const T* sb = Am(VA_QB1, m);
+  T tb = c.ld(Am(VA_TB, m));
   auto axis = [&](auto ax) {
     constexpr int AX = decltype(ax)::value;
     auto z = [&](int q) {
@@ -493,7 +614,7 @@ VJP_KERNEL k_quenchT2(VK<T> K) {
   axis(std::integral_constant<int, X>{});
   axis(std::integral_constant<int, Y>{});
   axis(std::integral_constant<int, Z>{});
-  c.st(A(VA_TB + m), tb);
+  c.st(Am(VA_TB, m), tb);
 }
 
 // ---------------------------------------------------------------------------
@@ -504,19 +625,26 @@ VJP_KERNEL k_quenchT2(VK<T> K) {
 //   dp_P += dup_Q(tau - pP uQ) - up_Q(J bQ) / mu,
 //   dp_Q += dup_P(tau - pQ uP) + up_P(J bP) / mu,
 //   dB_P -= dup_Q(E), dB_Q += dup_P(E), de += up_P up_Q(2 tau S + eta J^2 / mu).
-template <int C, class T, bool W, class F, class G, class H>
-__device__ __forceinline__ void edge_back(const Cell<T, W>& c, const VK<T>& K, const F& A, const G& Wt, const H& S) {
+template <bool ALL, int C, class T, bool W, class F, class G, class H>
+__device__ __forceinline__ void edge_back(const Cell<T, W>& c, const VArgs<T>& K, const Need& nd, const F& A, const G& Wt,
+                                          const H& S) {
   constexpr int P = (C + 1) % 3, Q = (C + 2) % 3;
   const Phys<T>& ph = K.ph;
-  const unsigned tm = ph.terms;
+  const unsigned tm = nd.tm;
   const bool visc = tm & T_VISC, res = tm & T_RESIST, ind = tm & T_INDUCT, lor = tm & T_LORENTZ,
              adv = tm & T_ADV;
-  const EdgeBase<C, T, W, F> E(c, A);
-  const T uP = c.template dn<Q>(A(VA_U + P)), uQ = c.template dn<P>(A(VA_U + Q));
-  const T bP = c.template dn<Q>(S(5 + P)), bQ = c.template dn<P>(S(5 + Q));
-  const T J = c.template ddn<P>(S(5 + Q)) - c.template ddn<Q>(S(5 + P));
-  T g1, g2;
-  flux_cot<C>(c, Wt, g1, g2);
+  const EdgeBase<ALL, C, T, W, F> E(c, A, nd);
+  T uP = T(0), uQ = T(0), bP = T(0), bQ = T(0), J = T(0), g1 = T(0), g2 = T(0);
+  if (ALL || nd.any(T_ADV | T_INDUCT)) {
+    uP = c.template dn<Q>(A(VA_U + P));
+    uQ = c.template dn<P>(A(VA_U + Q));
+  }
+  if (ALL || nd.any(T_INDUCT | T_LORENTZ)) {
+    bP = c.template dn<Q>(S(5 + P));
+    bQ = c.template dn<P>(S(5 + Q));
+  }
+  if (ALL || nd.any(T_RESIST | T_LORENTZ)) J = c.template ddn<P>(S(5 + Q)) - c.template ddn<Q>(S(5 + P));
+  if (ALL || nd.any(T_VISC | T_ADV)) flux_cot<C>(c, Wt, g1, g2);
   T uPb = T(0), uQb = T(0), pPb = T(0), pQb = T(0), bPb = T(0), bQb = T(0), Jb = T(0), Sb = T(0), rb = T(0),
     nb = T(0);
   if (visc) {
@@ -538,7 +666,8 @@ __device__ __forceinline__ void edge_back(const Cell<T, W>& c, const VK<T>& K, c
     pQb = -uP * g2;
     uPb = -pQ * g2;
   }
-  const T Eb = c.template dupT<P>(Wt(5 + Q)) - c.template dupT<Q>(Wt(5 + P));
+  T Eb = T(0);
+  if (ALL || nd.any(T_INDUCT | T_RESIST)) Eb = c.template dupT<P>(Wt(5 + Q)) - c.template dupT<Q>(Wt(5 + P));
   if (ind) {
     uPb -= bQ * Eb;
     bQb -= uP * Eb;
@@ -558,15 +687,22 @@ __device__ __forceinline__ void edge_back(const Cell<T, W>& c, const VK<T>& K, c
     bPb += J * l2;
   }
   auto put = [&](int q, T v) { c.st(A(VA_EDGE + C * EQ_COUNT + q), v); };
-  put(EQ_UAB, uPb);
-  put(EQ_UBA, uQb);
-  put(EQ_PAB, pPb);
-  put(EQ_PBA, pQb);
-  put(EQ_BAB, bPb);
-  put(EQ_BBA, bQb);
-  put(EQ_J, Jb);
-  put(EQ_RHO, rb);
-  put(EQ_LNU, E.nu * nb);
+  if (ALL || nd.any(T_ADV | T_INDUCT)) {
+    put(EQ_UAB, uPb);
+    put(EQ_UBA, uQb);
+  }
+  if (ALL || nd.any(T_ADV)) {
+    put(EQ_PAB, pPb);
+    put(EQ_PBA, pQb);
+  }
+  if (ALL || nd.any(T_INDUCT | T_LORENTZ)) {
+    put(EQ_BAB, bPb);
+    put(EQ_BBA, bQb);
+  }
+  if (ALL || nd.any(T_RESIST | T_LORENTZ)) put(EQ_J, Jb);
+  if (ALL || nd.any(T_VISC)) put(EQ_RHO, rb);
+  if (ALL || nd.enu()) put(EQ_LNU, E.nu * nb);
+  if (!(ALL || nd.shear())) return;
   const T hs = T(0.5) * Sb;
   if (order2(K)) {
     const bool r = (unsigned)c.ld(A(VA_RGF)) & (2u << C);
@@ -581,22 +717,23 @@ __device__ __forceinline__ void edge_back(const Cell<T, W>& c, const VK<T>& K, c
 // dn_a(nu) dn_a(e_m) ddn_a(ln e_m), backwards; with T_LNP the pressure
 // gradient exp(dn_a ln P) ddn_a ln P too (the plane mean of eq. pressure
 // drops out of the product and of its derivative).
-template <int AX, class T, bool W, class F, class G, class H>
-__device__ __forceinline__ void face_back(const Cell<T, W>& c, const VK<T>& K, const F& A, const G& Wt, const H& S) {
+template <bool ALL, int AX, class T, bool W, class F, class G, class H>
+__device__ __forceinline__ void face_back(const Cell<T, W>& c, const VArgs<T>& K, const Need& nd, const F& A, const G& Wt,
+                                          const H& S) {
   const Phys<T>& ph = K.ph;
   const T Hb = c.template dupT<AX>(Wt(4));
   T xe = T(0), uf = T(0), rf = T(0), xn = T(0), xm = T(0), dl = T(0);
-  if (ph.terms & T_ADV) {
+  if (nd.tm & T_ADV) {
     xe = -(c.ld(A(VA_U + AX)) * Hb);
     uf = -(c.template dn<AX>(S(4)) * Hb);
   }
-  if (ph.terms & T_EDIFF) {
+  if (nd.tm & T_EDIFF) {
     const T l = (W && AX == Z && c.b.stretched) ? c.plane(ZJ_LZF) : T(c.b.lv[AX]);
     const T kr = ph.nuE * c.ld(A(VA_R + AX));
     const T ln = l * c.template dn<AX>(A(VA_NT));
     const T em = c.template dn<AX>(A(VA_EM));
     T dv = c.template ddn<AX>(A(VA_LEM));
-    if (AX == Z && (ph.terms & T_EDIFFAV)) {
+    if (AX == Z && (nd.tm & T_EDIFFAV)) {
       // ln <e_m> of the offset's plane
       const double* pm = K.pm + c.b.poff;
       dv -= c.template op<Z, 1, 0>([&](unsigned f) { return T(log(T(pm[(c.o + f) / c.sz]))); });
@@ -606,56 +743,63 @@ __device__ __forceinline__ void face_back(const Cell<T, W>& c, const VK<T>& K, c
     xm = kr * ln * dv * Hb;
     dl = kr * ln * em * Hb;
   }
-  c.st(A(VA_XE + AX), xe);
-  c.st(A(VA_UF + AX), uf);
-  c.st(A(VA_RF + AX), rf);
-  c.st(A(VA_XNT + AX), xn);
-  c.st(A(VA_XEM + AX), xm);
-  c.st(A(VA_DLEM + AX), dl);
-  if ((ph.terms & T_PRES) && (ph.terms & T_LNP)) {
+  if (ALL || nd.any(T_ADV)) {
+    c.st(A(VA_XE + AX), xe);
+    c.st(A(VA_UF + AX), uf);
+  }
+  if (ALL || nd.any(T_EDIFF)) {
+    c.st(A(VA_RF + AX), rf);
+    c.st(A(VA_XNT + AX), xn);
+    c.st(A(VA_XEM + AX), xm);
+    c.st(A(VA_DLEM + AX), dl);
+  }
+  if (nd.lnp()) {
     const T gb = -c.ld(Wt(1 + AX)) * exp(c.template dn<AX>(A(VA_LNP)));
     c.st(A(VA_QI + AX), gb * c.template ddn<AX>(A(VA_LNP)));
     c.st(A(VA_QD + AX), gb);
   }
 }
 
-// Edges (blockIdx.y 0..2, the direction) and faces (3..5, the normal).
-VJP_KERNEL_WAVES(5) k_edge_face(VK<T> K) {
+// Edges (roles 0..2, the direction) and faces (3..5, the normal); the launch
+// takes the roles from `role` on.
+VJP_KERNEL_WAVES(5) k_edge_face(VK<T, ALL> K, int role) {
   VJP_CELL
-  switch (blockIdx.y) {
-    case 0: edge_back<X>(c, K, A, Wt, S); break;
-    case 1: edge_back<Y>(c, K, A, Wt, S); break;
-    case 2: edge_back<Z>(c, K, A, Wt, S); break;
-    case 3: face_back<X>(c, K, A, Wt, S); break;
-    case 4: face_back<Y>(c, K, A, Wt, S); break;
-    default: face_back<Z>(c, K, A, Wt, S); break;
+  switch (role + (int)blockIdx.y) {
+    case 0: edge_back<ALL, X>(c, K, nd, A, Wt, S); break;
+    case 1: edge_back<ALL, Y>(c, K, nd, A, Wt, S); break;
+    case 2: edge_back<ALL, Z>(c, K, nd, A, Wt, S); break;
+    case 3: face_back<ALL, X>(c, K, nd, A, Wt, S); break;
+    case 4: face_back<ALL, Y>(c, K, nd, A, Wt, S); break;
+    default: face_back<ALL, Z>(c, K, nd, A, Wt, S); break;
   }
 }
 
 // The edges' ln nu gathered along their second axis, and with the optional
 // terms the cotangents of div B and of the plane means' log.
-VJP_KERNEL k_lines_back(VK<T> K) {
+VJP_KERNEL k_lines_back(VK<T, ALL> K) {
   VJP_CELL
   auto Eq = [&](int e, int q) { return A(VA_EDGE + e * EQ_COUNT + q); };
-  c.st(A(VA_XLB), c.template dnT<Y>(Eq(Z, EQ_LNU)) + c.template dnT<Z>(Eq(Y, EQ_LNU)));
-  c.st(A(VA_YLB), c.template dnT<Z>(Eq(X, EQ_LNU)));
+  if (ALL || nd.enu()) {
+    c.st(A(VA_XLB), c.template dnT<Y>(Eq(Z, EQ_LNU)) + c.template dnT<Z>(Eq(Y, EQ_LNU)));
+    c.st(A(VA_YLB), c.template dnT<Z>(Eq(X, EQ_LNU)));
+  }
   if ((tm & T_DIVB) && K.dt > 0.0) {
     const T kd = T(K.c_divb / K.dt * b.hmin) * T(b.hmin);
     c.st(A(VA_DVB), kd * (c.template ddnT<X>(Wt(5)) + c.template ddnT<Y>(Wt(6)) + c.template ddnT<Z>(Wt(7))));
   }
-  if ((tm & T_EDIFF) && (tm & T_EDIFFAV)) c.st(A(VA_EDX), c.template ddnT<Z>(A(VA_DLEM + Z)));
+  if (nd.ediffav()) c.st(A(VA_EDX), c.template ddnT<Z>(A(VA_DLEM + Z)));
 }
 
 // Cotangent of a centre stress component: momentum flux and heating, or the
 // quenching's transpose.
 template <int AX, class T, bool W, class F, class G>
-__device__ __forceinline__ T taub_centre(const Cell<T, W>& c, const VK<T>& K, const F& A, const G& Wt, T vs, T we) {
+__device__ __forceinline__ T taub_centre(const Cell<T, W>& c, const VArgs<T>& K, const F& A, const G& Wt, T vs, T we) {
   if (quenched(K)) return c.ld(A(VA_TB + 3 + AX));
   return c.template ddnT<AX>(Wt(1 + AX)) + vs * we;
 }
 
 // <nu>: from the centre stress, the faces and the edges' logs.
-VJP_KERNEL k_nu_back(VK<T> K) {
+VJP_KERNEL k_nu_back(VK<T, ALL> K) {
   VJP_CELL
   const T nt = c.ld(A(VA_NT));
   T nb = T(0);
@@ -667,14 +811,15 @@ VJP_KERNEL k_nu_back(VK<T> K) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) nb += rho * len_c(c, a) * (E.vs[a] + K.ph.c1 * E.vD) * tb[a];
   }
-  nb += c.template dnT<X>(A(VA_XNT)) + c.template dnT<Y>(A(VA_XNT + 1)) + c.template dnT<Z>(A(VA_XNT + 2));
-  nb += (c.template dnT<X>(A(VA_XLB)) + c.template dnT<Y>(A(VA_YLB))) / nt;
+  if (ALL || nd.any(T_EDIFF))
+    nb += c.template dnT<X>(A(VA_XNT)) + c.template dnT<Y>(A(VA_XNT + 1)) + c.template dnT<Z>(A(VA_XNT + 2));
+  if (ALL || nd.enu()) nb += (c.template dnT<X>(A(VA_XLB)) + c.template dnT<Y>(A(VA_YLB))) / nt;
   c.st(A(VA_NTB), nt > T(1e-30) ? nb : T(0));
 }
 
 // Transpose of the three-cell means: on a wall axis output q averages over
 // 2 cells at an end, else 3.
-VJP_KERNEL k_mean_back(VK<T> K) {
+VJP_KERNEL k_mean_back(VK<T, ALL> K) {
   VJP_CELL
   const T* a = A(VA_NTB);
   const int N = b.nzt;
@@ -691,16 +836,24 @@ VJP_KERNEL k_mean_back(VK<T> K) {
 
 // Centre: the stress, the diagonal momentum fluxes, -P div u and the
 // speed-like viscosity (mb: the cotangent of its first maximum), backwards.
-VJP_KERNEL_WAVES(5) k_centre_back(VK<T> K, int mb) {
+VJP_KERNEL_WAVES(5) k_centre_back(VK<T, ALL> K, int mb) {
   VJP_CELL
   const Phys<T>& ph = K.ph;
-  const Centre<T, W, decltype(A)> E(c, K, A);
-  const T rho = c.ld(S(0)), e = c.ld(S(4)), nt = c.ld(A(VA_NT)), we = c.ld(Wt(4));
+  const Centre<T, W, decltype(A)> E(c, K, A, ALL || nd.strain());
+  const T rho = c.ld(S(0)), e = c.ld(S(4)), nt = ALL || nd.any(T_VISC) ? c.ld(A(VA_NT)) : T(0), we = c.ld(Wt(4));
   const T P = ph.gamma1 * e;
   T Db = T(0), vDb = T(0), rb = T(0), Pb = T(0);
-  T vsb[3] = {}, sb[3] = {}, cp[3] = {}, cu[3] = {}, cb[3] = {};
-  T uc[3] = {c.template up<X>(A(VA_U)), c.template up<Y>(A(VA_U + 1)), c.template up<Z>(A(VA_U + 2))};
-  const T gf[3] = {c.template ddnT<X>(Wt(1)), c.template ddnT<Y>(Wt(2)), c.template ddnT<Z>(Wt(3))};
+  T vsb[3] = {}, sb[3] = {}, cp[3] = {}, cu[3] = {}, cb[3] = {}, uc[3] = {}, gf[3] = {};
+  if (ALL || nd.cu()) {
+    uc[0] = c.template up<X>(A(VA_U));
+    uc[1] = c.template up<Y>(A(VA_U + 1));
+    uc[2] = c.template up<Z>(A(VA_U + 2));
+  }
+  if (ALL || nd.any(T_VISC | T_ADV)) {
+    gf[0] = c.template ddnT<X>(Wt(1));
+    gf[1] = c.template ddnT<Y>(Wt(2));
+    gf[2] = c.template ddnT<Z>(Wt(3));
+  }
   if (tm & T_VISC) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -729,8 +882,8 @@ VJP_KERNEL_WAVES(5) k_centre_back(VK<T> K, int mb) {
     Pb -= E.D * we;
     Db -= P * we;
   }
-  if (!(ph.nu_const > T(0))) {
-    const T nb = c.template max3T<X>(A(VA_MX), A(mb));
+  if (ALL ? !nd.cst : nd.chain()) {
+    const T nb = c.template max3T<X>(A(VA_MX), An(mb));
     const T ub = vnorm3(uc[0], uc[1], uc[2]);
     const T wu = ub > T(0) ? ph.nu1 * nb / ub : T(0);
     const T bc[3] = {c.template up<X>(S(5)), c.template up<Y>(S(6)), c.template up<Z>(S(7))};
@@ -769,11 +922,11 @@ VJP_KERNEL_WAVES(5) k_centre_back(VK<T> K, int mb) {
       v6 += v2;
       v2 = T(0);
     }
-    c.st(A(VA_SD + a), v6);
+    if (ALL || nd.strain()) c.st(A(VA_SD + a), v6);
     if (order2(K)) c.st(A(VA_SD2 + a), v2);
-    c.st(A(VA_CP + a), cp[a]);
-    c.st(A(VA_CU + a), cu[a]);
-    c.st(A(VA_CB + a), cb[a]);
+    if (ALL || nd.any(T_ADV)) c.st(A(VA_CP + a), cp[a]);
+    if (ALL || nd.cu()) c.st(A(VA_CU + a), cu[a]);
+    if (ALL || nd.chain()) c.st(A(VA_CB + a), cb[a]);
   }
   T eb = ph.gamma1 * Pb;
   // Newtonian cooling (eq. NewtonCool, eq. rhocool): -(e - rho e_cool) / t
@@ -788,83 +941,102 @@ VJP_KERNEL_WAVES(5) k_centre_back(VK<T> K, int mb) {
     eb -= ph.inv_tcool * fac * we;
     rb += (ph.e_cool * fac - (e - rho * ph.e_cool) * dfac) * ph.inv_tcool * we;
   }
-  c.st(A(VA_RHOB), rb);
-  c.st(A(VA_EB), eb);
+  if (ALL || nd.rhob()) c.st(A(VA_RHOB), rb);
+  if (ALL || nd.eb()) c.st(A(VA_EB), eb);
 }
 
 // T_SMAG: the centre shear's cotangents back on the edges.
-VJP_KERNEL k_smag_back(VK<T> K) {
+VJP_KERNEL k_smag_back(VK<T, ALL> K) {
   VJP_CELL
   const int e = (int)blockIdx.y;
   const T v = e == X ? c.template iiT<Y, 1, Z, 1>(A(VA_SC))
                      : (e == Y ? c.template iiT<X, 1, Z, 1>(A(VA_SC + 1)) : c.template iiT<X, 1, Y, 1>(A(VA_SC + 2)));
-  T* h = A(VA_EDGE + e * EQ_COUNT + EQ_HS);
+  auto hs = [&](int edge) { return A(VA_EDGE + edge * EQ_COUNT + EQ_HS); };
+  T* h = e == X ? hs(X) : (e == Y ? hs(Y) : hs(Z));
   c.st(h, c.ld(h) + T(0.5) * v);
 }
 
 template <class T, bool W>
-__device__ __forceinline__ void add_to(const Cell<T, W>& c, const VK<T>& K, int v, T x) {
+__device__ __forceinline__ void add_to(const Cell<T, W>& c, const VArgs<T>& K, int v, T x) {
   T* g = K.g.p[v] + c.b.off;
   c.st(g, K.acc ? c.ld(g) + x : x);
 }
 
 // Component a of the velocity: every gather, then the momentum and the face
 // density it came from.
-template <int AX, class T, bool W, class F, class G>
-__device__ __forceinline__ void vel_back(const Cell<T, W>& c, const VK<T>& K, const F& A, const G& Wt) {
+template <bool ALL, int AX, class T, bool W, class F, class G>
+__device__ __forceinline__ void vel_back(const Cell<T, W>& c, const VArgs<T>& K, const Need& nd, const F& A, const G& Wt) {
   constexpr int B1 = (AX + 1) % 3, A2 = (AX + 2) % 3;   // edges along A2 (as P) and along B1 (as Q)
-  const unsigned tm = K.ph.terms;
   auto Eq = [&](int e, int q) { return A(VA_EDGE + e * EQ_COUNT + q); };
-  T ub = c.ld(A(VA_UF + AX)) + c.template dnT<B1>(Eq(A2, EQ_UAB)) + c.template ddnT<B1>(Eq(A2, EQ_HS)) +
-         c.template dnT<A2>(Eq(B1, EQ_UBA)) + c.template ddnT<A2>(Eq(B1, EQ_HS)) + c.template upT<AX>(A(VA_CU + AX)) +
-         c.template dupT<AX>(A(VA_SD + AX));
+  T ub = T(0), pb = T(0), rf = T(0);
+  const bool ui = ALL || nd.any(T_ADV | T_INDUCT);
+  if (ALL || nd.any(T_ADV)) ub += c.ld(A(VA_UF + AX));
+  if (ui) ub += c.template dnT<B1>(Eq(A2, EQ_UAB));
+  if (ALL || nd.shear()) ub += c.template ddnT<B1>(Eq(A2, EQ_HS));
+  if (ui) ub += c.template dnT<A2>(Eq(B1, EQ_UBA));
+  if (ALL || nd.shear()) ub += c.template ddnT<A2>(Eq(B1, EQ_HS));
+  if (ALL || nd.cu()) ub += c.template upT<AX>(A(VA_CU + AX));
+  if (ALL || nd.strain()) ub += c.template dupT<AX>(A(VA_SD + AX));
   if (order2(K))
     ub += c.template d2nT<B1>(A(VA_HS2 + A2)) + c.template d2nT<A2>(A(VA_HS2 + B1)) +
           c.template d2uT<AX>(A(VA_SD2 + AX));
-  T pb = c.template dnT<B1>(Eq(A2, EQ_PAB)) + c.template dnT<A2>(Eq(B1, EQ_PBA)) + c.template upT<AX>(A(VA_CP + AX));
-  if (tm & T_CONT) pb -= c.template dupT<AX>(Wt(0));
-  if (tm & T_CORI) {
+  if (ALL || nd.any(T_ADV))
+    pb += c.template dnT<B1>(Eq(A2, EQ_PAB)) + c.template dnT<A2>(Eq(B1, EQ_PBA)) + c.template upT<AX>(A(VA_CP + AX));
+  if (nd.tm & T_CONT) pb -= c.template dupT<AX>(Wt(0));
+  if (nd.tm & T_CORI) {
     // p_AX drives dp_P and dp_Q (P, Q the next axes): -2 Omega x p
     pb += K.ph.cor2[A2] * c.template iiT<AX, 1, B1, 0>(Wt(1 + B1)) * T(-1);
     pb += K.ph.cor2[B1] * c.template iiT<AX, 1, A2, 0>(Wt(1 + A2));
   }
-  const T r = c.ld(A(VA_R + AX));
-  const T q = ub / r;
-  T rb = c.ld(A(VA_RF + AX)) - q * c.ld(A(VA_U + AX));
-  if constexpr (AX == X) rb += c.template dnT<Y>(Eq(Z, EQ_RHO)) + c.template dnT<Z>(Eq(Y, EQ_RHO));
-  if constexpr (AX == Y) rb += c.template dnT<Z>(Eq(X, EQ_RHO));
-  c.st(A(VA_RB + AX), rb);
-  add_to(c, K, 1 + AX, pb + q);
+  if (ALL || nd.faces()) {
+    const T r = c.ld(A(VA_R + AX));
+    const T q = ub / r;
+    if (ALL || nd.any(T_EDIFF)) rf = c.ld(A(VA_RF + AX));
+    T rb = rf - q * c.ld(A(VA_U + AX));
+    if (ALL || nd.any(T_VISC)) {
+      if constexpr (AX == X) rb += c.template dnT<Y>(Eq(Z, EQ_RHO)) + c.template dnT<Z>(Eq(Y, EQ_RHO));
+      if constexpr (AX == Y) rb += c.template dnT<Z>(Eq(X, EQ_RHO));
+    }
+    c.st(A(VA_RB + AX), rb);
+    pb += q;
+  }
+  add_to(c, K, 1 + AX, pb);
 }
-template <int AX, class T, bool W, class F>
-__device__ __forceinline__ void field_back(const Cell<T, W>& c, const VK<T>& K, const F& A) {
+template <bool ALL, int AX, class T, bool W, class F>
+__device__ __forceinline__ void field_back(const Cell<T, W>& c, const VArgs<T>& K, const Need& nd, const F& A) {
   constexpr int B1 = (AX + 1) % 3, A2 = (AX + 2) % 3;
   auto Eq = [&](int e, int q) { return A(VA_EDGE + e * EQ_COUNT + q); };
-  T v = c.template dnT<B1>(Eq(A2, EQ_BAB)) - c.template ddnT<B1>(Eq(A2, EQ_J)) + c.template dnT<A2>(Eq(B1, EQ_BBA)) +
-        c.template ddnT<A2>(Eq(B1, EQ_J)) + c.template upT<AX>(A(VA_CB + AX));
+  T v = T(0);
+  const bool bq = ALL || nd.any(T_INDUCT | T_LORENTZ), jq = ALL || nd.any(T_RESIST | T_LORENTZ);
+  if (bq) v += c.template dnT<B1>(Eq(A2, EQ_BAB));
+  if (jq) v -= c.template ddnT<B1>(Eq(A2, EQ_J));
+  if (bq) v += c.template dnT<A2>(Eq(B1, EQ_BBA));
+  if (jq) v += c.template ddnT<A2>(Eq(B1, EQ_J));
+  if (ALL || nd.chain()) v += c.template upT<AX>(A(VA_CB + AX));
   if ((K.ph.terms & T_DIVB) && K.dt > 0.0) v += c.template dupT<AX>(A(VA_DVB));
   add_to(c, K, 5 + AX, v);
 }
 // blockIdx.y 0..2 the velocities, 3..5 the magnetic field.
-VJP_KERNEL_WAVES(6) k_vector_back(VK<T> K) {
+VJP_KERNEL_WAVES(6) k_vector_back(VK<T, ALL> K) {
   VJP_CELL
   switch (blockIdx.y) {
-    case 0: vel_back<X>(c, K, A, Wt); break;
-    case 1: vel_back<Y>(c, K, A, Wt); break;
-    case 2: vel_back<Z>(c, K, A, Wt); break;
-    case 3: field_back<X>(c, K, A); break;
-    case 4: field_back<Y>(c, K, A); break;
-    default: field_back<Z>(c, K, A); break;
+    case 0: vel_back<ALL, X>(c, K, nd, A, Wt); break;
+    case 1: vel_back<ALL, Y>(c, K, nd, A, Wt); break;
+    case 2: vel_back<ALL, Z>(c, K, nd, A, Wt); break;
+    case 3: field_back<ALL, X>(c, K, nd, A); break;
+    case 4: field_back<ALL, Y>(c, K, nd, A); break;
+    default: field_back<ALL, Z>(c, K, nd, A); break;
   }
 }
 
 // e_m, the pressure gradient and gravity, then e and rho.
-VJP_KERNEL k_scalar_back(VK<T> K) {
+VJP_KERNEL k_scalar_back(VK<T, ALL> K) {
   VJP_CELL
   const Phys<T>& ph = K.ph;
-  const T rho = c.ld(S(0)), em = c.ld(A(VA_EM));
-  T eb = c.ld(A(VA_EB)) + c.template dnT<X>(A(VA_XE)) + c.template dnT<Y>(A(VA_XE + 1)) +
-         c.template dnT<Z>(A(VA_XE + 2));
+  T eb = T(0), rb = T(0);
+  if (ALL || nd.eb()) eb += c.ld(A(VA_EB));
+  if (ALL || nd.any(T_ADV))
+    eb = eb + c.template dnT<X>(A(VA_XE)) + c.template dnT<Y>(A(VA_XE + 1)) + c.template dnT<Z>(A(VA_XE + 2));
   if (tm & T_PRES) {
     if (tm & T_LNP)
       eb += (c.template dnT<X>(A(VA_QI)) + c.template ddnT<X>(A(VA_QD)) + c.template dnT<Y>(A(VA_QI + 1)) +
@@ -873,10 +1045,12 @@ VJP_KERNEL k_scalar_back(VK<T> K) {
     else
       eb -= ph.gamma1 * (c.template ddnT<X>(Wt(1)) + c.template ddnT<Y>(Wt(2)) + c.template ddnT<Z>(Wt(3)));
   }
-  T rb = c.ld(A(VA_RHOB)) + c.template dnT<X>(A(VA_RB)) + c.template dnT<Y>(A(VA_RB + 1)) +
-         c.template dnT<Z>(A(VA_RB + 2));
+  if (ALL || nd.rhob()) rb += c.ld(A(VA_RHOB));
+  if (ALL || nd.faces())
+    rb = rb + c.template dnT<X>(A(VA_RB)) + c.template dnT<Y>(A(VA_RB + 1)) + c.template dnT<Z>(A(VA_RB + 2));
   if (tm & T_GRAV) rb -= ph.gz * c.template dnT<Z>(Wt(3));
   if (tm & T_EDIFF) {
+    const T rho = c.ld(S(0)), em = c.ld(A(VA_EM));
     T mb = c.template dnT<X>(A(VA_XEM)) + c.template dnT<Y>(A(VA_XEM + 1)) + c.template dnT<Z>(A(VA_XEM + 2)) +
            (c.template ddnT<X>(A(VA_DLEM)) + c.template ddnT<Y>(A(VA_DLEM + 1)) + c.template ddnT<Z>(A(VA_DLEM + 2))) /
                em;
@@ -939,59 +1113,62 @@ __global__ __launch_bounds__(kBlock) void k_axpby8(const BoxDev* boxes, const Bl
   }
 }
 
-template <class T, bool W>
-void run(const VjpLaunch& L, const VK<T>& K) {
-  const unsigned tm = K.ph.terms;
+template <class T, bool W, bool ALL>
+void run(const VjpLaunch& L, const VK<T, ALL>& K) {
   const int g = 8 * ((L.nblk + 7) / 8);
   const dim3 blk(kBlock);
-  auto go = [&](void (*kern)(VK<T>), int roles) { hipLaunchKernelGGL(kern, dim3(g, roles), blk, 0, L.stream, K); };
+  auto go = [&](auto* kern, int roles, auto... args) {
+    hipLaunchKernelGGL(kern, dim3(g, roles), blk, 0, L.stream, K, args...);
+  };
+  auto slot = [&](int id) { return K.slot(id); };
   auto max1 = [&](int ax, int src, int dst) {
-    auto* kern = ax == X ? k_max1<T, W, X> : (ax == Y ? k_max1<T, W, Y> : k_max1<T, W, Z>);
-    hipLaunchKernelGGL(kern, dim3(g), blk, 0, L.stream, K, src, dst);
+    auto* kern = ax == X ? k_max1<T, W, ALL, X> : (ax == Y ? k_max1<T, W, ALL, Y> : k_max1<T, W, ALL, Z>);
+    go(kern, 1, slot(src), slot(dst));
   };
   auto max1T = [&](int ax, int prim, int yb, int dst, int comps) {
-    auto* kern = ax == X ? k_max1T<T, W, X> : (ax == Y ? k_max1T<T, W, Y> : k_max1T<T, W, Z>);
-    hipLaunchKernelGGL(kern, dim3(g, comps), blk, 0, L.stream, K, prim, yb, dst);
+    auto* kern = ax == X ? k_max1T<T, W, ALL, X> : (ax == Y ? k_max1T<T, W, ALL, Y> : k_max1T<T, W, ALL, Z>);
+    go(kern, comps, slot(prim), slot(yb), slot(dst));
   };
   auto plane_mean = [&](int id, double* pm) {
     hipLaunchKernelGGL(k_plane_mean<T>, dim3(L.nplanes), dim3(kPlaneBlock), 0, L.stream, L.boxes, L.nbox,
-                       (const T*)(K.base + (long long)id * K.stride), pm);
+                       (const T*)(K.base + (long long)slot(id) * K.stride), pm);
   };
-  const bool visc = tm & T_VISC, cst = K.ph.nu_const > T(0);
-  const bool av = (tm & T_EDIFF) && (tm & T_EDIFFAV);
-  go(k_prim<T, W>, 1);
-  if (av) plane_mean(VA_EM, L.pm);
-  if (visc && (tm & T_ORDER2)) {
-    go(k_rough<T, W>, 1);
-    go(k_rough_flags<T, W>, 1);
+  const Need nd(K.ph);
+  const bool chain = ALL ? !nd.cst : nd.chain(), smag = chain && nd.any(T_SMAG);
+  const bool edges = ALL || nd.edges(), fluxes = ALL || nd.fluxes();
+  if (ALL || nd.faces() || nd.heat()) go(k_prim<T, W, ALL>, 1);
+  if (nd.ediffav()) plane_mean(VA_EM, L.pm);
+  if (nd.order2()) {
+    go(k_rough<T, W, ALL>, 1);
+    go(k_rough_flags<T, W, ALL>, 1);
   }
-  if (!cst) {
-    if (tm & T_SMAG) go(k_shear<T, W>, 3);
-    go(k_nus<T, W>, 1);
-    if (tm & T_MAX5)
+  if (chain) {
+    if (smag) go(k_shear<T, W, ALL>, 3);
+    go(k_nus<T, W, ALL>, 1);
+    if (K.nmax == 6)
       for (int m = 0; m < 6; ++m) max1(m / 2, mx_id(m), mx_id(m + 1));
     else
-      go(k_max3<T, W>, 1);
+      go(k_max3<T, W, ALL>, 1);
   }
-  go(k_mean<T, W>, 1);
-  go(k_lines<T, W>, 1);
-  if (visc && (tm & T_QUENCH)) {
-    go(k_tau<T, W>, 4);
-    go(k_quench<T, W>, 6);
-    go(k_quench_max<T, W>, 6);
-    go(k_taub<T, W>, 4);
+  if (ALL || nd.nu()) go(k_mean<T, W, ALL>, 1, slot(mx_id(K.nmax)));
+  if (ALL || nd.enu()) go(k_lines<T, W, ALL>, 1);
+  if (nd.quench()) {
+    go(k_tau<T, W, ALL>, 4);
+    go(k_quench<T, W, ALL>, 6);
+    go(k_quench_max<T, W, ALL>, 6);
+    go(k_taub<T, W, ALL>, 4);
     max1T(Z, VA_Q2, VA_QB0, VA_QB1, 6);
     max1T(Y, VA_Q1, VA_QB1, VA_QB0, 6);
-    go(k_quenchT<T, W>, 6);
-    go(k_quenchT2<T, W>, 6);
+    go(k_quenchT<T, W, ALL>, 6);
+    go(k_quenchT2<T, W, ALL>, 6);
   }
-  go(k_edge_face<T, W>, 6);
-  go(k_lines_back<T, W>, 1);
-  if (av) plane_mean(VA_EDX, L.pm + L.nplanes);
+  if (edges || fluxes) go(k_edge_face<T, W, ALL>, edges && fluxes ? 6 : 3, edges ? 0 : 3);
+  if (ALL || nd.enu() || nd.ediffav() || (nd.any(T_DIVB) && K.dt > 0.0)) go(k_lines_back<T, W, ALL>, 1);
+  if (nd.ediffav()) plane_mean(VA_EDX, L.pm + L.nplanes);
   int mb = VA_MB0;
-  if (!cst) {
-    go(k_nu_back<T, W>, 1);
-    go(k_mean_back<T, W>, 1);
+  if (chain) {
+    go(k_nu_back<T, W, ALL>, 1);
+    go(k_mean_back<T, W, ALL>, 1);
     // back through the maxima but the first, which the centre pass takes
     for (int m = K.nmax - 1; m > 0; --m) {
       const int to = mb == VA_MB0 ? VA_MB1 : VA_MB0;
@@ -999,50 +1176,56 @@ void run(const VjpLaunch& L, const VK<T>& K) {
       mb = to;
     }
   }
-  hipLaunchKernelGGL((k_centre_back<T, W>), dim3(g), blk, 0, L.stream, K, mb);
-  if (!cst && (tm & T_SMAG)) go(k_smag_back<T, W>, 3);
-  go(k_vector_back<T, W>, 6);
-  go(k_scalar_back<T, W>, 1);
+  if (ALL || nd.centre()) go(k_centre_back<T, W, ALL>, 1, slot(mb));
+  if (smag) go(k_smag_back<T, W, ALL>, 3);
+  go(k_vector_back<T, W, ALL>, 6);
+  go(k_scalar_back<T, W, ALL>, 1);
 }
 
 }  // namespace
 
-int vjp_arrays(unsigned terms) {
-  int n = VA_CORE;
-  if (terms & T_MAX5) n = VA_LNP;
-  if (terms & T_LNP) n = VA_DVB;
-  if (terms & T_DIVB) n = VA_EDX;
-  if (terms & T_EDIFFAV) n = VA_SE;
-  if (terms & T_SMAG) n = VA_TAU;
-  if (terms & T_QUENCH) n = VA_RGH;
-  if (terms & T_ORDER2) n = VA_COUNT;
-  return n;
+template <class T> int vjp_arrays(const Phys<T>& ph) {
+  unsigned char at[VA_COUNT];
+  bool all;
+  return std::max(layout(Need(ph), at, all), kFillTmp);
 }
+template int vjp_arrays<float>(const Phys<float>&);
+template int vjp_arrays<double>(const Phys<double>&);
 
 template <class T>
 void vjp_rhs(const VjpLaunch& L, const Phys<T>& ph, double nu2, double c_smag, double c_divb, CP8<T> s, CP8<T> w,
              P8<T> g, bool acc, T* base, long long stride, double dt) {
-  VK<T> K;
-  K.boxes = L.boxes;
-  K.tab = L.tab;
-  K.nblk = L.nblk;
-  K.s = s;
-  K.w = w;
-  K.g = g;
-  K.base = base;
-  K.stride = stride;
-  K.zt = static_cast<const T*>(L.ztab);
-  K.pm = L.pm;
-  K.nplanes = L.nplanes;
-  K.ph = ph;
-  K.nu2 = nu2;
-  K.c_smag = c_smag;
-  K.c_divb = c_divb;
-  K.dt = dt;
-  K.acc = acc ? 1 : 0;
-  K.nmax = (ph.terms & T_MAX5) ? 6 : 3;
-  if (L.wall) run<T, true>(L, K);
-  else run<T, false>(L, K);
+  auto set = [&](VArgs<T>& K) {
+    K.boxes = L.boxes;
+    K.tab = L.tab;
+    K.nblk = L.nblk;
+    K.s = s;
+    K.w = w;
+    K.g = g;
+    K.base = base;
+    K.stride = stride;
+    K.zt = static_cast<const T*>(L.ztab);
+    K.pm = L.pm;
+    K.nplanes = L.nplanes;
+    K.ph = ph;
+    K.nu2 = nu2;
+    K.c_smag = c_smag;
+    K.c_divb = c_divb;
+    K.dt = dt;
+    K.acc = acc ? 1 : 0;
+    K.nmax = (ph.terms & T_MAX5) ? 6 : 3;
+  };
+  VK<T, true> every;
+  VK<T, false> lean;
+  bool all;
+  (void)layout(Need(ph), lean.at, all);
+  if (all) {
+    set(every);
+    L.wall ? run<T, true, true>(L, every) : run<T, false, true>(L, every);
+  } else {
+    set(lean);
+    L.wall ? run<T, true, false>(L, lean) : run<T, false, false>(L, lean);
+  }
 }
 
 template <class T> void vjp_axpby8(const VjpLaunch& L, P8<T> y, CP8<T> x, double a, double b, bool mask) {

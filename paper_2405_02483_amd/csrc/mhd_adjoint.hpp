@@ -22,12 +22,13 @@ struct VjpLaunch {
   int nghost_blk;
 };
 
-// Workspace arrays (of the packed field size) that vjp_rhs needs.
-int vjp_arrays(unsigned terms);
+// Workspace arrays (of the packed field size) that vjp_rhs needs with the
+// terms and constant coefficients of ph (6 at least, for vjp_fill).
+template <class T> int vjp_arrays(const Phys<T>& ph);
 
 // g[v] (+)= (dF/df_v)^T w at the state s (acc: added, else overwritten).  s,
 // w and g are packed field arrays, none overlapping another; base holds
-// vjp_arrays(terms) arrays `stride` elements apart.  dt: the step's (the
+// vjp_arrays(ph) arrays `stride` elements apart.  dt: the step's (the
 // div B diffusion's coefficient; 0 leaves that term out).  nu2, c_smag: the
 // coefficients before rounding to T (the lengths multiply them first).
 template <class T>

@@ -981,7 +981,7 @@ static void rhs_transpose(mhd_ctx* c, bool walls, CP8<T> s, CP8<T> w, P8<T> g, b
 // holds (and the transpose addresses a box with 32-bit offsets).
 template <class T> static T* adjoint_workspace(mhd_ctx* c, bool walls, int& rc) {
   const long long n = c->nelem;
-  const size_t narr = (size_t)vjp_arrays(c->p.terms) + 24 + (walls ? 16 : 0);
+  const size_t narr = (size_t)vjp_arrays(make_phys<T>(c->p)) + 24 + (walls ? 16 : 0);
   const size_t need = narr * (size_t)n * c->esize;
   rc = MHD_OK;
   for (const BoxDev& b : c->h_boxes)
@@ -1020,7 +1020,7 @@ static int do_adjoint(mhd_ctx* c, void* const fn[8], double dt, void* const gin[
   int rc = MHD_OK;
   T* base = adjoint_workspace<T>(c, walls, rc);
   if (!base) return rc;
-  T* rest = base + (long long)vjp_arrays(c->p.terms) * n;
+  T* rest = base + (long long)vjp_arrays(make_phys<T>(c->p)) * n;
   auto set8 = [&](int first) {
     P8<T> q;
     for (int v = 0; v < 8; ++v) q.p[v] = rest + (long long)(first + v) * n;
@@ -1084,7 +1084,7 @@ static int do_rhs_adjoint(mhd_ctx* c, void* const f[8], void* const wbar[8],
   int rc = MHD_OK;
   T* base = adjoint_workspace<T>(c, walls, rc);
   if (!base) return rc;
-  T* rest = base + (long long)vjp_arrays(c->p.terms) * n;
+  T* rest = base + (long long)vjp_arrays(make_phys<T>(c->p)) * n;
   const size_t bytes = (size_t)n * c->esize;
   const Launch L = make_launch(c);
   L.at(PASS_ADJOINT);
