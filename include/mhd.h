@@ -356,14 +356,15 @@ int mhd_get_final_tile(const mhd_ctx* ctx, int32_t* tile);
 /* Autotuner: times reps RK stages of the kind a step repeats (the right-hand
  * side of f with the stage update: dU read and written, the next state
  * written to scratch; after one mhd_rhs(f, dfdt) as warm-up) in every tile
- * shape and launch mode, in three rounds over all of them, keeps the
- * fastest (each candidate's best round) and, if ms is not NULL, writes the
- * milliseconds per stage to ms[2 * tile + persistent] (12 entries; 0 for a
- * shape not built for the context's dtype).  Then, with that shape (and any
- * within 2 % of it) for the other passes, times every shape for pass F alone
- * in both modes (three rounds again), and keeps the fastest combination if
- * it beats the uniform launch by more than 1 % (mhd_get_launch,
- * mhd_get_final_tile).  dfdt is
+ * shape and launch mode, in three rounds over all of them (each candidate's
+ * best round counts).  Then, for the launches within 2 % of the fastest (five
+ * at most), times every other shape for pass F alone, and keeps the fastest
+ * combination if it beats the uniform launches by more than 1 %
+ * (mhd_get_launch, mhd_get_final_tile), else the fastest uniform launch.  If
+ * ms is not NULL, writes the milliseconds per stage to
+ * ms[2 * tile + persistent] (12 entries; 0 for a shape not built for the
+ * context's dtype; the kept launch's with its shape of pass F, so that it is
+ * the smallest).  dfdt is
  * overwritten; with walls the ghost planes of f are filled.  Allocates 8
  * fields of scratch for the call (MHD_ENOMEM).  Waits for the stream.      */
 int mhd_autotune(mhd_ctx* ctx, void* const f[8], void* const dfdt[8], int32_t reps,

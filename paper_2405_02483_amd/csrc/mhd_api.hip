@@ -18,6 +18,7 @@
 #include "mhd_clean.hpp"
 #include "mhd_kernels.hpp"
 #include "mhd_adjoint.hpp"
+#include "mhd_tune.hpp"
 #include "mhd_zmarch_api.hpp"
 
 using namespace smhd;
@@ -515,6 +516,17 @@ static void start_tiles(const mhd_ctx* c, int& tile, int& ftile) {
     if (big && columns(ZTILE_64x8) <= 1.1 * columns(tile)) tile = ZTILE_64x8;
     ftile = tile;
   }
+}
+
+// The shape of the passes and that of pass F; only tables that change are
+// made again.
+static int set_tiles(mhd_ctx* c, int tile, int ftile) {
+  if (tile != c->tile) {
+    const int rc = upload_items(c, tile, 0, ZC_F);
+    if (rc != MHD_OK) return rc;
+    c->tile = tile;
+  }
+  return ftile == c->ftile ? MHD_OK : set_ftile(c, ftile);
 }
 
 template <class T> static P8<T> p8(void* const f[8]) {
@@ -1399,96 +1411,44 @@ int mhd_autotune(mhd_ctx* c, void* const f[8], void* const dfdt[8], int32_t reps
     per = (double)el / reps;
     return r0;
   };
-  // every pass in one shape and mode.  Each candidate is timed in
-  // kRounds rounds over all candidates and keeps its fastest: a launch's
-  // time varies from call to call by several percent (the memory system's
-  // state), more than some candidates differ.
-  constexpr int kRounds = 3;
   double tm[ZTILE_COUNT][2];
-  for (int t = 0; t < ZTILE_COUNT; ++t) tm[t][0] = tm[t][1] = -1.0;
-  for (int round = 0; round < kRounds && rc == MHD_OK; ++round)
-    for (int t = 0; t < ZTILE_COUNT && rc == MHD_OK; ++t)
-      for (int m = 0; m < 2 && rc == MHD_OK; ++m) {
-        if (!ztile_ok(t, c->esize)) continue;
-        if ((rc = mhd_set_launch(c, t, m)) != MHD_OK) break;
-        double per = 0.0;
-        rc = timed(per);
-        if (rc == MHD_OK && (tm[t][m] < 0.0 || per < tm[t][m])) tm[t][m] = per;
-      }
-  double best = -1.0;
-  int bt = c->tile, bp = c->persistent;
-  for (int t = 0; t < ZTILE_COUNT; ++t)
-    for (int m = 0; m < 2; ++m) {
-      if (ms) ms[t * 2 + m] = tm[t][m] > 0.0 ? tm[t][m] : 0.0;
-      if (tm[t][m] > 0.0 && (best < 0.0 || tm[t][m] < best)) {
-        best = tm[t][m];
-        bt = t;
-        bp = m;
-      }
-    }
-  // then pass F's own shape, with the others' shape fixed, in both modes
-  // (fastest of the rounds again), for the fastest shape and those within
-  // 2 % of it: a uniform launch can owe its place to pass F alone (512^3
-  // float64, ms per stage: 64x8 39.12 and 16x16 39.31 throughout, but 34.7
-  // with 16x16 and pass F in 64x8, while 64x8 has no better shape for F).  A
-  // change only if it is faster by more than the timing noise (1 %; the
-  // fastest of three rounds varies by about 0.1 %).
-  double tf[ZTILE_COUNT][2][ZTILE_COUNT];
-  bool near[ZTILE_COUNT];
-  for (int s = 0; s < ZTILE_COUNT; ++s) {
-    near[s] = s == bt;
-    for (int m = 0; m < 2; ++m) {
-      near[s] |= tm[s][m] > 0.0 && tm[s][m] < 1.02 * best;
-      for (int t = 0; t < ZTILE_COUNT; ++t) tf[s][m][t] = -1.0;
-    }
-  }
-  for (int round = 0; round < kRounds && rc == MHD_OK; ++round)
-    for (int s = 0; s < ZTILE_COUNT && rc == MHD_OK; ++s)
-      for (int m = 0; m < 2 && rc == MHD_OK && near[s]; ++m) {
-        if ((rc = mhd_set_launch(c, s, m)) != MHD_OK) break;
-        for (int t = 0; t < ZTILE_COUNT && rc == MHD_OK; ++t) {
-          if (!ztile_ok(t, c->esize)) continue;
-          if ((rc = set_ftile(c, t)) != MHD_OK) break;
-          double per = 0.0;
-          rc = timed(per);
-          if (rc == MHD_OK && (tf[s][m][t] < 0.0 || per < tf[s][m][t])) tf[s][m][t] = per;
-        }
-      }
-  int bs = bt, bm = bp, bf = bt;
+  for (int t = 0; t < ZTILE_COUNT; ++t) tm[t][0] = tm[t][1] = 0.0;
+  TuneChoice best{c->tile, c->persistent, c->ftile};
+  const int was = c->cells;
+  c->cells = 0;
+  rc = tune_march<ZTILE_COUNT>([&](int t) { return ztile_ok(t, c->esize); },
+                               [&](int t, int m, int f, double& per) {
+                                 c->persistent = m;
+                                 const int r = set_tiles(c, t, f);
+                                 return r != MHD_OK ? r : timed(per);
+                               },
+                               tm, best);
+  if (ms)
+    for (int t = 0; t < ZTILE_COUNT; ++t)
+      for (int m = 0; m < 2; ++m) ms[t * 2 + m] = tm[t][m];
   if (rc == MHD_OK) {
-    const double base = tf[bt][bp][bt];
-    for (int s = 0; s < ZTILE_COUNT; ++s)
-      for (int m = 0; m < 2; ++m)
-        for (int t = 0; t < ZTILE_COUNT; ++t)
-          if (tf[s][m][t] > 0.0 && tf[s][m][t] < 0.99 * base && tf[s][m][t] < tf[bs][bm][bf]) {
-            bs = s;
-            bm = m;
-            bf = t;
-          }
-    rc = mhd_set_launch(c, bs, bm);
-    if (rc == MHD_OK) rc = set_ftile(c, bf);
+    c->persistent = best.mode;
+    rc = set_tiles(c, best.tile, best.ftile);
   }
   // and the cell-parallel stage against the best of them
   bool cells = false;
   if (rc == MHD_OK && c->cells_ok) {
     double tc = -1.0;
     c->cells = 1;
-    for (int round = 0; round < kRounds && rc == MHD_OK; ++round) {
+    for (int round = 0; round < 3 && rc == MHD_OK; ++round) {
       double per = 0.0;
       rc = timed(per);
       if (rc == MHD_OK && (tc < 0.0 || per < tc)) tc = per;
     }
-    cells = rc == MHD_OK && tc < std::min(best, tf[bs][bm][bf]);
+    cells = rc == MHD_OK && tc < tm[best.tile][best.mode];
     c->cells = 0;
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   (void)hipFree(next);
   c->prof = prof;
-  if (rc != MHD_OK) return rc;
-  if ((rc = set_ftile(c, bf)) != MHD_OK) return rc;
-  c->cells = cells ? 1 : 0;
-  return MHD_OK;
+  c->cells = rc == MHD_OK ? (cells ? 1 : 0) : was;
+  return rc;
 }
 
 }  // extern "C"

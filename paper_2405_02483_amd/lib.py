@@ -465,7 +465,7 @@ class Context:
         """Times RK stages of f in every tile shape and launch mode and keeps
         the fastest (then, possibly, another shape for pass F alone:
         get_final_tile); returns {(tile, persistent): ms per stage} of the
-        uniform launches."""
+        uniform launches (the kept one's with pass F in its own shape)."""
         dfdt = dfdt if dfdt is not None else self.empty()
         ms = mhd_autotune(self.ctx, f, dfdt, reps, dtype=self.dtype, n=self.n)
         names = {v: k for k, v in TILES.items()}
