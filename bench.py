@@ -159,7 +159,7 @@ def _window(f_np, box, x0, y0, width):
 def run_gpu(size, dtype, steps, warmup, workload="stratified", tile=None, over=None,
             launch=None, window=None, state_kw=None, final_tile=None):
     """Times `steps` RK steps.  over: parameters replacing the workload's;
-    launch: a (tile, persistent, final-pass tile) to use instead of tuning;
+    launch: a (tile, persistent, final-pass tile, cells) to use instead of tuning;
     window: (x0, y0) of a column window: after the timing, one step of the
     initial state with its Courant dt, whose central columns are returned
     (with the window of the initial state and the dt) for the oracle."""
@@ -179,8 +179,11 @@ def run_gpu(size, dtype, steps, warmup, workload="stratified", tile=None, over=N
     del f_np
     tune = None
     if launch is not None:
+        start = ctx.get_cells()      # (not with every term)
         ctx.set_launch(launch[0], launch[1])
         ctx.set_final_tile(launch[2])
+        if launch[3] and start:
+            ctx.set_cells(1)
     elif tile is None:
         tune = ctx.autotune(f, reps=3)          # tile shape and launch mode
     else:
@@ -221,7 +224,7 @@ def run_gpu(size, dtype, steps, warmup, workload="stratified", tile=None, over=N
                             for t in ctx.box_view(f0, 0)])
         del f0
     launch = ctx.get_launch()
-    ftile = ctx.get_final_tile()
+    ftile, cells = ctx.get_final_tile(), ctx.get_cells()
     dt_last = ctx.last_dt()
     s_end = ctx.reductions(f)
     ctx.close()
@@ -230,7 +233,7 @@ def run_gpu(size, dtype, steps, warmup, workload="stratified", tile=None, over=N
     ms = (t1 - t0) * 1e3 / steps
     passes, stage_ms = stage_times(prof, steps)
     return dict(ms_per_step=ms, value=ncell * steps / (t1 - t0), stage_ms=stage_ms,
-                launch={"tile": launch[0], "persistent": launch[1], "final_pass_tile": ftile},
+                launch={"tile": launch[0], "persistent": launch[1], "final_pass_tile": ftile, "cells": cells},
                 autotune_ms_per_stage=None if tune is None else {
                     "%s/%s" % (k[0], "persistent" if k[1] else "grid"): round(v, 4)
                     for k, v in tune.items()},
@@ -554,7 +557,7 @@ def main():
                                      ("stretched", 0, {}, dict(stretch=STRETCH))):
             rsrc[name] = run_gpu(a.size, torch.float32, max(2, a.steps // 5), 1, a.workload,
                                  over=dict(over, terms=T_ALL | bit),
-                                 launch=(L["tile"], L["persistent"], L["final_pass_tile"]),
+                                 launch=(L["tile"], L["persistent"], L["final_pass_tile"], L["cells"]),
                                  state_kw=skw)
             log("f32 with %s: %.2f ms/step" % (name, rsrc[name]["ms_per_step"]))
     r64 = None

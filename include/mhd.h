@@ -328,11 +328,16 @@ int mhd_divb_clean(mhd_ctx* ctx, void* const f[8]);
 /* The dt of the last step taken with dt == 0 (waits for the stream).      */
 int mhd_last_dt(mhd_ctx* ctx, double* dt);
 
-/* Tile shape of the stage kernels: columns per workgroup, 0: 64x4,
+/* How a context runs its RK stages.  Workgroups march along z, each on a
+ * tile of columns (tile shapes and launch modes below), or, in small contexts
+ * (mhd_set_cells), one thread computes one cell.  Every way gives the same
+ * results, bit for bit.  mhd_init chooses from the boxes and the terms; the
+ * calls that set a tile or a launch mode ask for the march.
+ *
+ * Tile shape of the stage kernels: columns per workgroup, 0: 64x4,
  * 1: 32x8, 2: 16x16, 3: 16x8 (256 threads), 4: 64x8, 5: 32x16 (512
- * threads).  Any shape gives the same results (bit for bit); the default is
- * chosen by mhd_init from the boxes.  Other values: MHD_EINVAL.  Also sets
- * pass F to this shape (mhd_set_final_tile).                               */
+ * threads).  Other values: MHD_EINVAL.  Also sets pass F to this shape
+ * (mhd_set_final_tile), and the march (mhd_set_cells).                     */
 int mhd_set_tile(mhd_ctx* ctx, int32_t tile);
 
 /* Tile shape (as mhd_set_tile) and launch mode of the stage kernels.
@@ -340,18 +345,32 @@ int mhd_set_tile(mhd_ctx* ctx, int32_t tile);
  * persistent = 1: about one resident wave of workgroups, each taking work
  * items from a queue per XCD and from the other XCDs' queues once its own is
  * empty (load balance for ensembles of uneven boxes).  Results are the same
- * bit for bit in every tile shape and mode.  MHD_EINVAL on other values.   */
+ * bit for bit in every tile shape and mode.  MHD_EINVAL on other values.
+ * Sets the march (mhd_set_cells).                                          */
 int mhd_set_launch(mhd_ctx* ctx, int32_t tile, int32_t persistent);
 
-/* Current tile shape and launch mode.                                      */
+/* Current tile shape and launch mode of the march (also while the context
+ * runs one thread per cell: what mhd_set_cells(ctx, 0) would run).          */
 int mhd_get_launch(const mhd_ctx* ctx, int32_t* tile, int32_t* persistent);
 
 /* Tile shape of pass F alone (the divergences and the RK stage update), as
  * mhd_set_tile; mhd_set_tile and mhd_set_launch set it to their own shape.
- * Results are the same bit for bit.  MHD_EINVAL on other values.            */
+ * Results are the same bit for bit.  MHD_EINVAL on other values.  Sets the
+ * march (mhd_set_cells).                                                   */
 int mhd_set_final_tile(mhd_ctx* ctx, int32_t tile);
 int mhd_get_final_tile(const mhd_ctx* ctx, int32_t* tile);
 
+/* cells = 1: the stages run one thread per cell, 0: they march.  Possible
+ * for contexts without MHD_T_SMAG, MHD_T_QUENCH and MHD_T_ORDER2 of up to
+ * 1,000,000 cells (float32; 550,000 with walls) or 400,000 (float64), ghost
+ * planes included, which start with it; MHD_EUNSUPPORTED for others,
+ * MHD_EINVAL for other values.  mhd_set_tile, mhd_set_launch and
+ * mhd_set_final_tile set 0, mhd_autotune whichever is faster.  A launch is
+ * read with mhd_get_launch, mhd_get_final_tile and mhd_get_cells, and set
+ * again, on this or another context of the same boxes, with the three set
+ * calls in that order.                                                     */
+int mhd_set_cells(mhd_ctx* ctx, int32_t cells);
+int mhd_get_cells(const mhd_ctx* ctx, int32_t* cells);
 
 /* Autotuner: times reps RK stages of the kind a step repeats (the right-hand
  * side of f with the stage update: dU read and written, the next state
@@ -360,7 +379,9 @@ int mhd_get_final_tile(const mhd_ctx* ctx, int32_t* tile);
  * best round counts).  Then, for the launches within 2 % of the fastest (five
  * at most), times every other shape for pass F alone, and keeps the fastest
  * combination if it beats the uniform launches by more than 1 %
- * (mhd_get_launch, mhd_get_final_tile), else the fastest uniform launch.  If
+ * (mhd_get_launch, mhd_get_final_tile), else the fastest uniform launch.
+ * Where the context can, times one thread per cell too and keeps it if it is
+ * faster than any of them (mhd_get_cells).  If
  * ms is not NULL, writes the milliseconds per stage to
  * ms[2 * tile + persistent] (12 entries; 0 for a shape not built for the
  * context's dtype; the kept launch's with its shape of pass F, so that it is
@@ -371,7 +392,8 @@ int mhd_autotune(mhd_ctx* ctx, void* const f[8], void* const dfdt[8], int32_t re
                  double* ms);
 
 /* Timing of the library's own kernel passes, for performance measurement.
- * Pass ids (index into the arrays of mhd_profile_read):                    */
+ * Pass ids (index into the arrays of mhd_profile_read; one thread per cell
+ * books the quantities of Q and P together under MHD_PASS_EDGES):          */
 enum {
     MHD_PASS_PRIM = 0,      /* A1: u_z, div u, speed-like viscosity            */
     MHD_PASS_NUS = 1,       /* (unused)                                        */

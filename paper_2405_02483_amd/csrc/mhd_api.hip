@@ -168,7 +168,8 @@ static double divb_limit(double dx, double dy, double dz) {
   return rk3_real_limit() / (kh * kh * s);
 }
 // Stage workspace arrays: 34, 6 more for the quenched stress, and 2 more
-// for the second-order switch.
+// for the second-order switch; 10 more than the 34 for one thread per cell
+// (which runs without those two).
 static int work_arrays(const mhd_params& p, bool cells = false) {
   if (cells) return WC_COUNT;
   if (p.terms & MHD_T_ORDER2) return WS_COUNT_ALL;
@@ -1368,6 +1369,20 @@ int mhd_set_final_tile(mhd_ctx* c, int32_t tile) {
 int mhd_get_final_tile(const mhd_ctx* c, int32_t* tile) {
   if (!c || !tile) return MHD_EINVAL;
   *tile = c->ftile;
+  return MHD_OK;
+}
+
+int mhd_set_cells(mhd_ctx* c, int32_t cells) {
+  if (!c) return fail(nullptr, MHD_EINVAL, "ctx is NULL");
+  if (cells != 0 && cells != 1) return fail(c, MHD_EINVAL, "cells must be 0 or 1");
+  if (cells && !c->cells_ok) return fail(c, MHD_EUNSUPPORTED, "this context does not run one thread per cell (terms or size)");
+  c->cells = cells;
+  return MHD_OK;
+}
+
+int mhd_get_cells(const mhd_ctx* c, int32_t* cells) {
+  if (!c || !cells) return MHD_EINVAL;
+  *cells = c->cells;
   return MHD_OK;
 }
 

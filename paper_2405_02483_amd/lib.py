@@ -22,7 +22,7 @@ __all__ = [
     "mhd_box_offset", "mhd_rhs", "mhd_rhs_noalloc", "mhd_step", "mhd_step_adjoint", "mhd_divb_clean",
     "mhd_reductions", "mhd_profile", "mhd_profile_read", "mhd_last_dt", "mhd_set_tile",
     "mhd_set_launch", "mhd_get_launch", "mhd_set_final_tile", "mhd_get_final_tile",
-    "mhd_autotune", "mhd_rhs_adjoint",
+    "mhd_set_cells", "mhd_get_cells", "mhd_autotune", "mhd_rhs_adjoint",
     "PASS_NAMES", "TILES", "Context",
 ]
 
@@ -153,6 +153,10 @@ def load():
     L.mhd_set_final_tile.restype = ctypes.c_int
     L.mhd_get_final_tile.argtypes = [vp, ctypes.POINTER(i32)]
     L.mhd_get_final_tile.restype = ctypes.c_int
+    L.mhd_set_cells.argtypes = [vp, i32]
+    L.mhd_set_cells.restype = ctypes.c_int
+    L.mhd_get_cells.argtypes = [vp, ctypes.POINTER(i32)]
+    L.mhd_get_cells.restype = ctypes.c_int
     L.mhd_autotune.argtypes = [vp, _P8, _P8, i32, ctypes.POINTER(ctypes.c_double)]
     L.mhd_autotune.restype = ctypes.c_int
     L.mhd_profile.argtypes = [vp, i32]
@@ -283,6 +287,16 @@ def mhd_get_final_tile(ctx):
     t = ctypes.c_int32()
     _check(load().mhd_get_final_tile(ctx, ctypes.byref(t)), ctx)
     return t.value
+
+
+def mhd_set_cells(ctx, cells):
+    _check(load().mhd_set_cells(ctx, int(cells)), ctx)
+
+
+def mhd_get_cells(ctx):
+    c = ctypes.c_int32()
+    _check(load().mhd_get_cells(ctx, ctypes.byref(c)), ctx)
+    return c.value
 
 
 def mhd_autotune(ctx, f, dfdt, reps, *, dtype, n):
@@ -447,9 +461,11 @@ class Context:
         mhd_set_tile(self.ctx, TILES[tile] if isinstance(tile, str) else tile)
 
     def set_launch(self, tile, persistent):
+        """The march in this tile shape and mode (set_cells undoes it)."""
         mhd_set_launch(self.ctx, TILES[tile] if isinstance(tile, str) else tile, persistent)
 
     def get_launch(self):
+        """(tile, persistent) of the march, whether or not it runs (get_cells)."""
         t, m = mhd_get_launch(self.ctx)
         return {v: k for k, v in TILES.items()}[t], m
 
@@ -460,11 +476,19 @@ class Context:
     def get_final_tile(self):
         return {v: k for k, v in TILES.items()}[mhd_get_final_tile(self.ctx)]
 
+    def set_cells(self, cells):
+        """1: the stages of a small context run one thread per cell; 0: they
+        march, as after set_tile, set_launch and set_final_tile."""
+        mhd_set_cells(self.ctx, cells)
+
+    def get_cells(self):
+        return mhd_get_cells(self.ctx)
 
     def autotune(self, f, reps=3, dfdt=None):
         """Times RK stages of f in every tile shape and launch mode and keeps
         the fastest (then, possibly, another shape for pass F alone:
-        get_final_tile); returns {(tile, persistent): ms per stage} of the
+        get_final_tile), or one thread per cell where that is faster still
+        (get_cells); returns {(tile, persistent): ms per stage} of the
         uniform launches (the kept one's with pass F in its own shape)."""
         dfdt = dfdt if dfdt is not None else self.empty()
         ms = mhd_autotune(self.ctx, f, dfdt, reps, dtype=self.dtype, n=self.n)
