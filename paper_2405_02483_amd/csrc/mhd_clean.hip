@@ -145,17 +145,26 @@ void symbol_sq(int n, int count, double h, std::vector<double>& out) {
 // [y inverse] -> [x inverse] -> phi.  The z transform, the division by the
 // symbol and the inverse share one load and one store of the spectrum.  A
 // workgroup transforms `cols` lines at once (x: pairs of real rows as one
-// complex line each; y, z: neighbouring kx, up to a cache line of them) in
+// complex line each; y, z: neighbouring kx, up to a cache line of them and
+// more where they are short) in
 // place, in Stockham passes of radix 8, 4, 2, 3, 5, 7, 11, 13 whose
 // elements wait in registers across a barrier.  The kernels come in three
 // classes of radices: with 11 and 13 in the same kernel as the powers of two
 // its registers (244) would leave 2 waves a SIMD.  us per call, these
 // transforms against rocFFT with kernels of their own for div B and the
-// solve (stencils in chunks of 32 planes in both): float32 24^3 45 / 50, 64^3 60 / 64, 100x120x84 101 / 110, 128^3 108 /
-// 114, 256^3 416 / 506, but 160^3 189 / 162, 200^3 319 / 268 (170 registers);
-// float64 24^3 52 / 76, 96^3 110 / 159, 128^3 146 / 183, 256^3 775 / 914,
-// 160^3 244 / 249, 216x220x208 733 / 624.  The first call of a context:
-// 0.3-1 ms against 1.2-1.8 s in a new process (3.5 ms after that).
+// solve (and 32-plane stencils): float32 24^3 33 / 55, 64^3 36 / 65,
+// 100x100x200 112 / 129, 128^3 83 / 113, 256^3 389 / 504, 1000x40x50 100 / 112,
+// 500x20x20 41 / 53; float64 64^3 39 / 108, 96^3 79 / 157, 128^3 114 / 182, 256^3
+// 750 / 912.  Behind it: 16x256x256 float32 95 / 87 and 12x400x400 float64
+// 336 / 305 (a cache line of kx holds 9 and 7), 1000x12x12 float32 45 / 42.
+// The first call of a context: 0.3-1 ms against 1.2-1.8 s in a new process
+// (3.5 ms after that).
+//
+// Boxes with odd factors take them up to kCleanMixed cells: every box measured
+// below it but the three above is faster than before; above, with everything
+// else equal, float32 144^3 127 / 137 and 150^3 144 / 156 but 160^3 168 / 147,
+// 18x512x512 281 / 237, 200^3 255 / 254; float64 150^3 203 / 193, 160^3 217 / 202,
+// 216x220x208 562 / 589.
 constexpr int kFftThreads = 256, kFftPasses = 12;
 constexpr long long kCleanMixed = 2000000;
 // bytes of the lines of a workgroup, and elements a thread holds
@@ -179,7 +188,44 @@ template <bool INV, class T> __device__ __forceinline__ Cx<T> rot(Cx<T> a) {
   return INV ? Cx<T>{-a.y, a.x} : Cx<T>{a.y, -a.x};
 }
 
-template <int R, bool INV, class T> __device__ __forceinline__ void dft(Cx<T> (&v)[R], const Cx<T>* tw, int n) {
+// cos and sin of 2 pi m / R, m < R, of the odd radices, by their power series
+// (constants of the kernels: read from the twiddle table in LDS and with
+// integer divisions below, float32 96x192x108 took 119 us against 93).
+template <int R> struct Root { double c[R], s[R]; };
+constexpr double kPi = 3.14159265358979323846;
+constexpr double series_cos(double x) {   // |x| <= pi / 2
+  double t = 1.0, v = 1.0;
+  for (int k = 1; k <= 14; ++k) {
+    t *= -x * x / ((2 * k - 1) * (2 * k));
+    v += t;
+  }
+  return v;
+}
+constexpr double series_sin(double x) {
+  double t = x, v = x;
+  for (int k = 1; k <= 14; ++k) {
+    t *= -x * x / ((2 * k) * (2 * k + 1));
+    v += t;
+  }
+  return v;
+}
+template <int R> constexpr Root<R> roots() {
+  Root<R> r{};
+  r.c[0] = 1.0;
+  r.s[0] = 0.0;
+  for (int m = 1; m <= R / 2; ++m) {
+    // (4 m < R: an angle up to pi / 2; above, from its supplement)
+    const bool low = 4 * m < R;
+    const double x = low ? 2.0 * kPi * m / R : kPi * (R - 2 * m) / R;
+    r.c[m] = low ? series_cos(x) : -series_cos(x);
+    r.s[m] = series_sin(x);
+    r.c[R - m] = r.c[m];
+    r.s[R - m] = -r.s[m];
+  }
+  return r;
+}
+
+template <int R, bool INV, class T> __device__ __forceinline__ void dft(Cx<T> (&v)[R]) {
   if constexpr (R == 2) {
     const Cx<T> a = v[0], b = v[1];
     v[0] = a + b;
@@ -192,8 +238,8 @@ template <int R, bool INV, class T> __device__ __forceinline__ void dft(Cx<T> (&
     v[3] = b - d;
   } else if constexpr (R == 8) {
     Cx<T> e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
-    dft<4, INV, T>(e, tw, n);
-    dft<4, INV, T>(o, tw, n);
+    dft<4, INV, T>(e);
+    dft<4, INV, T>(o);
     const T h = T(0.70710678118654752440);
     const Cx<T> r1 = rot<INV>(o[1]), r3 = rot<INV>(o[3]);
     o[1] = {h * (o[1].x + r1.x), h * (o[1].y + r1.y)};
@@ -215,15 +261,15 @@ template <int R, bool INV, class T> __device__ __forceinline__ void dft(Cx<T> (&
       b[r] = v[r + 1] - v[R - 1 - r];
       out[0] = out[0] + a[r];
     }
-    const int step = n / R;
+    constexpr Root<R> W = roots<R>();
 #pragma unroll
     for (int q = 1; q <= H; ++q) {
       Cx<T> s = v[0], d = {T(0), T(0)};
 #pragma unroll
       for (int r = 1; r <= H; ++r) {
-        const Cx<T> w = tw[(r * q % R) * step];   // cos, -sin
-        s = {s.x + w.x * a[r - 1].x, s.y + w.x * a[r - 1].y};
-        d = {d.x - w.y * b[r - 1].x, d.y - w.y * b[r - 1].y};
+        const T wc = T(W.c[r * q % R]), ws = T(W.s[r * q % R]);
+        s = {s.x + wc * a[r - 1].x, s.y + wc * a[r - 1].y};
+        d = {d.x + ws * b[r - 1].x, d.y + ws * b[r - 1].y};
       }
       const Cx<T> t = rot<INV>(d);
       out[q] = s + t;
@@ -234,6 +280,10 @@ template <int R, bool INV, class T> __device__ __forceinline__ void dft(Cx<T> (&
   }
 }
 
+// t / n for t < 2^16, n < 2^16 (inv_of(n), the same in every thread, once).
+__device__ __forceinline__ unsigned inv_of(int n) { return 0xffffffffu / (unsigned)n + 1u; }
+__device__ __forceinline__ int div_by(int t, unsigned inv) { return (int)__umulhi((unsigned)t, inv); }
+
 // One Stockham pass over `cols` lines, element (i, c) at i * cp + c, in
 // place: every thread holds its butterflies in registers across the barrier.
 template <int R, bool INV, int CL, class T>
@@ -242,6 +292,7 @@ __device__ __forceinline__ void fft_pass(Cx<T>* __restrict__ l, const Cx<T>* __r
   constexpr int E = (int)(kFftLine<CL> / sizeof(Cx<T>)) / kFftThreads;   // elements per thread
   constexpr int U = (E + R - 1) / R;
   const int nb = n / R, step = nb / ns, cnt = nb << lc;
+  const unsigned ins = CL == 0 ? 0u : inv_of(ns);
   Cx<T> v[U][R];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -258,7 +309,7 @@ __device__ __forceinline__ void fft_pass(Cx<T>* __restrict__ l, const Cx<T>* __r
     const int t = (int)threadIdx.x + u * kFftThreads;
     if (t >= cnt) continue;
     const int c = t & ((1 << lc) - 1), j = t >> lc;
-    const int q = CL == 0 ? j >> __builtin_ctz((unsigned)ns) : (ns == 1 ? j : j / ns), k = j - q * ns;
+    const int q = CL == 0 ? j >> __builtin_ctz((unsigned)ns) : (ns == 1 ? j : div_by(j, ins)), k = j - q * ns;
     if (ns > 1) {
 #pragma unroll
       for (int r = 1; r < R; ++r) {
@@ -267,7 +318,7 @@ __device__ __forceinline__ void fft_pass(Cx<T>* __restrict__ l, const Cx<T>* __r
         v[u][r] = mul(v[u][r], w);
       }
     }
-    dft<R, INV, T>(v[u], tw, n);
+    dft<R, INV, T>(v[u]);
     const int o = q * ns * R + k;
 #pragma unroll
     for (int r = 0; r < R; ++r) l[(o + r * ns) * cp + c] = v[u][r];
@@ -327,7 +378,8 @@ __global__ __launch_bounds__(kFftThreads) void k_fft_x(FftAxis A, BoxDev b, cons
   Cx<T>* tw = reinterpret_cast<Cx<T>*>(lds_);
   Cx<T>* l = tw + n;
   const int row0 = (int)blockIdx.x * A.cols * 2, nh = n / 2 + 1;
-  auto line = [&](int t) { return CL == 0 ? t >> __builtin_ctz((unsigned)n) : t / n; };
+  const unsigned in = CL == 0 ? 0u : inv_of(n), inh = inv_of(nh);
+  auto line = [&](int t) { return CL == 0 ? t >> __builtin_ctz((unsigned)n) : div_by(t, in); };
   for (int t = (int)threadIdx.x; t < n; t += kFftThreads) tw[t] = tws[A.tw + t];
   if (!INV) {
     for (int t = (int)threadIdx.x; t < (n << lc); t += kFftThreads) {
@@ -342,7 +394,7 @@ __global__ __launch_bounds__(kFftThreads) void k_fft_x(FftAxis A, BoxDev b, cons
     }
   } else {
     for (int t = (int)threadIdx.x; t < (nh << lc); t += kFftThreads) {
-      const int p = t / nh, k = t - p * nh, r = row0 + 2 * p;
+      const int p = div_by(t, inh), k = t - p * nh, r = row0 + 2 * p;
       const Cx<T> zero = {T(0), T(0)};
       Cx<T> u = r < rows ? spec[(long long)r * pitch + k] : zero;
       Cx<T> v = r + 1 < rows ? spec[(long long)(r + 1) * pitch + k] : zero;
@@ -356,7 +408,7 @@ __global__ __launch_bounds__(kFftThreads) void k_fft_x(FftAxis A, BoxDev b, cons
   fft_lines<INV, CL>(l, tw, A, lc, cp);
   if (!INV) {
     for (int t = (int)threadIdx.x; t < (nh << lc); t += kFftThreads) {
-      const int p = t / nh, k = t - p * nh, r = row0 + 2 * p;
+      const int p = div_by(t, inh), k = t - p * nh, r = row0 + 2 * p;
       const Cx<T> a = l[k * cp + p], c = l[(k == 0 ? 0 : n - k) * cp + p];
       if (r < rows) spec[(long long)r * pitch + k] = {T(0.5) * (a.x + c.x), T(0.5) * (a.y - c.y)};
       if (r + 1 < rows) spec[(long long)(r + 1) * pitch + k] = {T(0.5) * (a.y + c.y), T(0.5) * (c.x - a.x)};
@@ -430,6 +482,27 @@ bool fft_axis(int n, size_t csize, FftAxis& A) {
   A.cols = 128 / (int)csize;   // a cache line of kx
   while (A.cols > 1 && (size_t)n * A.cols * csize > (A.cl < 2 ? kFftLine<0> : kFftLine<2>)) A.cols /= 2;
   return A.cols >= 4;
+}
+
+// Lines a workgroup by the box (fft_axis: what the LDS buffers hold, a cache
+// line of kx at most).  Fewer while the workgroups do not fill the device,
+// down to an element a thread: us per call before and after, float32
+// 500x20x20 91 / 41, 512x32x32 83 / 45, 250x80x100 121 / 110, 64^3 45 / 36 (x);
+// 60x60x512 109 / 104, 20x500x20 63 / 54 (y, z; 4 lines at least).  The powers
+// of two gain up to 768 workgroups (1024x64x64 135 / 129), odd factors lose
+// beyond 256 (400x60x80 127 / 134).  More for short lines while enough
+// workgroups remain: a workgroup of 16 lines of 16 holds one element a
+// thread, 512x512x16 153 / 129, float64 239 / 196.
+void fft_cols(FftAxis (&ax)[3], int nx, int ny, int nz) {
+  const long long rows = (long long)ny * nz;
+  const int nxh = nx / 2 + 1;
+  while (ax[0].cols > 1 && ax[0].n * ax[0].cols >= 512 && rows < 2LL * ax[0].cols * (ax[0].cl == 0 ? 768 : 256)) ax[0].cols /= 2;
+  for (int a = 1; a < 3; ++a) {
+    FftAxis& A = ax[a];
+    auto groups = [&](int cols) { return (long long)((nxh + cols - 1) / cols) * (a == 1 ? nz : ny); };
+    while (A.cols > 4 && A.n * A.cols >= 512 && groups(A.cols) <= 256) A.cols /= 2;
+    while (A.n * A.cols < 1024 && nxh > A.cols && groups(2 * A.cols) >= 1024) A.cols *= 2;
+  }
 }
 
 std::once_flag g_rocfft_once;
@@ -547,6 +620,7 @@ int clean_boxes(CleanState** sp, const std::vector<BoxDev>& boxes, P8<T> f, hipS
       for (int a = 0; a < 3; ++a) p.own = p.own && fft_axis(edge[a], sizeof(C), p.ax[a]);
       p.own = p.own && (b.ncell <= kCleanMixed || p.ax[0].cl + p.ax[1].cl + p.ax[2].cl == 0);
       if (p.own) {
+        fft_cols(p.ax, b.nx, b.ny, b.nzt);
         for (FftAxis& A : p.ax) {
           A.tw = (int)tw.size();
           for (int m = 0; m < A.n; ++m) {
