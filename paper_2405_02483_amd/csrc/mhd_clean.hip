@@ -465,6 +465,11 @@ __global__ __launch_bounds__(kFftThreads) void k_fft_yz(FftAxis A, const Cx<T>* 
   }
 }
 
+// Whether a workgroup holds `cols` lines of the axis (fft_pass).
+bool fft_holds(const FftAxis& A, int cols, size_t csize) {
+  return (size_t)A.n * cols * csize <= (A.cl < 2 ? kFftLine<0> : kFftLine<2>);
+}
+
 // The passes of an axis of n cells, or false: a prime above 13, or longer
 // than the LDS buffers hold four lines of.
 bool fft_axis(int n, size_t csize, FftAxis& A) {
@@ -480,7 +485,7 @@ bool fft_axis(int n, size_t csize, FftAxis& A) {
   const int top = A.radix[A.np - 1];   // (the largest prime comes last)
   A.cl = (n & (n - 1)) == 0 ? 0 : (top <= 7 ? 1 : 2);
   A.cols = 128 / (int)csize;   // a cache line of kx
-  while (A.cols > 1 && (size_t)n * A.cols * csize > (A.cl < 2 ? kFftLine<0> : kFftLine<2>)) A.cols /= 2;
+  while (A.cols > 1 && !fft_holds(A, A.cols, csize)) A.cols /= 2;
   return A.cols >= 4;
 }
 
@@ -493,7 +498,7 @@ bool fft_axis(int n, size_t csize, FftAxis& A) {
 // beyond 256 (400x60x80 127 / 134).  More for short lines while enough
 // workgroups remain: a workgroup of 16 lines of 16 holds one element a
 // thread, 512x512x16 153 / 129, float64 239 / 196.
-void fft_cols(FftAxis (&ax)[3], int nx, int ny, int nz) {
+void fft_cols(FftAxis (&ax)[3], int nx, int ny, int nz, size_t csize) {
   const long long rows = (long long)ny * nz;
   const int nxh = nx / 2 + 1;
   while (ax[0].cols > 1 && ax[0].n * ax[0].cols >= 512 && rows < 2LL * ax[0].cols * (ax[0].cl == 0 ? 768 : 256)) ax[0].cols /= 2;
@@ -501,7 +506,8 @@ void fft_cols(FftAxis (&ax)[3], int nx, int ny, int nz) {
     FftAxis& A = ax[a];
     auto groups = [&](int cols) { return (long long)((nxh + cols - 1) / cols) * (a == 1 ? nz : ny); };
     while (A.cols > 4 && A.n * A.cols >= 512 && groups(A.cols) <= 256) A.cols /= 2;
-    while (A.n * A.cols < 1024 && nxh > A.cols && groups(2 * A.cols) >= 1024) A.cols *= 2;
+    while (A.n * A.cols < 1024 && nxh > A.cols && groups(2 * A.cols) >= 1024 && fft_holds(A, 2 * A.cols, csize))
+      A.cols *= 2;
   }
 }
 
@@ -620,7 +626,7 @@ int clean_boxes(CleanState** sp, const std::vector<BoxDev>& boxes, P8<T> f, hipS
       for (int a = 0; a < 3; ++a) p.own = p.own && fft_axis(edge[a], sizeof(C), p.ax[a]);
       p.own = p.own && (b.ncell <= kCleanMixed || p.ax[0].cl + p.ax[1].cl + p.ax[2].cl == 0);
       if (p.own) {
-        fft_cols(p.ax, b.nx, b.ny, b.nzt);
+        fft_cols(p.ax, b.nx, b.ny, b.nzt, sizeof(C));
         for (FftAxis& A : p.ax) {
           A.tw = (int)tw.size();
           for (int m = 0; m < A.n; ++m) {

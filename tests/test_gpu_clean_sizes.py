@@ -2,7 +2,7 @@
 to which div B is formed in the x transform (a power of two, and odd lengths
 with an odd number of rows), above the cells up to which lengths with odd
 factors take the library's own transforms, long x with few rows (few lines a
-workgroup), short y and z (many).  Each with a small box in the same context,
+workgroup), short y and z (many, up to what a workgroup holds).  Each with a small box in the same context,
 so that the shared scratch and row pitch are those of the other.  Against the
 float64 oracle, with the bounds of the other cleaning tests (1e-12 and 1e-5
 relative L2 per component)."""
@@ -20,7 +20,9 @@ pytestmark = pytest.mark.gpu
 PRM = dict(gamma=5.0 / 3.0, mu=1.0)
 BIG = [(128, 128, 64), (125, 105, 99), (150, 135, 105)]
 LINES = [(500, 9, 20), (512, 9, 6), (1000, 12, 7), (728, 7, 9), (1024, 6, 33), (33, 100, 100), (256, 256, 16),
-         (300, 7, 150), (66, 6, 1024), (40, 12, 250)]
+         (300, 7, 150), (66, 6, 1024), (40, 12, 250),
+         # as many lines of a short axis as a workgroup holds of each class
+         (256, 512, 11), (128, 1024, 13), (300, 260, 22), (256, 512, 7), (300, 512, 8)]
 
 
 def _fields(shape, seed):
