@@ -18,10 +18,12 @@
 // consecutive workgroups of an XCD take consecutive cells, so that the
 // stencils' repeated reads hit in L1 (x, y) and in that XCD's L2 (z).
 //
-// The passes are bound by the arrays they stream: 88 with the core
-// terms, some 190 reads and writes per cell and stage, against 1700 of an
-// operation-by-operation program, which this replaced (each operation a
-// pass over 2 to 5 arrays, 160 launches a stage).  One step's adjoint:
+// With the core terms 88 arrays, some 190 reads and writes per cell and
+// stage, against 1700 of an operation-by-operation program, which this
+// replaced (each operation a pass over 2 to 5 arrays, 160 launches a stage).
+// The pointwise passes are bound by those bytes, the edges' and vectors'
+// gathers (half the time) by the caches' latency, at 2.9 TB/s.  One step's
+// adjoint:
 // 128^3 float32 23.06 -> 3.14 ms, 64^3 float32 with walls and every
 // optional term 14.37 -> 2.35 ms; a 6-step float64 rollout of 48^3 with its
 // gradient 63.2 -> 6.5 ms.

@@ -472,7 +472,12 @@ static int set_tile(mhd_ctx* c, int tile) {
 // 129 / 154, 72^3 174 / 202, 80^3 205 / 206.  With walls every z stencil
 // also decides for the table or the constants, cell by cell: float32 64x64x74
 // 122 / 163, 80x80x90 197 / 195, 96x96x106 317 / 239; float64 48x48x58 108 /
-// 155, 64x64x74 189 / 195, 72x72x82 234 / 234.
+// 155, 64x64x74 189 / 195, 72x72x82 234 / 234.  The terms move the crossing
+// little: float32 96^3 with the maximum over five cells 217 / 214, with the
+// ln P gradient 213 / 215, with all the optional terms this path has 273 /
+// 261 (80^3 168 / 189), with the continuity alone 176 / 187; 78x78x88 between
+// walls 190 / 205, all terms 243 / 258; stretched 72x72x82 168 / 206, all terms
+// 211 / 251; float64 72^3 all terms 250 / 279, 66x66x76 between walls 283 / 323.
 static bool cells_fit(const mhd_ctx* c) {
   bool walls = false;
   for (const BoxDev& d : c->h_boxes) walls |= d.wall != 0;

@@ -226,27 +226,24 @@ CELL_KERNEL k_cedges(CK<T> K) {
   const bool lnp = (tm & T_PRES) && (tm & T_LNP);
   const T* pav = K.ws.lnpav + b.poff;
   const T lpa = lnp ? pav[c.k] : T(0);
-  auto in = [&](int id, const T* a, int x, int y) {
-    (void)id;
-    return c.ld(a, c.d[X][x + 3] + c.d[Y][y + 3]);
-  };
+  auto in = [&](const T* a, int x, int y) { return c.ld(a, c.d[X][x + 3] + c.d[Y][y + 3]); };
   auto S = [&](int q, int x, int y) -> T {
     switch (q) {
-      case DQ_PX: return in(q, F(1), x, y);
-      case DQ_PY: return in(q, F(2), x, y);
-      case DQ_E: return in(q, F(4), x, y);
-      case DQ_BX: return in(q, F(5), x, y);
-      case DQ_BY: return in(q, F(6), x, y);
-      case DQ_UX: return in(q, A(WC_UX), x, y);
-      case DQ_UY: return in(q, A(WC_UY), x, y);
-      case DQ_NU: return in(q, A(WC_NU), x, y);
-      case DQ_EM: return in(q, A(WC_EM), x, y);
-      case DQ_LEM: return in(q, A(WC_LEM), x, y);
-      case DQ_RXD: return in(q, A(WC_RX), x, y);
-      case DQ_RYD: return in(q, A(WC_RY), x, y);
-      case DQ_XL: return in(q, A(WC_XL), x, y);
+      case DQ_PX: return in(F(1), x, y);
+      case DQ_PY: return in(F(2), x, y);
+      case DQ_E: return in(F(4), x, y);
+      case DQ_BX: return in(F(5), x, y);
+      case DQ_BY: return in(F(6), x, y);
+      case DQ_UX: return in(A(WC_UX), x, y);
+      case DQ_UY: return in(A(WC_UY), x, y);
+      case DQ_NU: return in(A(WC_NU), x, y);
+      case DQ_EM: return in(A(WC_EM), x, y);
+      case DQ_LEM: return in(A(WC_LEM), x, y);
+      case DQ_RXD: return in(A(WC_RX), x, y);
+      case DQ_RYD: return in(A(WC_RY), x, y);
+      case DQ_XL: return in(A(WC_XL), x, y);
       case DQ_RHO: return c.ld(F(0));
-      case DQ_LQ: return log(ph.gamma1 * in(q, F(4), x, y)) - lpa;
+      case DQ_LQ: return log(ph.gamma1 * in(F(4), x, y)) - lpa;
       default: return c.ld(A(WS_D));
     }
   };

@@ -90,7 +90,8 @@ enum ZClass : int {
   ZC_COUNT
 };
 // planes a chunk's march takes besides its own (P marches only its own: one
-// plane's worth of set-up)
+// plane's worth of set-up; A1's ten read their own column alone, A2's do not:
+// 9, 5 and 3 for the class gave the same times)
 constexpr int kZLead[ZC_COUNT] = {9, 5, 1, 5};
 
 struct ZLaunch {
