@@ -766,7 +766,7 @@ __device__ __forceinline__ void face_back(const Cell<T, W>& c, const VArgs<T>& K
 // takes the roles from `role` on.
 VJP_KERNEL_WAVES(5) k_edge_face(VK<T, ALL> K, int role) {
   VJP_CELL
-  switch (role + (int)blockIdx.y) {
+  switch ((ALL ? 0 : role) + (int)blockIdx.y) {
     case 0: edge_back<ALL, X>(c, K, nd, A, Wt, S); break;
     case 1: edge_back<ALL, Y>(c, K, nd, A, Wt, S); break;
     case 2: edge_back<ALL, Z>(c, K, nd, A, Wt, S); break;
@@ -1035,7 +1035,11 @@ VJP_KERNEL_WAVES(6) k_vector_back(VK<T, ALL> K) {
 VJP_KERNEL k_scalar_back(VK<T, ALL> K) {
   VJP_CELL
   const Phys<T>& ph = K.ph;
-  T eb = T(0), rb = T(0);
+  T eb = T(0), rb = T(0), rho = T(1), em = T(1);
+  if (ALL || nd.any(T_EDIFF)) {
+    rho = c.ld(S(0));
+    em = c.ld(A(VA_EM));
+  }
   if (ALL || nd.eb()) eb += c.ld(A(VA_EB));
   if (ALL || nd.any(T_ADV))
     eb = eb + c.template dnT<X>(A(VA_XE)) + c.template dnT<Y>(A(VA_XE + 1)) + c.template dnT<Z>(A(VA_XE + 2));
@@ -1052,7 +1056,6 @@ VJP_KERNEL k_scalar_back(VK<T, ALL> K) {
     rb = rb + c.template dnT<X>(A(VA_RB)) + c.template dnT<Y>(A(VA_RB + 1)) + c.template dnT<Z>(A(VA_RB + 2));
   if (tm & T_GRAV) rb -= ph.gz * c.template dnT<Z>(Wt(3));
   if (tm & T_EDIFF) {
-    const T rho = c.ld(S(0)), em = c.ld(A(VA_EM));
     T mb = c.template dnT<X>(A(VA_XEM)) + c.template dnT<Y>(A(VA_XEM + 1)) + c.template dnT<Z>(A(VA_XEM + 2)) +
            (c.template ddnT<X>(A(VA_DLEM)) + c.template ddnT<Y>(A(VA_DLEM + 1)) + c.template ddnT<Z>(A(VA_DLEM + 2))) /
                em;
