@@ -257,8 +257,11 @@ template <class T, bool W> __device__ __forceinline__ double h_shock(const Cell<
 VJP_KERNEL k_prim(VK<T, ALL> K) {
   VJP_CELL
   const T* rho = S(0);
-  if (ALL || nd.faces()) {
-    const T rx = c.template dn<X>(rho), ry = c.template dn<Y>(rho), rz = c.template dn<Z>(rho);
+  const bool faces = ALL || nd.faces(), diff = ALL || nd.any(T_EDIFF), logs = diff || nd.order2();
+  const T rx = faces ? c.template dn<X>(rho) : T(1), ry = faces ? c.template dn<Y>(rho) : T(1),
+          rz = faces ? c.template dn<Z>(rho) : T(1);
+  const T em = logs ? c.ld(S(4)) / c.ld(rho) : T(1);
+  if (faces) {
     c.st(A(VA_R), rx);
     c.st(A(VA_R + 1), ry);
     c.st(A(VA_R + 2), rz);
@@ -266,11 +269,8 @@ VJP_KERNEL k_prim(VK<T, ALL> K) {
     c.st(A(VA_U + 1), c.ld(S(2)) / ry);
     c.st(A(VA_U + 2), c.ld(S(3)) / rz);
   }
-  if (ALL || nd.any(T_EDIFF) || nd.order2()) {
-    const T em = c.ld(S(4)) / c.ld(rho);
-    if (ALL || nd.any(T_EDIFF)) c.st(A(VA_EM), em);
-    c.st(A(VA_LEM), log(em));
-  }
+  if (diff) c.st(A(VA_EM), em);
+  if (logs) c.st(A(VA_LEM), log(em));
   if (ALL || nd.heat()) {
     c.st(A(VA_XWE), c.template upT<X>(Wt(4)));
     c.st(A(VA_YWE), c.template upT<Y>(Wt(4)));
@@ -845,17 +845,12 @@ VJP_KERNEL_WAVES(5) k_centre_back(VK<T, ALL> K, int mb) {
   const T rho = c.ld(S(0)), e = c.ld(S(4)), nt = ALL || nd.any(T_VISC) ? c.ld(A(VA_NT)) : T(0), we = c.ld(Wt(4));
   const T P = ph.gamma1 * e;
   T Db = T(0), vDb = T(0), rb = T(0), Pb = T(0);
-  T vsb[3] = {}, sb[3] = {}, cp[3] = {}, cu[3] = {}, cb[3] = {}, uc[3] = {}, gf[3] = {};
-  if (ALL || nd.cu()) {
-    uc[0] = c.template up<X>(A(VA_U));
-    uc[1] = c.template up<Y>(A(VA_U + 1));
-    uc[2] = c.template up<Z>(A(VA_U + 2));
-  }
-  if (ALL || nd.any(T_VISC | T_ADV)) {
-    gf[0] = c.template ddnT<X>(Wt(1));
-    gf[1] = c.template ddnT<Y>(Wt(2));
-    gf[2] = c.template ddnT<Z>(Wt(3));
-  }
+  T vsb[3] = {}, sb[3] = {}, cp[3] = {}, cu[3] = {}, cb[3] = {};
+  const bool vel = ALL || nd.cu(), flux = ALL || nd.any(T_VISC | T_ADV);
+  const T uc[3] = {vel ? c.template up<X>(A(VA_U)) : T(0), vel ? c.template up<Y>(A(VA_U + 1)) : T(0),
+                   vel ? c.template up<Z>(A(VA_U + 2)) : T(0)};
+  const T gf[3] = {flux ? c.template ddnT<X>(Wt(1)) : T(0), flux ? c.template ddnT<Y>(Wt(2)) : T(0),
+                   flux ? c.template ddnT<Z>(Wt(3)) : T(0)};
   if (tm & T_VISC) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
