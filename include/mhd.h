@@ -244,10 +244,11 @@ int mhd_rhs(mhd_ctx* ctx, void* const f[8], void* const dfdt[8]);
 
 /* mhd_rhs for callers that cannot allocate device memory: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  The
- * result is that of mhd_rhs, bit for bit (same kernels, same order).  The
- * call allocates nothing: its per-call scratch (stage workspace, per-plane
- * tables, queue counters) lives in a static device array of 64 MiB that
- * each GPU holds from the first mhd_init on it until the process ends; the
+ * result is that of mhd_rhs, bit for bit (where one thread per cell runs but
+ * its 44 arrays do not fit, the march takes over).  The call allocates
+ * nothing: its per-call scratch (stage workspace, per-plane tables, queue
+ * counters) lives in a static device array of 64 MiB that each GPU holds
+ * from the first mhd_init on it until the process ends; the
  * context's tables come from mhd_init.  That fits about 490,000 cells of
  * float32 or 245,000 of float64 (ghost planes included; 34 arrays per cell,
  * 40 with MHD_T_QUENCH, 42 with MHD_T_ORDER2, plus small per-plane
