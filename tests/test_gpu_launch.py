@@ -77,3 +77,33 @@ def test_null_arguments():
     v = ctypes.c_int32()
     assert L.mhd_set_cells(None, 0) == lib.MHD_EINVAL
     assert L.mhd_get_cells(None, ctypes.byref(v)) == lib.MHD_EINVAL
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_the_tables_follow_each_set_call(dtype):
+    """Whatever shapes the passes had before, a shape gives what a new context
+    set to it gives: RHS, step, time step and reductions."""
+    from paper_2405_02483_amd.lib import Context, TILES
+    (f, box, prm), (g, small, _) = inputs.turbulent(n=24, seed=3), inputs.turbulent(n=12, seed=4)
+    boxes, fs = [box, small, box], [f, g, f]
+
+    def results(ctx):
+        fd = ctx.upload(fs)
+        d = ctx.rhs(fd)
+        red = ctx.reductions(fd, d)
+        out = [t.clone() for t in d]
+        ctx.step(fd, 0.0)
+        return out + [t.clone() for t in fd], red, ctx.last_dt()
+
+    ctx = Context(boxes, prm, dtype=dtype)
+    for tile in TILES:
+        for final in TILES:
+            new = Context(boxes, prm, dtype=dtype)
+            for c in (ctx, new):
+                c.set_tile(tile)
+                c.set_final_tile(final)
+                assert c.get_launch()[0] == tile and c.get_final_tile() == final
+            (a, ra, ta), (b, rb, tb) = results(ctx), results(new)
+            assert all(torch.equal(x, y) for x, y in zip(a, b)) and ra == rb and ta == tb
+            new.close()
+    ctx.close()
